@@ -7,10 +7,10 @@
 //             the spreading records (stencil base, fractional offsets,
 //             friction impulse) plus the chain's stencil bounding box.
 //   k_lb      the fused step over a work list: interior rows and tiles do
-//             pull streaming, collide and store (periodic boxes also gather
-//             the spread force of their chains); boundary items store the
-//             boundary equilibrium populations that point into the interior.
-//   k_force   after k_lb, one workgroup per chain of a non-periodic box: the
+//             pull streaming, collide and store (in-place streaming also
+//             gathers the spread force of the chains); boundary items store
+//             the boundary equilibrium populations that point into the interior.
+//   k_force   after k_lb with two buffers, one workgroup per chain: the
 //             nodes of the chain's stencil box collide again with the spread
 //             force gathered from the records (fixed bead order, no atomics);
 //             on steps without a check pass its last workgroup ends the step.
@@ -182,6 +182,7 @@ __global__ __launch_bounds__(CB, 3) void k_chain(const BoxDesc* __restrict__ box
 
   // stencil at t_n: R = anchor + rel, anchor split into integer + fractional parts
   int base[3] = {0, 0, 0};
+  int ubase[3] = {0, 0, 0};  // PER: before the wrap of periodic axes
   R dl[3] = {0, 0, 0};
   if (act) {
     const R rr[3] = {rx, ry, rz};
@@ -192,6 +193,7 @@ __global__ __launch_bounds__(CB, 3) void k_chain(const BoxDesc* __restrict__ box
       const R r = (R)c.af[a] + rr[a];
       const R fl = floor(r);
       base[a] = c.ai[a] + (int)fl;
+      if (PER) ubase[a] = base[a];
       dl[a] = r - fl;
       if (!((b.pmask >> a) & 1)) {
         if (base[a] < 1 || base[a] + 1 > n3[a] - 2) out = true;
@@ -407,27 +409,45 @@ __global__ __launch_bounds__(CB, 3) void k_chain(const BoxDesc* __restrict__ box
     rec_dp[3 * gj] = dpx;
     rec_dp[3 * gj + 1] = dpy;
     rec_dp[3 * gj + 2] = dpz;
-    atomicMin(&sbox[0], base[0]);
-    atomicMin(&sbox[1], base[1]);
-    atomicMin(&sbox[2], base[2]);
-    atomicMax(&sbox[3], base[0] + 1);
-    atomicMax(&sbox[4], base[1] + 1);
-    atomicMax(&sbox[5], base[2] + 1);
-  }
-  __syncthreads();
-  if (j == 0) {
-    if (b.pmask) {
-      // wrapped stencils: every tile of the box checks this chain
-      bbox[6 * ci + 0] = 0;
-      bbox[6 * ci + 1] = 0;
-      bbox[6 * ci + 2] = 0;
-      bbox[6 * ci + 3] = b.nx - 1;
-      bbox[6 * ci + 4] = b.ny - 1;
-      bbox[6 * ci + 5] = b.nz - 1;
-    } else {
-      for (int a = 0; a < 6; a++) bbox[6 * ci + a] = sbox[a];
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+      const int lo = PER ? ubase[a] : base[a];
+      atomicMin(&sbox[a], lo);
+      atomicMax(&sbox[3 + a], lo + 1);
     }
   }
+  __syncthreads();
+  if (j < 3) {
+    int lo = sbox[j], hi = sbox[3 + j];
+    if (PER && ((b.pmask >> j) & 1)) {
+      // periodic axis: lo in [0, n), hi = lo + extent - 1 (n or more where the
+      // range wraps), the whole axis at most
+      const int n = j == 0 ? b.nx : (j == 1 ? b.ny : b.nz);
+      const int ext = hi - lo < n - 1 ? hi - lo : n - 1;
+      lo = hi - lo < n - 1 ? ((lo % n) + n) % n : 0;
+      hi = lo + ext;
+    }
+    bbox[6 * ci + j] = lo;
+    bbox[6 * ci + 3 + j] = hi;
+  }
+}
+
+// Whether coordinate v lies in the stencil range lo..hi of an axis of n nodes
+// (a range of a periodic axis may wrap: hi >= n).
+template <bool PER>
+__device__ __forceinline__ bool in_range(int v, int lo, int hi, int n, bool periodic) {
+  if (PER && periodic) {
+    const int d = v - lo < 0 ? v - lo + n : v - lo;
+    return (unsigned)d <= (unsigned)(hi - lo);
+  }
+  return v >= lo && v <= hi;
+}
+
+// Whether a tile's range t..t+e-1 of an axis meets a stencil range.
+template <bool PER>
+__device__ __forceinline__ bool ranges_meet(int t, int e, int lo, int hi, int n, bool periodic) {
+  if (lo <= t + e - 1 && hi >= t) return true;
+  return PER && periodic && hi >= n && hi - n >= t;  // the wrapped part 0..hi-n
 }
 
 // ----------------------------------------------------- boundary helpers
@@ -654,7 +674,8 @@ __device__ __forceinline__ void collide_ext(R d[Q], R gx, R gy, R gz, R rho0, R 
 // Spread force g(x) = - sum_j w_jx dP_j at node (x, y, z): chains whose stencil
 // box overlaps the tile (cmask), beads in fixed order, no atomics.
 // UNROLL: beads whose records are loaded together (1 inside the fused step,
-// where registers are short)
+// where registers are short; 4 in k_force: one at a time its pass over a
+// 16-bead chain takes 9.8 us instead of 6.7)
 template <typename R, bool PER, int UNROLL>
 __device__ __forceinline__ void gather_force(const LbArgs& A, const BoxDesc& b,
                                              unsigned long long cmask, int x, int y, int z, R& gx,
@@ -668,28 +689,44 @@ __device__ __forceinline__ void gather_force(const LbArgs& A, const BoxDesc& b,
     if (!((cmask >> c) & 1ull)) continue;
     const int gc = b.chain_first + c;
     const int* bb = A.bbox + 6 * gc;
-    if (z < bb[2] || z > bb[5]) continue;
-    if (!(x >= bb[0] && x <= bb[3] && y >= bb[1] && y <= bb[4])) continue;
+    if (!in_range<PER>(z, bb[2], bb[5], b.nz, b.pmask & 4)) continue;
+    if (!(in_range<PER>(x, bb[0], bb[3], b.nx, b.pmask & 1) &&
+          in_range<PER>(y, bb[1], bb[4], b.ny, b.pmask & 2)))
+      continue;
     const ChainDesc& ch = A.chains[gc];
-    // no branch per bead (a bead whose stencil misses the node subtracts a
-    // selected zero), so the record loads of consecutive beads overlap
-#pragma unroll UNROLL
-    for (int jb = ch.first; jb < ch.first + ch.nb; jb++) {
-      const int4 bs = A.rec_base[jb];
-      int ox = x - bs.x, oy = y - bs.y, oz = z - bs.z;
-      if (PER) {
-        if ((b.pmask & 1) && ox < 0) ox += b.nx;
-        if ((b.pmask & 2) && oy < 0) oy += b.ny;
-        if ((b.pmask & 4) && oz < 0) oz += b.nz;
+    // the records of UNROLL beads loaded before the first is used, and no
+    // branch per bead (a bead whose stencil misses the node, or the last bead
+    // read again past the end, subtracts a selected zero)
+    const int last = ch.first + ch.nb - 1;
+    for (int j0 = ch.first; j0 <= last; j0 += UNROLL) {
+      int4 bs[UNROLL];
+      double d[UNROLL][3], p[UNROLL][3];
+#pragma unroll
+      for (int u = 0; u < UNROLL; u++) {
+        const int jb = j0 + u < last ? j0 + u : last;
+        bs[u] = A.rec_base[jb];
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+          d[u][a] = rd[3 * jb + a];
+          p[u][a] = rp[3 * jb + a];
+        }
       }
-      const bool hit = (unsigned)ox <= 1u && (unsigned)oy <= 1u && (unsigned)oz <= 1u;
-      const double w = (ox ? rd[3 * jb] : 1.0 - rd[3 * jb]) *
-                       (oy ? rd[3 * jb + 1] : 1.0 - rd[3 * jb + 1]) *
-                       (oz ? rd[3 * jb + 2] : 1.0 - rd[3 * jb + 2]);
-      const double px = rp[3 * jb], py = rp[3 * jb + 1], pz = rp[3 * jb + 2];
-      sx -= hit ? w * px : 0.0;
-      sy -= hit ? w * py : 0.0;
-      sz -= hit ? w * pz : 0.0;
+#pragma unroll
+      for (int u = 0; u < UNROLL; u++) {
+        int ox = x - bs[u].x, oy = y - bs[u].y, oz = z - bs[u].z;
+        if (PER) {
+          if ((b.pmask & 1) && ox < 0) ox += b.nx;
+          if ((b.pmask & 2) && oy < 0) oy += b.ny;
+          if ((b.pmask & 4) && oz < 0) oz += b.nz;
+        }
+        const bool hit =
+            j0 + u <= last && (unsigned)ox <= 1u && (unsigned)oy <= 1u && (unsigned)oz <= 1u;
+        const double w = (ox ? d[u][0] : 1.0 - d[u][0]) * (oy ? d[u][1] : 1.0 - d[u][1]) *
+                         (oz ? d[u][2] : 1.0 - d[u][2]);
+        sx -= hit ? w * p[u][0] : 0.0;
+        sy -= hit ? w * p[u][1] : 0.0;
+        sz -= hit ? w * p[u][2] : 0.0;
+      }
     }
   }
   gx += (R)sx;
@@ -1209,9 +1246,10 @@ constexpr int lb_min_waves(int S, int COLL) {
 // its instantiations ask for two resident waves per SIMD.
 constexpr int lb_min_waves_ext(int S, int COLL, bool EXT) { return EXT ? 2 : lb_min_waves(S, COLL); }
 
-// AA: the instantiation for in-place streaming on boxes without periodic
-// axes (no row items, no stores of the two-buffer step); the periodic
-// instantiation takes either streaming from A.aa.
+// AA: the instantiation for in-place streaming (no row items, no stores of the
+// two-buffer step; the chains' force gathered here, whose registers the
+// two-buffer instantiations do not pay: with both in one periodic kernel a
+// 96^3 FP32 step took 135 us against 107).
 template <int S, int COLL, bool PER, int BS = WG, bool EXT = false, bool AA = false>
 __global__ __launch_bounds__(BS, lb_min_waves_ext(S, COLL, EXT)) void k_lb(LbArgs A) {
   using St = Store<S>;
@@ -1230,7 +1268,7 @@ __global__ __launch_bounds__(BS, lb_min_waves_ext(S, COLL, EXT)) void k_lb(LbArg
   const T* __restrict__ srcA = (const T*)(par ? A.a1 : A.a0);
   T* __restrict__ dstA = (T*)(par ? A.a0 : A.a1);
   const bool pre = A.pre != 0;
-  const bool aa = AA || (PER && A.aa);
+  constexpr bool aa = AA;
 
   for (int e = blockIdx.x; e < A.n_entries; e += gridDim.x) {
     const int ii = A.order[e];
@@ -1260,14 +1298,14 @@ __global__ __launch_bounds__(BS, lb_min_waves_ext(S, COLL, EXT)) void k_lb(LbArg
         else face_rows<S, 2, BS>(b, it, dst, step, rho0);
       }
     } else if (it.kind == ITEM_TILE) {
-      // chains whose stencil box overlaps this tile, periodic boxes only (the
-      // chains of the other boxes couple in k_force)
+      // in-place streaming: chains whose stencil box overlaps this tile (with
+      // two buffers the chains couple in k_force)
       unsigned long long cmask = 0;
-      const bool gather = (PER && b.pmask) || aa;
-      for (int c = 0; gather && c < b.chain_count && c < MAX_BOX_CHAINS; c++) {
+      for (int c = 0; aa && c < b.chain_count && c < MAX_BOX_CHAINS; c++) {
         const int* bb = A.bbox + 6 * (b.chain_first + c);
-        const bool ov = bb[0] <= it.x0 + it.ex - 1 && bb[3] >= it.x0 && bb[1] <= it.y0 + it.ey - 1 &&
-                        bb[4] >= it.y0 && bb[2] <= it.z0 + it.ez - 1 && bb[5] >= it.z0;
+        const bool ov = ranges_meet<PER>(it.x0, it.ex, bb[0], bb[3], b.nx, b.pmask & 1) &&
+                        ranges_meet<PER>(it.y0, it.ey, bb[1], bb[4], b.ny, b.pmask & 2) &&
+                        ranges_meet<PER>(it.z0, it.ez, bb[2], bb[5], b.nz, b.pmask & 4);
         if (ov) cmask |= 1ull << c;
       }
       if (!PER && !AA && b.fast) {
@@ -1330,13 +1368,17 @@ __global__ __launch_bounds__(BS, lb_min_waves_ext(S, COLL, EXT)) void k_lb(LbArg
 // evaluating the boundary source with dependent loads.  Node k of a box:
 // k = side (ny-2)(nz-2) + (z-1)(ny-2) + (y-1), velocity at xface[xf_off + 3k].
 // ------------------------------------------------------------ chain forcing
-// Chains of non-periodic boxes couple to the fluid in a pass of their own,
+// With two buffers the chains couple to the fluid in a pass of their own,
 // right after the fused step: the interior nodes of each chain's stencil box
 // collide again from the same pre-collision populations (the fused step reads
 // one buffer and writes the other, so they are intact), now with the spread
 // force of every chain of the box whose stencil box holds the node (Guo
 // forcing, the same collision), and overwrite what the fused step stored
-// there.  The fused step then never gathers spread force for these boxes.
+// there.  The fused step then never gathers spread force.  (Periodic boxes
+// did, every node of the box testing every bead, a wrapped stencil box being
+// taken to cover the whole box: a step of a 96^3 FP32 box with four 32-bead
+// chains took 1461 us, 1414 us of it k_lb; with this pass 98 us, k_lb 48 us
+// and the pass 10 us.)
 // Where the stencil boxes of two chains overlap, both workgroups compute the
 // node and store the same values.  One workgroup per chain.  On steps that
 // have no check pass it also ends the step (step index advance), which then
@@ -1358,7 +1400,7 @@ __global__ __launch_bounds__(WG) void k_force(LbArgs A) {
   for (int a = 0; a < 6; a++) bb[a] = A.bbox[6 * gc + a];
   put_stamp(A.stamp_after);
   if (latched) return;  // uniform: set before this launch or not at all
-  if (!b.pmask) {       // periodic boxes gather inside the fused step
+  if (PER || !b.pmask) {
     const int par = (int)(step & 1);
     const T* __restrict__ src = (const T*)(par ? A.a1 : A.a0) + b.off;
     T* __restrict__ dst = (T*)(par ? A.a0 : A.a1) + b.off;
@@ -1370,7 +1412,12 @@ __global__ __launch_bounds__(WG) void k_force(LbArgs A) {
     const int n = (lx > 0 && ly > 0 && lz > 0) ? lx * ly * lz : 0;
 #pragma unroll 1
     for (int p = threadIdx.x; p < n; p += WG) {
-      const int x = bb[0] + p % lx, y = bb[1] + (p / lx) % ly, z = bb[2] + p / (lx * ly);
+      int x = bb[0] + p % lx, y = bb[1] + (p / lx) % ly, z = bb[2] + p / (lx * ly);
+      if (PER) {  // a stencil box may wrap on periodic axes
+        if ((b.pmask & 1) && x >= b.nx) x -= b.nx;
+        if ((b.pmask & 2) && y >= b.ny) y -= b.ny;
+        if ((b.pmask & 4) && z >= b.nz) z -= b.nz;
+      }
       if (!is_interior(b, x, y, z)) continue;
       R d[Q];
       load_pre<S, PER>(src, b, x, y, z, A.pre != 0, d);

@@ -20,6 +20,7 @@ void launch_lb(dim3 g, hipStream_t s, const LbArgs& a) {
 
 template <int S, int C>
 LbLaunch pick_lb(bool periodic, bool ext, bool in_place) {
+  if (periodic && in_place) return ext ? launch_lb<S, C, true, true, true> : launch_lb<S, C, true, false, true>;
   if (periodic) return ext ? launch_lb<S, C, true, true, false> : launch_lb<S, C, true, false, false>;
   if (in_place) return ext ? launch_lb<S, C, false, true, true> : launch_lb<S, C, false, false, true>;
   return ext ? launch_lb<S, C, false, true, false> : launch_lb<S, C, false, false, false>;

@@ -853,7 +853,7 @@ void enqueue_step(lb_ctx* ctx, hipStream_t s, int pre, const hipEvent_t* ev3,
   // on a step known to have no check pass, k_force's last workgroup ends it
   // (in-place streaming: the fused step gathers every chain's force itself)
   const bool force_ends = chains && chk == 0 && !ctx->aa;
-  if (chains && !ctx->aa) {  // spread force of the chains of non-periodic boxes
+  if (chains && !ctx->aa) {  // spread force of the chains
     LbArgs f = t;
     f.advance = force_ends ? 1 : 0;
     ctx->force_fn(dim3((unsigned)ctx->ch.size()), s, f);
