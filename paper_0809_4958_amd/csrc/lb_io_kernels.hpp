@@ -26,12 +26,16 @@ __global__ __launch_bounds__(WG) void k_finalize(LbArgs A) {
   if (tid == 0) s_bad = 0x7fffffff;
   __syncthreads();
   if (check) {
-    for (int bx = tid; bx < A.n_boxes; bx += WG) {
+    // a wavefront per box: lane l adds partials l, l + 64, ..., then the lanes
+    for (int bx = tid >> 6; bx < A.n_boxes; bx += WG / 64) {
       double s[4] = {0.0, 0.0, 0.0, 0.0};
-      for (int q = A.check_off[bx]; q < A.check_off[bx + 1]; q++) {
+      for (int q = A.check_off[bx] + (tid & 63); q < A.check_off[bx + 1]; q += 64) {
 #pragma unroll
         for (int m = 0; m < 4; m++) s[m] += A.partials[4 * q + m];
       }
+#pragma unroll
+      for (int m = 0; m < 4; m++) s[m] = wave_sum(s[m]);
+      if (tid & 63) continue;
       const double M = A.rho0 * A.boxes[bx].interior + s[0];
       double* mm = A.mass_mom + 5 * bx;
       mm[0] = (double)(step + 1);

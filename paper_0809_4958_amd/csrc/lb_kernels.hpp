@@ -569,7 +569,7 @@ struct LbArgs {
   const int* bbox;
   DevState* st;
   double* partials;        // [n_check][4] mass/momentum partials of k_check
-  const int4* check_items; // k_check workgroups: box, first plane, end plane
+  const int4* check_items; // k_check workgroups: box, first row, end row (row z ny + y)
   const int* check_off;    // [n_boxes + 1] first k_check workgroup of each box
   double* mass_mom;        // [n_boxes][5]
   long long* stamp_first;  // timed graphs: start of the step's first kernel,
@@ -1502,9 +1502,9 @@ __global__ __launch_bounds__(WG) void k_xface(LbArgs A) {
 // On check steps ((n+1) % K == 0), after the fused step: the interior's mass
 // and momentum at t_{n+1}, i.e. every stored population of the arena just
 // written whose target node x + c_i is interior (FP64).  Workgroup w covers
-// the planes [cz0, cz1) of box cbox, one FP64 partial of each sum per
-// workgroup (wave shuffle -> LDS, fixed order); k_finalize adds the partials
-// of a box in workgroup order.  A separate pass, so the step itself is the
+// a range of rows of a box, one FP64 partial of each sum per workgroup (wave
+// shuffle -> LDS, fixed order); k_finalize adds the partials of a box in a
+// fixed order.  A separate pass, so the step itself is the
 // same arithmetic on every step.
 template <int S, bool PER>
 __global__ __launch_bounds__(WG) void k_check(LbArgs A) {
@@ -1518,7 +1518,7 @@ __global__ __launch_bounds__(WG) void k_check(LbArgs A) {
   const bool latched =
       __hip_atomic_load(&A.st->err_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != ERR_NONE;
   const long long step = A.st->step;
-  const int4 cw = A.check_items[w];  // box, first plane, end plane
+  const int4 cw = A.check_items[w];  // box, first row, end row
   const BoxDesc b = A.boxes[cw.x];
   put_stamp(A.stamp_after);
   if (latched) return;
@@ -1536,10 +1536,10 @@ __global__ __launch_bounds__(WG) void k_check(LbArgs A) {
     // whatever a boundary node holds in them never enters a sum.
     constexpr int NV = 8 * (int)sizeof(T) / 16;
     const int cpr = b.nx / 8;
-    const int n_chunks = (cw.z - cw.y) * b.ny * cpr;
+    const int n_chunks = (cw.z - cw.y) * cpr;
     for (int p = tid; p < n_chunks; p += WG) {
-      const int row = p / cpr, c = p - row * cpr;
-      const int zz = row / b.ny, y = row - zz * b.ny, z = cw.y + zz;
+      const int r = p / cpr, c = p - r * cpr, row = cw.y + r;
+      const int z = row / b.ny, y = row - z * b.ny;
       const int x0 = 8 * c;
       uint4 raw[Q][NV];
 #pragma unroll
@@ -1568,12 +1568,11 @@ __global__ __launch_bounds__(WG) void k_check(LbArgs A) {
       }
     }
   } else {
-    // node by node; a slab holds fewer than 2^31 nodes (32-bit indices);
-    // loads first and selects after, as above
-    const int n_slab = (cw.z - cw.y) * b.ny * b.nx;
+    // node by node (32-bit indices); loads first and selects after, as above
+    const int n_slab = (cw.z - cw.y) * b.nx;
     for (int p = tid; p < n_slab; p += WG) {
-      const int row = p / b.nx, x = p - row * b.nx;
-      const int zz = row / b.ny, y = row - zz * b.ny, z = cw.y + zz;
+      const int r = p / b.nx, x = p - r * b.nx, row = cw.y + r;
+      const int z = row / b.ny, y = row - z * b.ny;
       T raw[Q];
 #pragma unroll
       for (int i = 0; i < Q; i++) raw[i] = arena[aidx(b, i, x, y, z)];

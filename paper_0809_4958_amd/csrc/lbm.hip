@@ -32,7 +32,7 @@ using namespace lbdev;
 
 namespace {
 
-constexpr int BND_CHUNK = 512;
+constexpr int BND_CHUNK = 256;
 
 struct BoxHost {
   lb_box dim;
@@ -47,6 +47,7 @@ struct BoxHost {
   void* d_bc = nullptr;
   const void* ring = nullptr;  // LEARNED: caller-owned device ring (not freed here)
   int ex = 0, ey = 0, ez = 0;  // tile shape
+  int fez = 4;                 // row boxes: workgroup iterations per face-row item
   int n_rect = 0;
   int rect_face[MAX_RECT] = {};
   int rect_cnt[MAX_RECT] = {};
@@ -194,7 +195,7 @@ struct lb_ctx {
   BoxDesc* d_boxes = nullptr;
   Item* d_items = nullptr;
   int* d_order = nullptr;
-  int4* d_check_items = nullptr;   // k_check workgroups: box, first plane, end plane
+  int4* d_check_items = nullptr;   // k_check workgroups: box, first row, end row
   int* d_check_off = nullptr;      // [n_boxes + 1]
   double* d_partials = nullptr;    // [n_check][4]
   int n_check = 0;
@@ -340,6 +341,31 @@ void default_tile(BoxHost& b) {
   b.ez = b.vec ? 4 : std::min(b.iz, 16);
 }
 
+// Small contexts: the default items above leave most of the chip idle (a 32^3
+// FP64 box was 4 tiles and 12 boundary chunks for 256 CUs), so items shrink
+// until the context has about SPLIT_ITEMS of them, down to one position per
+// thread and one plane or workgroup iteration.  k_lb with the default items,
+// 512, 2048 and 4096: 32^3 FP64 61 / 8.7 / 8.6 / 8.6 us, 64^3 FP16 22.5 /
+// 13.1 / 13.1 / 13.1, 96^3 periodic FP32 48 / 24.6 / 24.0 / 24.0, 128^3 FP32
+// 69.7 / 70.2 / 66.9 / 66.8, four 121^3 FP32 380 / 380 / 346 / 323; contexts
+// of 35 million nodes and more keep the default items.
+constexpr int SPLIT_ITEMS = 4096;
+void split_small(lb_ctx* ctx) {
+  int64_t work = 0;
+  for (auto& b : ctx->bx) work += b.interior;
+  const int64_t per = std::max<int64_t>(1, work / SPLIT_ITEMS);  // nodes per item
+  for (auto& b : ctx->bx) {
+    if (b.vec) {
+      const int64_t iter = (int64_t)WG * row_nodes(ctx->S, b.vw);
+      b.ez = (int)std::max<int64_t>(1, std::min<int64_t>(b.ez, per / iter));
+      b.fez = b.ez;
+    } else {
+      while (b.ez > 1 && 2 * (int64_t)b.ex * b.ey * b.ez > 3 * per) b.ez = (b.ez + 1) / 2;
+      if (2 * (int64_t)b.ex * b.ey > 3 * per) b.ey = std::max(1, std::min(b.ey, WG / b.ex));
+    }
+  }
+}
+
 std::string box_key(const lb_ctx* ctx, const BoxHost& b) {
   std::ostringstream s;
   s << "S" << ctx->S << "C" << ctx->coll << "_" << b.dim.nx << "x" << b.dim.ny << "x" << b.dim.nz
@@ -461,7 +487,7 @@ lb_status build_tables(lb_ctx* ctx, int grid_override) {
       // face rows: planes z = 0 and nz-1, then rows y = 0 and ny-1 of each
       // interior plane
       const int64_t fgroups = (int64_t)L * (2 * b.dim.ny + 2 * (b.dim.nz - 2));
-      const int64_t fper = (int64_t)WG * 4;
+      const int64_t fper = (int64_t)WG * b.fez;
       for (int64_t g0 = 0; g0 < fgroups; g0 += fper) {
         Item it{};
         it.box = (int)bi;
@@ -522,16 +548,17 @@ lb_status build_tables(lb_ctx* ctx, int grid_override) {
   bool ok = true;
   ctx->d_items = dalloc_t<Item>(ctx, items.size(), &ok);
   ctx->d_order = dalloc_t<int>(ctx, order.size(), &ok);
-  // mass/momentum check work list: slabs of whole planes, about 64k nodes each
+  // mass/momentum check work list: ranges of rows, about 1/128 of a box each
+  // within 4k..64k nodes (of the box alone, so that its record does not depend
+  // on its batch).  Slabs of 64k nodes were 14 workgroups on a 96^3 box: 674 us.
   std::vector<int4> check;
   std::vector<int> check_off(ctx->bx.size() + 1, 0);
   for (size_t bi = 0; bi < ctx->bx.size(); bi++) {
     const BoxHost& b = ctx->bx[bi];
     check_off[bi] = (int)check.size();
-    // whole planes of about 64k nodes; a slab stays below 2^31 nodes (32-bit
-    // indices in k_check)
-    const int zc = std::max(1, 65536 / std::max(1, b.dim.nx * b.dim.ny));
-    for (int z = 0; z < b.dim.nz; z += zc) check.push_back(make_int4((int)bi, z, std::min(b.dim.nz, z + zc), 0));
+    const int64_t nodes = std::max<int64_t>(4096, std::min<int64_t>(65536, b.nn / 128));
+    const int rows = b.dim.ny * b.dim.nz, rc = (int)std::max<int64_t>(1, nodes / b.dim.nx);
+    for (int r = 0; r < rows; r += rc) check.push_back(make_int4((int)bi, r, std::min(rows, r + rc), 0));
   }
   check_off[ctx->bx.size()] = (int)check.size();
   ctx->n_check = (int)check.size();
@@ -1175,6 +1202,7 @@ lb_status lb_init(const lb_config* cfg, lb_ctx** out) {
   select_launchers(ctx);
   ctx->check_fn = ctx->S == 0 ? pick_check<0>(ctx->per)
                               : (ctx->S == 1 ? pick_check<1>(ctx->per) : pick_check<2>(ctx->per));
+  split_small(ctx);
   load_tune_cache(ctx);
   if (upload_boxes(ctx) != LB_OK) {
     lb_free(ctx);

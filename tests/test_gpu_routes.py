@@ -77,3 +77,25 @@ def test_chains_around_periodic_edges(dims, pmask, storage, streaming):
                 u0=1e-3 * rng.standard_normal(dims[::-1] + (3,)), chains=chains, reduce_every=7)
     run_case(case, storage, steps, f"wrapped chains {dims} {pmask} {streaming}",
              streaming=lbm.STREAM_AA if streaming == "in_place" else lbm.STREAM_AB)
+
+
+@pytest.mark.parametrize("storage,tol", [("f64", 1e-13), ("f32", 1e-6), ("f16", 1e-5)])
+@pytest.mark.parametrize("dims", [(40, 80, 96), (41, 79, 83)])
+def test_check_record_of_many_row_ranges(dims, storage, tol):
+    """Mass and momentum summed over more row ranges than a wavefront has lanes
+    (16-byte chunks and node by node).  The bounds are those of the check
+    records in test_gpu_parity and test_gpu_aa, relative to the mass."""
+    rng = np.random.default_rng(37)
+    case = Case(dims, collision=oracle.MRT, tau=0.7,
+                bc=(oracle.BC_AFFINE, inputs.ou_strain(4, rng, corr_steps=20.0, rms=1e-4), 0, 1, 0),
+                u0=1e-3 * rng.standard_normal(dims[::-1] + (3,)), reduce_every=2)
+    say("case check record", dims, storage)
+    ob = case.oracle_box()
+    assert ob.step(2) == 0
+    ctx = make_ctx(case, storage)
+    ctx.step(2)
+    mm_o, mm_g = ob.mass_mom(), ctx.read(0, lbm.F_MASS_MOM)
+    say(mm_o, mm_g - mm_o)
+    assert mm_g[0] == mm_o[0] == 2
+    assert np.abs(mm_g[1:] - mm_o[1:]).max() < tol * mm_o[1]
+    ctx.close()
