@@ -1,11 +1,11 @@
 // lb_kernels.hpp -- gfx950 kernels of the fine-box lattice-Boltzmann step.
 //
-//   k_chain   one workgroup per chain (one wavefront when the chains have at
-//             most 64 beads): trilinear interpolation of the fluid
+//   k_chain   one workgroup per chain: trilinear interpolation of the fluid
 //             velocity at each bead from the pre-collision moments, the MD
 //             substeps (FENE, exact friction update, centre-of-mass pin) and
 //             the spreading records (stencil base, fractional offsets,
-//             friction impulse) plus the chain's stencil bounding box.
+//             friction impulse), the chain's stencil bounding box and the
+//             spread force of its nodes.
 //   k_lb      the fused step over a work list: interior rows and tiles do
 //             pull streaming, collide and store (in-place streaming also
 //             gathers the spread force of the chains); boundary items store
@@ -99,6 +99,15 @@ __device__ __forceinline__ void wave_sums(R (&v)[N]) {
   for (int k = 0; k < N; k++) v[k] = lane63(v[k]);
 }
 
+// Sum over each group of eight lanes, returned to all of them, in one fixed
+// order: pairs, pairs of pairs (quad permutes), then the other half.
+__device__ __forceinline__ double sum8(double v) {
+  v += dpp_get<0xB1, 0xf>(v);   // quad_perm 1,0,3,2
+  v += dpp_get<0x4E, 0xf>(v);   // quad_perm 2,3,0,1
+  v += dpp_get<0x141, 0xf>(v);  // row_half_mirror
+  return v;
+}
+
 // x-face boundary velocities of one work item by one wavefront (defined with
 // k_xface below)
 template <int S>
@@ -108,39 +117,58 @@ __device__ __forceinline__ void xface_wave(const BoxDesc* __restrict__ boxes,
                                            long long* stamp);
 
 // ---------------------------------------------------------------- chain
-// CB threads per chain (one per bead): 64 when no chain has more than 64
-// beads (one wavefront: the MD substeps exchange values by cross-lane
-// operations, with no barriers), else 256 (through LDS).
+// Nodes of a chain's stencil box whose spread force k_chain leaves in its table
+// (24 KB per chain); a larger box (a stretched chain) is gathered bead by bead.
+constexpr int GTAB = 1024;
+
+// One workgroup per chain, MB the most beads of a chain (64 or 256).  The pass
+// is a chain of dependent latencies, so its parts are spread over the waves:
+//   interpolation  eight lanes per bead, a stencil corner each (19 loads in
+//                  flight per lane, one round for 32 beads; a lane that took
+//                  all corners of its bead in two rounds of four held 76
+//                  loads, and with FP64 populations spilled 244 bytes)
+//   MD substeps    a thread per bead; with MB = 64 one wavefront, exchanging
+//                  neighbours by cross-lane moves without barriers; else
+//                  through LDS, one barrier per substep
+//   node force     the spread force of every node of the stencil box, the
+//                  beads' records read from LDS and split over the waves, so
+//                  that k_force and the in-place step read three numbers per
+//                  node instead of looping over the beads
+// The centre-of-mass pin needs no sums inside the substeps: the bond forces
+// cancel, so the mean velocity after a friction update is (1 - decay) times
+// the mean of u plus decay times the mean before, which is zero from the
+// second substep on (thermal noise has no such form and is summed).
+// Measured per launch, 128^3 FP32 with 64 beads 25.4 -> 13.8 us, 32^3 FP64 with
+// 16 beads 21.4 -> 11.0 us, 384^3 FP16 with 16 chains of 256 beads 46 -> 36 us;
+// k_force in the same boxes 13.3 -> 4.9, 6.7 -> 4.4 and 53 -> 8.5 us.  256
+// threads instead of 512 take 18.0 us on the 128^3 box (two rounds of
+// interpolation), 512 instead of 1024 with 256 beads 38-41 us.
 // Workgroups n_chains and up compute the x-face boundary velocities of the
-// step instead (CB / 64 work items each), so the two independent pieces of
+// step instead (a work item per wavefront), so the two independent pieces of
 // work before the fused step share one launch and run side by side.
-template <int S, bool PER, int CB, bool TH = false>
-__global__ __launch_bounds__(CB, 3) void k_chain(const BoxDesc* __restrict__ boxes,
-                                              const ChainDesc* __restrict__ chains,
-                                              const typename Store<S>::T* __restrict__ a0,
-                                              const typename Store<S>::T* __restrict__ a1,
-                                              double* __restrict__ pos,
-                                              double* __restrict__ vel,
-                                              int total_beads, int4* __restrict__ rec_base,
-                                              double* __restrict__ rec_d,
-                                              double* __restrict__ rec_dp,
-                                              int* __restrict__ bbox, DevState* __restrict__ st,
-                                              double rho0_d, int pre, long long* stamp,
-                                              int n_chains, const int4* __restrict__ xf_items,
-                                              int n_xf_items, float* __restrict__ xface,
-                                              unsigned key0, unsigned key1) {
+constexpr int chain_threads(int MB) { return MB == 64 ? 512 : 1024; }
+
+template <int S, bool PER, int MB, bool TH = false>
+__global__ __launch_bounds__(chain_threads(MB), 4) void k_chain(
+    const BoxDesc* __restrict__ boxes, const ChainDesc* __restrict__ chains,
+    const typename Store<S>::T* __restrict__ a0, const typename Store<S>::T* __restrict__ a1,
+    double* __restrict__ pos, double* __restrict__ vel, int total_beads,
+    int4* __restrict__ rec_base, double* __restrict__ rec_d, double* __restrict__ rec_dp,
+    int* __restrict__ bbox, double* __restrict__ gtab, DevState* __restrict__ st, double rho0,
+    int pre, long long* stamp, int n_chains, const int4* __restrict__ xf_items, int n_xf_items,
+    float* __restrict__ xface, unsigned key0, unsigned key1) {
   // Chain arithmetic in FP64 for every storage.  The friction impulses of a
   // chain's beads are dominated by their bond forces, which cancel between
   // neighbouring beads on the nodes the spreading shares: the node force is
   // a small difference of large terms, and FP32 impulses and stencil weights
   // cost 1e-4 of the fluid velocity near 32 collapsed 256-bead chains over
   // 2,000 steps (FP32 storage, against 5e-8 without chains).
-  using R = double;
   using RP = typename Store<S>::R;
-  const int ci = blockIdx.x;
+  constexpr int NT = chain_threads(MB), NW = NT / 64;
+  const int ci = blockIdx.x, tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   if (ci >= n_chains) {
-    const int item = (ci - n_chains) * (CB / 64) +
-                     __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int item = (ci - n_chains) * NW + wave;
     if (item < n_xf_items) xface_wave<S>(boxes, xf_items, item, xface, st, nullptr);
     return;
   }
@@ -150,26 +178,26 @@ __global__ __launch_bounds__(CB, 3) void k_chain(const BoxDesc* __restrict__ box
   const bool latched = __hip_atomic_load(&st->err_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != ERR_NONE;
   put_stamp(stamp);
   if (latched) return;
-  const R rho0 = (R)rho0_d;
   const long long step = st->step;
   const int par = (int)(step & 1);
   const typename Store<S>::T* src = (par ? a1 : a0) + b.off;
-  const int j = threadIdx.x;
-  const bool act = j < c.nb;
-  const int gj = c.first + j;
+  const size_t pin = (size_t)par * total_beads * 3, pout = (size_t)(par ^ 1) * total_beads * 3;
 
-  __shared__ R spx[CB], spy[CB], spz[CB];
-  __shared__ R bfx[CB], bfy[CB], bfz[CB];
-  __shared__ R red[3][CB];
-  __shared__ int sflag;
+  __shared__ double su[MB][3], sd[MB][3], sdp[MB][3];  // fluid velocity, stencil fraction, impulse
+  __shared__ int sbase[MB][3];                         // stencil base (wrapped)
+  __shared__ double spart[NW][64][3];                  // node-force partials, centre-of-mass sums
+  __shared__ double spos[MB == 64 ? 1 : 2][MB == 64 ? 1 : MB][3];  // bead positions by substep parity
+  __shared__ int sflag, sover[2];  // stencil out; bond overflow by substep parity
   __shared__ int sbox[6];
-  if (j == 0) {
-    sflag = 0;
+  if (tid == 0) {
+    sflag = sover[0] = sover[1] = 0;
     sbox[0] = sbox[1] = sbox[2] = 0x7fffffff;
     sbox[3] = sbox[4] = sbox[5] = -0x7fffffff;
   }
-  R rx = 0, ry = 0, rz = 0, vx = 0, vy = 0, vz = 0;
-  const size_t pin = (size_t)par * total_beads * 3, pout = (size_t)(par ^ 1) * total_beads * 3;
+  // bead tid of the MD substeps
+  const bool act = tid < c.nb;
+  const int gj = c.first + tid;
+  double rx = 0, ry = 0, rz = 0, vx = 0, vy = 0, vz = 0;
   if (act) {
     rx = pos[pin + 3 * gj];
     ry = pos[pin + 3 * gj + 1];
@@ -180,20 +208,21 @@ __global__ __launch_bounds__(CB, 3) void k_chain(const BoxDesc* __restrict__ box
   }
   __syncthreads();
 
-  // stencil at t_n: R = anchor + rel, anchor split into integer + fractional parts
-  int base[3] = {0, 0, 0};
-  int ubase[3] = {0, 0, 0};  // PER: before the wrap of periodic axes
-  R dl[3] = {0, 0, 0};
-  if (act) {
-    const R rr[3] = {rx, ry, rz};
+  // fluid velocity at t_n: lane group 8 k .. 8 k + 7 takes the eight corners of
+  // a bead's stencil, weight x j/rho each, summed in a fixed order
+  const int lay = pre == 2 ? aa_layout(step) : pre;
+  for (int t = tid; t < 8 * c.nb; t += NT) {
+    const int bead = t >> 3, o0 = t & 1, o1 = (t >> 1) & 1, o2 = (t >> 2) & 1;
     const int n3[3] = {b.nx, b.ny, b.nz};
+    int base[3], ub[3];
+    double dl[3];
     bool out = false;
 #pragma unroll
     for (int a = 0; a < 3; a++) {
-      const R r = (R)c.af[a] + rr[a];
-      const R fl = floor(r);
-      base[a] = c.ai[a] + (int)fl;
-      if (PER) ubase[a] = base[a];
+      // R = anchor + rel, the anchor split into integer and fractional parts
+      const double r = c.af[a] + pos[pin + 3 * (c.first + bead) + a];
+      const double fl = floor(r);
+      base[a] = ub[a] = c.ai[a] + (int)fl;
       dl[a] = r - fl;
       if (!((b.pmask >> a) & 1)) {
         if (base[a] < 1 || base[a] + 1 > n3[a] - 2) out = true;
@@ -201,198 +230,227 @@ __global__ __launch_bounds__(CB, 3) void k_chain(const BoxDesc* __restrict__ box
         base[a] = ((base[a] % n3[a]) + n3[a]) % n3[a];
       }
     }
-    if (out) atomicOr(&sflag, 1);
-  }
-  __syncthreads();
-  if (sflag) {
-    if (j == 0) atomicMin(&st->err_key, (ci << 4) | EC_BEAD_OUT);
-    return;
-  }
-
-  // fluid velocity at the bead: sum over the 8 corners of weight x j/rho, in
-  // corner order, four corners at a time (their loads in flight together).
-  // All eight at once took 214 VGPRs.  The kernel is compiled for three
-  // waves per SIMD (168 VGPRs with the FP64 chain arithmetic, a few spilled),
-  // so that the x-face waves sharing its launch run three per SIMD, not two
-  // (measured 27.6 against 30.2 us for the launch on the batch).
-  R ux = 0, uy = 0, uz = 0;
-  if (act) {
-#pragma unroll 1
-    for (int half = 0; half < 2; half++)
-#pragma unroll
-    for (int c4 = 0; c4 < 4; c4++) {
-      const int cc = 4 * half + c4;
-      const int o0 = cc & 1, o1 = (cc >> 1) & 1, o2 = (cc >> 2) & 1;
+    double ux = 0, uy = 0, uz = 0;
+    if (!out) {
       int qx = base[0] + o0, qy = base[1] + o1, qz = base[2] + o2;
       if (PER) {
         if (b.pmask & 1) qx = wrapc(qx, b.nx);
         if (b.pmask & 2) qy = wrapc(qy, b.ny);
         if (b.pmask & 4) qz = wrapc(qz, b.nz);
       }
-      const R w = (o0 ? dl[0] : (R)1 - dl[0]) * (o1 ? dl[1] : (R)1 - dl[1]) *
-                  (o2 ? dl[2] : (R)1 - dl[2]);
       RP d[Q];
-      load_pre<S, PER>(src, b, qx, qy, qz, pre == 2 ? aa_layout(step) : pre, d);
-      R drho = 0, jx = 0, jy = 0, jz = 0;
+      load_pre<S, PER>(src, b, qx, qy, qz, lay, d);
+      double drho = 0, jx = 0, jy = 0, jz = 0;
 #pragma unroll
       for (int i = 0; i < Q; i++) {
         drho += d[i];
-        if (CX[i]) jx += (R)CX[i] * d[i];
-        if (CY[i]) jy += (R)CY[i] * d[i];
-        if (CZ[i]) jz += (R)CZ[i] * d[i];
+        if (CX[i]) jx += (double)CX[i] * d[i];
+        if (CY[i]) jy += (double)CY[i] * d[i];
+        if (CZ[i]) jz += (double)CZ[i] * d[i];
       }
-      const R wr = w / (rho0 + drho);
-      ux += wr * jx;
-      uy += wr * jy;
-      uz += wr * jz;
+      const double w = (o0 ? dl[0] : 1.0 - dl[0]) * (o1 ? dl[1] : 1.0 - dl[1]) *
+                       (o2 ? dl[2] : 1.0 - dl[2]) / (rho0 + drho);
+      ux = w * jx;
+      uy = w * jy;
+      uz = w * jz;
+    }
+    ux = sum8(ux);
+    uy = sum8(uy);
+    uz = sum8(uz);
+    if ((t & 7) == 0) {
+      if (out) atomicOr(&sflag, 1);
+      su[bead][0] = ux;
+      su[bead][1] = uy;
+      su[bead][2] = uz;
+#pragma unroll
+      for (int a = 0; a < 3; a++) {
+        sbase[bead][a] = base[a];
+        sd[bead][a] = dl[a];
+        const int lo = PER ? ub[a] : base[a];
+        atomicMin(&sbox[a], lo);
+        atomicMax(&sbox[3 + a], lo + 1);
+      }
     }
   }
+  __syncthreads();
+  if (sflag) {
+    if (tid == 0) atomicMin(&st->err_key, (ci << 4) | EC_BEAD_OUT);
+    return;
+  }
 
-  // MD substeps.  With one wavefront per chain (CB = 64) the neighbour's
-  // position, the neighbour's bond force, the FENE overflow flag and the
-  // centre-of-mass sums move between lanes by cross-lane operations, with no
-  // barriers (the sums in the fixed DPP order of wave_sums); otherwise
-  // through LDS (a fixed-order tree).
-  constexpr bool WAVE = CB == 64;
-  const R h = (R)1 / (R)c.substeps;
-  const R decay = (R)c.decay;
-  const R mass = (R)c.mass, fk = (R)c.fene_k;
-  const R r02 = (R)(c.fene_r0 * c.fene_r0);
+  // MD substeps
+  constexpr bool WAVE = MB == 64;  // all beads in wavefront 0
+  const double h = 1.0 / c.substeps;
+  const double decay = c.decay, mass = c.mass, fk = c.fene_k;
+  const double r02 = c.fene_r0 * c.fene_r0;
   // reciprocals once: the substeps' dependent chain then holds one division
   // (the FENE factor) instead of five
-  const R izeta = (R)1 / (R)c.zeta, ir02 = (R)1 / r02, inb = (R)1 / (R)c.nb;
-  // FENE force of the bond to the next bead (separation e); false when the
-  // bond has reached its maximum extension
-  auto fene = [&](R ex, R ey, R ez, R& fx, R& fy, R& fz) -> bool {
-    const R r2 = ex * ex + ey * ey + ez * ez;
+  const double izeta = 1.0 / c.zeta, ir02 = 1.0 / r02, inb = 1.0 / c.nb;
+  // FENE force of a bond of separation e; false when it has reached its
+  // maximum extension
+  auto fene = [&](double ex, double ey, double ez, double& fx, double& fy, double& fz) -> bool {
+    const double r2 = ex * ex + ey * ey + ez * ez;
     if (r2 >= r02) return false;
-    const R fac = fk / ((R)1 - r2 * ir02);
+    const double fac = fk / (1.0 - r2 * ir02);
     fx = fac * ex;
     fy = fac * ey;
     fz = fac * ez;
     return true;
   };
-  R dpx = 0, dpy = 0, dpz = 0;
+  double dpx = 0, dpy = 0, dpz = 0;
   bool overflow = false;
-  for (int s = 0; s < c.substeps; s++) {
-    R fx = 0, fy = 0, fz = 0;  // bond j -> j+1
-    R gx = 0, gy = 0, gz = 0;  // bond j-1 -> j
-    if constexpr (WAVE) {
-      // next bead's position (wave_shl:1: lane j reads lane j+1)
-      const R qx = dpp_get<0x130, 0xf>(rx), qy = dpp_get<0x130, 0xf>(ry),
-              qz = dpp_get<0x130, 0xf>(rz);
-      bool bad = false;
-      if (act && j + 1 < c.nb) bad = !fene(qx - rx, qy - ry, qz - rz, fx, fy, fz);
-      if (__any(bad)) {
-        overflow = true;
-        break;
-      }
-      // previous bead's bond force (wave_shr:1: lane j reads lane j-1)
-      gx = dpp_get<0x138, 0xf>(fx);
-      gy = dpp_get<0x138, 0xf>(fy);
-      gz = dpp_get<0x138, 0xf>(fz);
-    } else {
-      spx[j] = rx;
-      spy[j] = ry;
-      spz[j] = rz;
-      __syncthreads();
-      if (act && j + 1 < c.nb && !fene(spx[j + 1] - rx, spy[j + 1] - ry, spz[j + 1] - rz, fx, fy, fz))
-        atomicOr(&sflag, 2);
-      bfx[j] = fx;
-      bfy[j] = fy;
-      bfz[j] = fz;
-      __syncthreads();
-      if (sflag) {
-        overflow = true;
-        break;
-      }
-      if (j > 0) {
-        gx = bfx[j - 1];
-        gy = bfy[j - 1];
-        gz = bfz[j - 1];
-      }
-    }
+  if (!WAVE || wave == 0) {
+    double ux = 0, uy = 0, uz = 0;
     if (act) {
-      R Fx = fx, Fy = fy, Fz = fz;
-      if (j > 0) {
-        Fx -= gx;
-        Fy -= gy;
-        Fz -= gz;
-      }
-      const R tx = ux + Fx * izeta, ty = uy + Fy * izeta, tz = uz + Fz * izeta;
-      R nvx = tx + (vx - tx) * decay, nvy = ty + (vy - ty) * decay, nvz = tz + (vz - tz) * decay;
-      if constexpr (TH) {
-        // Langevin noise of the exact friction update: the Ornstein-Uhlenbeck
-        // kick of the substep, from the Philox counter (bead index in the box,
-        // box, step, 16 + substep)
-        unsigned cc[4] = {(unsigned)(c.bead0 + j), (unsigned)b.index, (unsigned)step, 16u + (unsigned)s};
-        philox4x32(cc, key0, key1);
-        const double kick = c.kick;
-        nvx += (R)(kick * unit_uniform(cc[0]));
-        nvy += (R)(kick * unit_uniform(cc[1]));
-        nvz += (R)(kick * unit_uniform(cc[2]));
-      }
-      dpx += mass * (nvx - vx) - Fx * h;
-      dpy += mass * (nvy - vy) - Fy * h;
-      dpz += mass * (nvz - vz) - Fz * h;
-      vx = nvx;
-      vy = nvy;
-      vz = nvz;
-      rx += h * vx;
-      ry += h * vy;
-      rz += h * vz;
+      ux = su[tid][0];
+      uy = su[tid][1];
+      uz = su[tid][2];
     }
-    if (c.fix_com && WAVE) {
-      // fixed-order sums of velocity and relative position, all six at once
-      // (the position sum does not depend on the velocity correction)
-      R t[6] = {act ? vx : (R)0, act ? vy : (R)0, act ? vz : (R)0,
-                act ? rx : (R)0, act ? ry : (R)0, act ? rz : (R)0};
+    // means over the beads of u, and of velocity and relative position before
+    // the first substep
+    double mu[3] = {0, 0, 0}, mv[3] = {0, 0, 0}, mr[3] = {0, 0, 0};
+    if (c.fix_com && !TH) {
+      double t[9] = {ux, uy, uz, vx, vy, vz, rx, ry, rz};
       wave_sums(t);
-      vx -= t[0] * inb;
-      vy -= t[1] * inb;
-      vz -= t[2] * inb;
-      rx -= t[3] * inb;
-      ry -= t[4] * inb;
-      rz -= t[5] * inb;
-    } else if (c.fix_com) {
-      // fixed-order tree sums of velocity and relative position
-#pragma unroll 1
-      for (int pass = 0; pass < 2; pass++) {
-        R sx = act ? (pass ? rx : vx) : (R)0;
-        R sy = act ? (pass ? ry : vy) : (R)0;
-        R sz = act ? (pass ? rz : vz) : (R)0;
-        red[0][j] = sx;
-        red[1][j] = sy;
-        red[2][j] = sz;
+      if constexpr (!WAVE) {
+        if (lane < 9) {
+          double v = t[0];
+#pragma unroll
+          for (int k = 1; k < 9; k++) v = lane == k ? t[k] : v;
+          spart[wave][lane][0] = v;
+        }
         __syncthreads();
-        for (int o = CB / 2; o > 0; o >>= 1) {
-          if (j < o) {
-            red[0][j] += red[0][j + o];
-            red[1][j] += red[1][j + o];
-            red[2][j] += red[2][j + o];
+#pragma unroll
+        for (int k = 0; k < 9; k++) {
+          t[k] = spart[0][k][0];
+          for (int w = 1; w < NW; w++) t[k] += spart[w][k][0];
+        }
+      }
+#pragma unroll
+      for (int a = 0; a < 3; a++) {
+        mu[a] = t[a] * inb * (1.0 - decay);
+        mv[a] = mu[a] + t[3 + a] * inb * decay;
+        mr[a] = t[6 + a] * inb;
+      }
+    }
+    for (int s = 0; s < c.substeps; s++) {
+      double fx = 0, fy = 0, fz = 0;  // bond j -> j+1
+      double gx = 0, gy = 0, gz = 0;  // bond j-1 -> j
+      bool bad = false;
+      if constexpr (WAVE) {
+        // next bead's position (wave_shl:1: lane j reads lane j+1)
+        const double qx = dpp_get<0x130, 0xf>(rx), qy = dpp_get<0x130, 0xf>(ry),
+                     qz = dpp_get<0x130, 0xf>(rz);
+        if (act && tid + 1 < c.nb) bad = !fene(qx - rx, qy - ry, qz - rz, fx, fy, fz);
+        if (__any(bad)) {
+          overflow = true;
+          break;
+        }
+        // previous bead's bond force (wave_shr:1: lane j reads lane j-1)
+        gx = dpp_get<0x138, 0xf>(fx);
+        gy = dpp_get<0x138, 0xf>(fy);
+        gz = dpp_get<0x138, 0xf>(fz);
+      } else {
+        // both bonds from the neighbours' positions (the same bits on either
+        // side).  An overflow is seen behind the next barrier, by all threads
+        // alike: the flag read here is written again only behind the barrier
+        // after this one
+        double(*p)[3] = spos[s & 1];
+        if (act) {
+          p[tid][0] = rx;
+          p[tid][1] = ry;
+          p[tid][2] = rz;
+        }
+        __syncthreads();
+        if (sover[(s & 1) ^ 1]) {
+          overflow = true;
+          break;
+        }
+        if (act && tid + 1 < c.nb) bad = !fene(p[tid + 1][0] - rx, p[tid + 1][1] - ry, p[tid + 1][2] - rz, fx, fy, fz);
+        if (act && tid > 0) bad |= !fene(rx - p[tid - 1][0], ry - p[tid - 1][1], rz - p[tid - 1][2], gx, gy, gz);
+        if (bad) atomicOr(&sover[s & 1], 1);
+      }
+      if (act) {
+        double Fx = fx, Fy = fy, Fz = fz;
+        if (tid > 0) {
+          Fx -= gx;
+          Fy -= gy;
+          Fz -= gz;
+        }
+        const double tx = ux + Fx * izeta, ty = uy + Fy * izeta, tz = uz + Fz * izeta;
+        double nvx = tx + (vx - tx) * decay, nvy = ty + (vy - ty) * decay, nvz = tz + (vz - tz) * decay;
+        if constexpr (TH) {
+          // Langevin noise of the exact friction update: the Ornstein-Uhlenbeck
+          // kick of the substep, from the Philox counter (bead index in the box,
+          // box, step, 16 + substep)
+          unsigned cc[4] = {(unsigned)(c.bead0 + tid), (unsigned)b.index, (unsigned)step, 16u + (unsigned)s};
+          philox4x32(cc, key0, key1);
+          const double kick = c.kick;
+          nvx += kick * unit_uniform(cc[0]);
+          nvy += kick * unit_uniform(cc[1]);
+          nvz += kick * unit_uniform(cc[2]);
+        }
+        dpx += mass * (nvx - vx) - Fx * h;
+        dpy += mass * (nvy - vy) - Fy * h;
+        dpz += mass * (nvz - vz) - Fz * h;
+        vx = nvx;
+        vy = nvy;
+        vz = nvz;
+        rx += h * vx;
+        ry += h * vy;
+        rz += h * vz;
+      }
+      if (c.fix_com && !TH) {
+        // mean position after the move: the mean before (zero from the second
+        // substep on) plus h times the mean velocity
+        vx -= mv[0];
+        vy -= mv[1];
+        vz -= mv[2];
+        rx -= mr[0] + h * mv[0];
+        ry -= mr[1] + h * mv[1];
+        rz -= mr[2] + h * mv[2];
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+          mv[a] = mu[a];
+          mr[a] = 0.0;
+        }
+      } else if (c.fix_com) {
+        // sums of velocity and relative position, all six at once
+        double t[6] = {act ? vx : 0.0, act ? vy : 0.0, act ? vz : 0.0,
+                       act ? rx : 0.0, act ? ry : 0.0, act ? rz : 0.0};
+        wave_sums(t);
+        if constexpr (!WAVE) {
+          if (lane < 6) {
+            double v = t[0];
+#pragma unroll
+            for (int k = 1; k < 6; k++) v = lane == k ? t[k] : v;
+            spart[wave][lane][s & 1] = v;
           }
           __syncthreads();
+#pragma unroll
+          for (int k = 0; k < 6; k++) {
+            t[k] = spart[0][k][s & 1];
+            for (int w = 1; w < NW; w++) t[k] += spart[w][k][s & 1];
+          }
         }
-        sx = red[0][0];
-        sy = red[1][0];
-        sz = red[2][0];
-        __syncthreads();
-        const R mx = sx * inb, my = sy * inb, mz = sz * inb;
-        if (pass == 0) {
-          vx -= mx;
-          vy -= my;
-          vz -= mz;
-        } else {
-          rx -= mx;
-          ry -= my;
-          rz -= mz;
-        }
+        vx -= t[0] * inb;
+        vy -= t[1] * inb;
+        vz -= t[2] * inb;
+        rx -= t[3] * inb;
+        ry -= t[4] * inb;
+        rz -= t[5] * inb;
       }
     }
-    if constexpr (!WAVE) __syncthreads();
+    if (WAVE && overflow && lane == 0) sover[0] = 1;
+    if (act) {
+      sdp[tid][0] = dpx;
+      sdp[tid][1] = dpy;
+      sdp[tid][2] = dpz;
+    }
   }
-  if (overflow) {
-    if (j == 0) atomicMin(&st->err_key, (ci << 4) | EC_FENE);
+  __syncthreads();
+  if (sover[0] | sover[1]) {
+    if (tid == 0) atomicMin(&st->err_key, (ci << 4) | EC_FENE);
     return;
   }
   if (act) {
@@ -402,33 +460,69 @@ __global__ __launch_bounds__(CB, 3) void k_chain(const BoxDesc* __restrict__ box
     vel[pout + 3 * gj] = vx;
     vel[pout + 3 * gj + 1] = vy;
     vel[pout + 3 * gj + 2] = vz;
-    rec_base[gj] = make_int4(base[0], base[1], base[2], 0);
-    rec_d[3 * gj] = dl[0];
-    rec_d[3 * gj + 1] = dl[1];
-    rec_d[3 * gj + 2] = dl[2];
+    rec_base[gj] = make_int4(sbase[tid][0], sbase[tid][1], sbase[tid][2], 0);
+#pragma unroll
+    for (int a = 0; a < 3; a++) rec_d[3 * gj + a] = sd[tid][a];
     rec_dp[3 * gj] = dpx;
     rec_dp[3 * gj + 1] = dpy;
     rec_dp[3 * gj + 2] = dpz;
+  }
+  // stencil box: on a periodic axis lo in [0, n) and hi = lo + extent - 1 (n
+  // or more where the range wraps), the whole axis at most
+  int lo[3], len[3];
 #pragma unroll
-    for (int a = 0; a < 3; a++) {
-      const int lo = PER ? ubase[a] : base[a];
-      atomicMin(&sbox[a], lo);
-      atomicMax(&sbox[3 + a], lo + 1);
+  for (int a = 0; a < 3; a++) {
+    lo[a] = sbox[a];
+    len[a] = sbox[3 + a] - lo[a] + 1;
+    if (PER && ((b.pmask >> a) & 1)) {
+      const int n = a == 0 ? b.nx : (a == 1 ? b.ny : b.nz);
+      lo[a] = len[a] < n ? ((lo[a] % n) + n) % n : 0;
+      len[a] = len[a] < n ? len[a] : n;
+    }
+    if (tid == 0) {
+      bbox[6 * ci + a] = lo[a];
+      bbox[6 * ci + 3 + a] = lo[a] + len[a] - 1;
     }
   }
-  __syncthreads();
-  if (j < 3) {
-    int lo = sbox[j], hi = sbox[3 + j];
-    if (PER && ((b.pmask >> j) & 1)) {
-      // periodic axis: lo in [0, n), hi = lo + extent - 1 (n or more where the
-      // range wraps), the whole axis at most
-      const int n = j == 0 ? b.nx : (j == 1 ? b.ny : b.nz);
-      const int ext = hi - lo < n - 1 ? hi - lo : n - 1;
-      lo = hi - lo < n - 1 ? ((lo % n) + n) % n : 0;
-      hi = lo + ext;
+  // spread force of the box's nodes, - sum_j w_jx dP_j: 64 nodes at a time,
+  // wave w summing its share of the beads, the waves' partials added in order
+  if ((int64_t)len[0] * len[1] * len[2] > GTAB) return;
+  const int vol = len[0] * len[1] * len[2];
+  const int per = (c.nb + NW - 1) / NW;
+  const int j0 = wave * per, j1 = j0 + per < c.nb ? j0 + per : c.nb;
+  for (int p0 = 0; p0 < vol; p0 += 64) {
+    const int p = p0 + lane;
+    int x = lo[0] + p % len[0], y = lo[1] + (p / len[0]) % len[1], z = lo[2] + p / (len[0] * len[1]);
+    if (PER) {
+      if ((b.pmask & 1) && x >= b.nx) x -= b.nx;
+      if ((b.pmask & 2) && y >= b.ny) y -= b.ny;
+      if ((b.pmask & 4) && z >= b.nz) z -= b.nz;
     }
-    bbox[6 * ci + j] = lo;
-    bbox[6 * ci + 3 + j] = hi;
+    double g[3] = {0, 0, 0};
+#pragma unroll 4
+    for (int j = j0; j < j1; j++) {
+      int ox = x - sbase[j][0], oy = y - sbase[j][1], oz = z - sbase[j][2];
+      if (PER) {
+        if ((b.pmask & 1) && ox < 0) ox += b.nx;
+        if ((b.pmask & 2) && oy < 0) oy += b.ny;
+        if ((b.pmask & 4) && oz < 0) oz += b.nz;
+      }
+      const bool hit = (unsigned)ox <= 1u && (unsigned)oy <= 1u && (unsigned)oz <= 1u;
+      const double w = (ox ? sd[j][0] : 1.0 - sd[j][0]) * (oy ? sd[j][1] : 1.0 - sd[j][1]) *
+                       (oz ? sd[j][2] : 1.0 - sd[j][2]);
+#pragma unroll
+      for (int a = 0; a < 3; a++) g[a] -= hit ? w * sdp[j][a] : 0.0;
+    }
+    __syncthreads();  // the last chunk's partials are read (and the sums above)
+#pragma unroll
+    for (int a = 0; a < 3; a++) spart[wave][lane][a] = g[a];
+    __syncthreads();
+    if (tid < 192 && p0 + tid / 3 < vol) {
+      double v = spart[0][tid / 3][tid % 3];
+#pragma unroll
+      for (int w = 1; w < NW; w++) v += spart[w][tid / 3][tid % 3];
+      gtab[((size_t)ci * GTAB + p0) * 3 + tid] = v;
+    }
   }
 }
 
@@ -567,6 +661,7 @@ struct LbArgs {
   const void* rec_d;
   const void* rec_dp;
   const int* bbox;
+  const double* gtab;      // [n_chains][GTAB][3] spread force of each chain's stencil box
   DevState* st;
   double* partials;        // [n_check][4] mass/momentum partials of k_check
   const int4* check_items; // k_check workgroups: box, first row, end row (row z ny + y)
@@ -672,10 +767,10 @@ __device__ __forceinline__ void collide_ext(R d[Q], R gx, R gy, R gz, R rho0, R 
 }
 
 // Spread force g(x) = - sum_j w_jx dP_j at node (x, y, z): chains whose stencil
-// box overlaps the tile (cmask), beads in fixed order, no atomics.
+// box overlaps the tile (cmask), from k_chain's table or, for a stencil box
+// larger than it, over the beads in fixed order; no atomics.
 // UNROLL: beads whose records are loaded together (1 inside the fused step,
-// where registers are short; 4 in k_force: one at a time its pass over a
-// 16-bead chain takes 9.8 us instead of 6.7)
+// where registers are short; 4 in k_force)
 template <typename R, bool PER, int UNROLL>
 __device__ __forceinline__ void gather_force(const LbArgs& A, const BoxDesc& b,
                                              unsigned long long cmask, int x, int y, int z, R& gx,
@@ -693,6 +788,20 @@ __device__ __forceinline__ void gather_force(const LbArgs& A, const BoxDesc& b,
     if (!(in_range<PER>(x, bb[0], bb[3], b.nx, b.pmask & 1) &&
           in_range<PER>(y, bb[1], bb[4], b.ny, b.pmask & 2)))
       continue;
+    const int len0 = bb[3] - bb[0] + 1, len1 = bb[4] - bb[1] + 1, len2 = bb[5] - bb[2] + 1;
+    if ((int64_t)len0 * len1 * len2 <= GTAB) {  // summed by k_chain already
+      int ix = x - bb[0], iy = y - bb[1], iz = z - bb[2];
+      if (PER) {
+        if (ix < 0) ix += b.nx;
+        if (iy < 0) iy += b.ny;
+        if (iz < 0) iz += b.nz;
+      }
+      const double* g = A.gtab + ((size_t)gc * GTAB + (iz * len1 + iy) * len0 + ix) * 3;
+      sx += g[0];
+      sy += g[1];
+      sz += g[2];
+      continue;
+    }
     const ChainDesc& ch = A.chains[gc];
     // the records of UNROLL beads loaded before the first is used, and no
     // branch per bead (a bead whose stencil misses the node, or the last bead

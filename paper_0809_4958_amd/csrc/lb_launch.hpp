@@ -16,7 +16,7 @@ namespace lbhost {
 using LbLaunch = void (*)(dim3, hipStream_t, const lbdev::LbArgs&);
 using ChainLaunch = void (*)(int, hipStream_t, const lbdev::BoxDesc*, const lbdev::ChainDesc*,
                              const void*, const void*, void*, void*, int, int4*, void*, void*, int*,
-                             lbdev::DevState*, double, int, long long*, const int4*, int,
+                             double*, lbdev::DevState*, double, int, long long*, const int4*, int,
                              float*, unsigned, unsigned);
 
 // fused step launcher: storage S (0 FP64, 1 FP32, 2 FP16 deviations), collision
@@ -29,8 +29,8 @@ LbLaunch pick_lb(bool periodic, bool ext, bool in_place);
 template <int S, int C>
 LbLaunch pick_force(bool periodic, bool ext);
 
-// chain kernel launcher for storage S; one wavefront per chain when no chain
-// has more than 64 beads, else 256 threads; the same launch computes the
+// chain kernel launcher for storage S, for chains of at most 64 beads or of
+// up to 256; the same launch computes the
 // x-face velocities of the step in workgroups after the chains; thermal: the
 // beads' Langevin noise
 template <int S>

@@ -42,24 +42,25 @@ LbLaunch pick_force(bool periodic, bool ext) {
 template LbLaunch pick_force<LB_S, LB_C>(bool, bool);
 
 #if LB_C == 0
-template <int S, bool P, int CB, bool TH>
+template <int S, bool P, int MB, bool TH>
 void launch_chain(int nch, hipStream_t s, const BoxDesc* boxes, const ChainDesc* chains,
                   const void* a0, const void* a1, void* pos, void* vel, int total, int4* rb,
-                  void* rd, void* rp, int* bbox, DevState* st, double rho0, int pre,
+                  void* rd, void* rp, int* bbox, double* gtab, DevState* st, double rho0, int pre,
                   long long* stamp, const int4* xf_items, int n_xf, float* xface, unsigned key0,
                   unsigned key1) {
   using T = typename Store<S>::T;
-  // one workgroup per chain, then CB / 64 x-face work items per workgroup
-  const int nxb = (n_xf + CB / 64 - 1) / (CB / 64);
-  hipLaunchKernelGGL((k_chain<S, P, CB, TH>), dim3(nch + nxb), dim3(CB), 0, s, boxes, chains,
+  // one workgroup per chain, then an x-face work item per wavefront
+  constexpr int NT = chain_threads(MB);
+  const int nxb = (n_xf + NT / 64 - 1) / (NT / 64);
+  hipLaunchKernelGGL((k_chain<S, P, MB, TH>), dim3(nch + nxb), dim3(NT), 0, s, boxes, chains,
                      (const T*)a0, (const T*)a1, (double*)pos, (double*)vel, total, rb, (double*)rd,
-                     (double*)rp, bbox, st, rho0, pre, stamp, nch, xf_items, n_xf, xface, key0, key1);
+                     (double*)rp, bbox, gtab, st, rho0, pre, stamp, nch, xf_items, n_xf, xface, key0, key1);
 }
 
 template <int S, bool TH>
 ChainLaunch pick_chain_th(bool periodic, int max_beads) {
   if (max_beads <= 64) return periodic ? launch_chain<S, true, 64, TH> : launch_chain<S, false, 64, TH>;
-  return periodic ? launch_chain<S, true, WG, TH> : launch_chain<S, false, WG, TH>;
+  return periodic ? launch_chain<S, true, 256, TH> : launch_chain<S, false, 256, TH>;
 }
 
 template <int S>

@@ -211,6 +211,7 @@ struct lb_ctx {
   void* d_rec_d = nullptr;
   void* d_rec_dp = nullptr;
   int* d_bbox = nullptr;
+  double* d_gtab = nullptr;        // [n_chains][GTAB][3] spread force of the stencil boxes
   int total_beads = 0;
   int n_items = 0, n_entries = 0, grid = 0;
   std::vector<Item> items;
@@ -663,6 +664,8 @@ lb_status upload_chains(lb_ctx* ctx) {
   dfree(ctx, ctx->d_rec_d);
   dfree(ctx, ctx->d_rec_dp);
   dfree(ctx, ctx->d_bbox);
+  dfree(ctx, ctx->d_gtab);
+  ctx->d_gtab = nullptr;
   ctx->d_chains = nullptr;
   ctx->d_pos = ctx->d_vel = nullptr;
   ctx->d_rec_base = nullptr;
@@ -720,6 +723,7 @@ lb_status upload_chains(lb_ctx* ctx) {
   ctx->d_rec_d = dalloc(ctx, 3 * nbd * rb);
   ctx->d_rec_dp = dalloc(ctx, 3 * nbd * rb);
   ctx->d_bbox = dalloc_t<int>(ctx, 6 * std::max<size_t>(1, cd.size()), &ok);
+  ctx->d_gtab = dalloc_t<double>(ctx, cd.size() * GTAB * 3, &ok);
   if (!ok || !ctx->d_pos || !ctx->d_vel || !ctx->d_rec_d || !ctx->d_rec_dp)
     return fail(ctx, LB_ERR_OOM, "chain allocation failed");
   if (!cd.empty())
@@ -802,6 +806,7 @@ LbArgs make_args(lb_ctx* ctx, int pre, int advance, int reduce_every) {
   a.rec_d = ctx->d_rec_d;
   a.rec_dp = ctx->d_rec_dp;
   a.bbox = ctx->d_bbox;
+  a.gtab = ctx->d_gtab;
   a.st = ctx->d_st;
   a.partials = ctx->d_partials;
   a.check_items = ctx->d_check_items;
@@ -859,7 +864,7 @@ void enqueue_step(lb_ctx* ctx, hipStream_t s, int pre, const hipEvent_t* ev3,
   if (chains) {  // chains and x-face velocities in one launch
     ctx->chain_fn((int)ctx->ch.size(), s, ctx->d_boxes, ctx->d_chains, ctx->arena[0], ctx->arena[1],
                   ctx->d_pos, ctx->d_vel, ctx->total_beads, ctx->d_rec_base, ctx->d_rec_d,
-                  ctx->d_rec_dp, ctx->d_bbox, ctx->d_st, ctx->cfg.rho0, ctx->aa ? 2 : pre, st3,
+                  ctx->d_rec_dp, ctx->d_bbox, ctx->d_gtab, ctx->d_st, ctx->cfg.rho0, ctx->aa ? 2 : pre, st3,
                   ctx->d_xf_items, ctx->n_xf_items, ctx->d_xface,
                   (unsigned)(ctx->seed & 0xffffffffu), (unsigned)(ctx->seed >> 32));
   } else if (xf) {
@@ -2315,6 +2320,7 @@ void lb_free(lb_ctx* ctx) {
   dfree(ctx, ctx->d_rec_base);
   dfree(ctx, ctx->d_rec_d);
   dfree(ctx, ctx->d_rec_dp);
+  dfree(ctx, ctx->d_gtab);
   dfree(ctx, ctx->d_bbox);
   for (auto e : ctx->ev) (void)hipEventDestroy(e);
   drop_stamps(ctx);

@@ -99,3 +99,70 @@ def test_check_record_of_many_row_ranges(dims, storage, tol):
     assert mm_g[0] == mm_o[0] == 2
     assert np.abs(mm_g[1:] - mm_o[1:]).max() < tol * mm_o[1]
     ctx.close()
+
+
+def walk(beads, anchor, rng, bond):
+    pos, vel = inputs.chain_init(beads, anchor, rng, bond=bond)
+    return dict(pos=pos, vel=vel, fene_k=1.0 if bond < 0.5 else 0.003, anchor=anchor)
+
+
+@pytest.mark.parametrize("streaming", ["two_buffers", "in_place"])
+@pytest.mark.parametrize("storage", ["f64", "f16"])
+@pytest.mark.parametrize("beads,bond", [(1, CHAIN_BOND), (2, CHAIN_BOND), (9, 0.8), (64, 1.2), (65, CHAIN_BOND),
+                                        (65, 1.2), (129, CHAIN_BOND), (256, 0.9)])
+def test_chain_lengths_and_stencil_box_sizes(beads, bond, storage, streaming):
+    """One bead to 256, around the 64 of a wavefront and the eight lanes of a
+    bead, compact and stretched: stencil boxes inside and beyond the 1,024
+    nodes whose force the chain pass tabulates, two chains overlapping."""
+    rng = np.random.default_rng(41)
+    steps, dims = 9, (34, 31, 33)
+    A = inputs.ou_strain(steps + 1, rng, corr_steps=20.0, rms=1e-3)
+    xc = [16.4, 15.2, 15.9]
+    case = Case(dims, collision=oracle.MRT, tau=0.8, bc=(oracle.BC_AFFINE, A, 0, 1, 0),
+                chains=[walk(beads, xc, rng, bond), walk(5, [17.1, 15.0, 16.3], rng, CHAIN_BOND)], reduce_every=3)
+    if beads == 1:  # a pinned single bead has no size to compare positions with
+        case.chains[0]["fix_com"] = False
+    run_case(case, storage, steps, f"{beads} beads of bond {bond} {streaming}",
+             streaming=lbm.STREAM_AA if streaming == "in_place" else lbm.STREAM_AB)
+
+
+@pytest.mark.parametrize("beads", [12, 100])
+def test_thermal_chain_lengths(beads):
+    """Langevin noise, whose centre-of-mass sums stay inside the substeps, in
+    one wavefront and over several."""
+    rng = np.random.default_rng(43)
+    steps, dims = 6, (18, 17, 19)
+    A = inputs.ou_strain(steps + 1, rng, corr_steps=20.0, rms=1e-3)
+    case = Case(dims, collision=oracle.MRT, tau=0.8, bc=(oracle.BC_AFFINE, A, 0, 1, 0), kT=1e-6, seed=77,
+                chains=[walk(beads, [8.4, 8.1, 9.2], rng, CHAIN_BOND)])
+    say("case thermal chain", beads)
+    ob = case.oracle_box()
+    assert ob.step(steps) == 0
+    ctx = make_ctx(case, "f64")
+    ctx.set_thermal(case.kT, case.seed)
+    ctx.step(steps)
+    check(compare(ctx, ob, case, "f64"), "f64", f"thermal chain of {beads}")
+    ctx.close()
+
+
+@pytest.mark.parametrize("beads", [40, 150])
+def test_overstretched_bond_latches_at_the_oracles_step(beads):
+    """Beads thrown apart: the bond reaches its maximum extension in the middle
+    of a step; the error, its step and the state before it are the oracle's."""
+    rng = np.random.default_rng(47)
+    dims = (20, 20, 20)
+    A = inputs.ou_strain(12, rng, corr_steps=20.0, rms=1e-3)
+    chain = walk(beads, [9.5, 9.5, 9.5], rng, CHAIN_BOND)
+    chain.update(zeta=0.1 / beads, fene_k=1e-6, vel=np.zeros((beads, 3)))
+    chain["vel"][beads // 2:, 0] = 0.8
+    case = Case(dims, collision=oracle.MRT, tau=0.8, bc=(oracle.BC_AFFINE, A, 0, 1, 0), chains=[chain])
+    say("case overstretched bond", beads)
+    ob = case.oracle_box()
+    code = ob.step(10)
+    assert code == -4 and 0 < ob.step_index < 10
+    ctx = make_ctx(case, "f64")
+    ctx.step(10)
+    assert ctx.sync_status() == lbm.ERR_FENE
+    assert ctx.read(0, lbm.F_STEP, strict=False)[0] == ob.step_index
+    check(compare(ctx, ob, case, "f64", strict=False), "f64", "overstretched")
+    ctx.close()
