@@ -85,8 +85,8 @@ typedef enum { LB_STORE_F64 = 0, LB_STORE_F32 = 1, LB_STORE_F16DEV = 2 } lb_stor
  * node x + c_i, where the next even step finds the next pre-collision state
  * in place.  Every slot is read and written by one node only, so no step needs
  * a second buffer.  The same arithmetic as LB_STREAM_AB, bit for bit on tile
- * boxes; in-place contexts run every box as tile items (no row items), gather
- * the chains' spread force inside the fused step, and have no autotuner. */
+ * boxes; in-place contexts gather the chains' spread force inside the fused
+ * step, and have no autotuner. */
 typedef enum { LB_STREAM_AB = 0, LB_STREAM_AA = 1 } lb_streaming;
 
 typedef struct {

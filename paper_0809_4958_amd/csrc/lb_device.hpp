@@ -106,6 +106,8 @@ struct BoxDesc {
   int fast;             // non-periodic and 19*nn*sizeof(T) < 2^32 (32-bit offsets)
   int vec;              // interior rows handled as lane vectors (ITEM_ROWS) incl. the x-face nodes
   int ylog;             // log2 of the rows interleaved per population row (see aidx)
+  int px;               // nodes a row takes in memory (nx, or more for row boxes; see aidx)
+  int nyb;              // blocks of 2^ylog rows per plane
   int vw;               // row boxes: 32-bit words per lane vector (2 or 3)
   int xf_off;           // row boxes: first float of the box's x-face velocities, else -1
   int index;            // the box's index (random-number counters)
@@ -626,12 +628,15 @@ __device__ __forceinline__ void collide_mrt_pairs(R d[Q], R gx, R gy, R gz, R rh
 // 19 population rows of a block of Y consecutive y lines are adjacent, and
 // each population's Y rows are contiguous, so that a population row of a
 // block spans whole 128-byte lines when nx is short (Y = 1 gives
-// pop[z][y][i][x]).  The populations a node pulls lie in at most nine
+// pop[z][y][i][x]).  Row boxes whose nx no lane vector divides pad their rows
+// to px nodes and ny to whole blocks; pad nodes belong to no one: the step
+// computes on them, and nothing reads them into a node of the box.  The
+// populations a node pulls lie in at most nine
 // neighbouring lines (y - c_y, z - c_z).
 __host__ __device__ __forceinline__ int64_t aidx(const BoxDesc& b, int i, int x, int y, int z) {
   const int Y = 1 << b.ylog;
-  return (((int64_t)z * (b.ny >> b.ylog) + (y >> b.ylog)) * Q + i) * ((int64_t)b.nx << b.ylog) +
-         (int64_t)(y & (Y - 1)) * b.nx + x;
+  return (((int64_t)z * b.nyb + (y >> b.ylog)) * Q + i) * ((int64_t)b.px << b.ylog) +
+         (int64_t)(y & (Y - 1)) * b.px + x;
 }
 
 // Neighbour coordinate with wrap on periodic axes.

@@ -680,7 +680,7 @@ struct LbArgs {
   int advance;
   double kT;               // thermal fluctuations (fluctuating MRT) when > 0
   unsigned key0, key1;     // Philox key of the context's random numbers
-  int aa;                  // in-place streaming on one buffer (a0 == a1): tile items only
+  int aa;                  // in-place streaming on one buffer (a0 == a1)
 };
 
 // Collision dispatcher: 0 BGK, 1 MRT, 2 MRT with ghost rate 1.  CW: the
@@ -915,6 +915,22 @@ __device__ __forceinline__ void tile_fast(const LbArgs& A, const BoxDesc& b, con
 // shuffle inside the wavefront, or a direct load for the first and last lane
 // of a wavefront.  The groups holding x = 0 or x = nx-1 store the boundary
 // equilibrium of that node (face -x or +x), so every store is a full vector.
+// Rows are px nodes long in memory, so a row of any nx is whole lane vectors
+// (four 121^3 FP32 boxes: 215 us, as tiles 331 us).
+//
+// How a step reads and writes, by RowMode: with two buffers it pulls, or reads
+// in place on the first step of an uploaded state; in place, an even step
+// reads each node's own slots and writes the opposite ones, an odd step reads
+// the neighbours' opposite slots and writes f*_i into slot i of x + c_i.  That
+// push moves the finished vectors by c_x: by a lane shuffle and a shift inside
+// the vector, the elements that cross a wavefront's edge stored singly by the
+// lane that owns them (each slot is read and written by one node only, so
+// waves never touch each other's elements).  Even and odd steps take 532 and
+// 672 us on a 320^3 FP16 box without chains (two buffers 506, in-place tiles
+// 871; the single stores at wavefront edges are 57 us of the odd step), 860
+// and 886 us at 384^3, where rows end with wavefronts.
+enum RowMode : int { ROWS_PULL = 0, ROWS_PLACE = 1, ROWS_AA_EVEN = 2, ROWS_AA_ODD = 3 };
+
 template <int S, int W>
 struct RowVec {
   using T = typename Store<S>::T;
@@ -1037,7 +1053,100 @@ __device__ __forceinline__ void vput(unsigned (&w)[W], int e, typename Store<S>:
   }
 }
 
-template <int S, int W, int COLL, bool PRE, int BS, bool EXT>
+// Stores the out vectors of a lane pushed one step along their directions (in
+// place, odd steps).  D stores into the line (y + c_y, z + c_z) of population
+// i: vec a whole vector at the lane's x0, word and half 4 and 2 bytes at a byte
+// offset from it.  first: the lane starts a wavefront inside a row; last: it
+// ends one (or an item) inside a row; want(i): populations to store at all.
+template <int S, int W, typename D, typename F>
+__device__ __forceinline__ void push_vectors(const D& dst, const unsigned (&out)[Q][W], bool act,
+                                             bool first, bool last, unsigned lane_l,
+                                             unsigned lane_r, F want) {
+  constexpr int SB = (int)sizeof(typename Store<S>::T);
+  constexpr int VB = W * 4;  // bytes of a lane vector
+#pragma unroll
+  for (int i = 0; i < Q; i++) {
+    unsigned sh[W];
+    if (CX[i] == 0) {
+#pragma unroll
+      for (int w = 0; w < W; w++) sh[w] = out[i][w];
+    } else if (CX[i] == 1) {
+      const unsigned left = __shfl(out[i][W - 1], (int)lane_l, 64);
+#pragma unroll
+      for (int w = 0; w < W; w++) {
+        const unsigned lo = w ? out[i][w - 1] : left;
+        sh[w] = SB == 2 ? (lo >> 16) | (out[i][w] << 16) : lo;
+      }
+    } else {
+      const unsigned right = __shfl(out[i][0], (int)lane_r, 64);
+#pragma unroll
+      for (int w = 0; w < W; w++) {
+        const unsigned hi = w + 1 < W ? out[i][w + 1] : right;
+        sh[w] = SB == 2 ? (out[i][w] >> 16) | (hi << 16) : hi;
+      }
+    }
+    if (!act || !want(i)) continue;
+    if (!(CX[i] == 1 && first) && !(CX[i] == -1 && last)) dst.vec(i, sh);
+    if (CX[i] != 0 && (first || last)) {
+      if (CX[i] == 1 && first) {  // without element 0, the previous wavefront's
+        if (SB == 2) dst.half(i, 2, sh[0] >> 16);
+#pragma unroll
+        for (int w = 1; w < W; w++) dst.word(i, 4 * w, sh[w]);
+      }
+      if (CX[i] == 1 && last) {  // own last element into the next group
+        if (SB == 2) dst.half(i, VB, out[i][W - 1] >> 16);
+        else dst.word(i, VB, out[i][W - 1]);
+      }
+      if (CX[i] == -1 && last) {  // without the last element, the next wavefront's
+        if (SB == 2) dst.half(i, VB - 4, sh[W - 1] & 0xffffu);
+#pragma unroll
+        for (int w = 0; w < W - 1; w++) dst.word(i, 4 * w, sh[w]);
+      }
+      if (CX[i] == -1 && first) {  // own element 0 into the previous group
+        if (SB == 2) dst.half(i, -2, out[i][0] & 0xffffu);
+        else dst.word(i, -4, out[i][0]);
+      }
+    }
+  }
+}
+
+// push_vectors into the buffer of a row iteration
+template <int W>
+struct RowDst {
+  __amdgpu_buffer_rsrc_t r;
+  const unsigned* vo;  // line offsets of y - 1, y, y + 1
+  int pib, ps;
+  __device__ __forceinline__ int so(int i) const { return i * pib + (1 + CZ[i]) * ps; }
+  __device__ __forceinline__ void vec(int i, const unsigned (&w)[W]) const {
+    vstore<W>(r, vo[1 + CY[i]], so(i), w);
+  }
+  __device__ __forceinline__ void word(int i, int off, unsigned v) const {
+    __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)vo[1 + CY[i]] + off, so(i), 0);
+  }
+  __device__ __forceinline__ void half(int i, int off, unsigned v) const {
+    __builtin_amdgcn_raw_buffer_store_b16((unsigned short)v, r, (int)vo[1 + CY[i]] + off, so(i), 0);
+  }
+};
+
+// push_vectors by addresses (face rows)
+template <int W>
+struct PtrDst {
+  char* plane;         // the lane's x0 in line 0 of its plane, population 0
+  long long psb;       // bytes per plane
+  long long pib;
+  long long yo[3];     // line offsets of y - 1, y, y + 1
+  __device__ __forceinline__ char* at(int i) const { return plane + CZ[i] * psb + yo[1 + CY[i]] + i * pib; }
+  __device__ __forceinline__ void vec(int i, const unsigned (&w)[W]) const {
+#pragma unroll
+    for (int k = 0; k < W; k++) ((unsigned*)at(i))[k] = w[k];
+  }
+  __device__ __forceinline__ void word(int i, int off, unsigned v) const { *(unsigned*)(at(i) + off) = v; }
+  __device__ __forceinline__ void half(int i, int off, unsigned v) const {
+    *(unsigned short*)(at(i) + off) = (unsigned short)v;
+  }
+};
+
+template <int S, int W, int COLL, int MODE, int BS, bool EXT>
 __device__ __forceinline__ void tile_rows(const LbArgs& A, const BoxDesc& b, const Item& it,
                                           const typename Store<S>::T* src,
                                           typename Store<S>::T* dst, long long step,
@@ -1049,13 +1158,18 @@ __device__ __forceinline__ void tile_rows(const LbArgs& A, const BoxDesc& b, con
   using R = typename St::R;
   constexpr int V = RowVec<S, W>::V;
   constexpr int SB = (int)sizeof(T);
+  constexpr bool PRE = MODE == ROWS_PLACE || MODE == ROWS_AA_EVEN;  // reads each node's own slots
+  // slot of population i read and, in place on even steps, written
+  auto rslot = [](int i) { return MODE == ROWS_AA_ODD ? OPP[i] : i; };
+  auto wslot = [](int i) { return MODE == ROWS_AA_EVEN ? OPP[i] : i; };
   const int nx = b.nx, ny = b.ny, nyi = b.ny - 2;
-  const int L = nx / V;                            // lane groups per row
-  const int nxb = nx * SB;                         // bytes per population row
+  const int L = b.px / V;                          // lane groups per row
+  const int cr = (nx - 1) / V, kr = (nx - 1) - cr * V;  // group and element of x = nx - 1
+  const int nxb = b.px * SB;                       // bytes per population row
   const int yl = b.ylog, ym = (1 << b.ylog) - 1;
   const int pib = nxb << yl;                       // bytes per population in a block of Y rows
   const int bkb = Q * pib;                         // bytes per block of Y rows
-  const long long psb = (long long)Q * nxb * ny;   // bytes per plane
+  const long long psb = (long long)bkb * b.nyb;    // bytes per plane
   const long long box_bytes = psb * b.nz;
   const int g_last = L * nyi * (b.nz - 2) - 1;     // last group of the box
   const int q_end = it.x0 + it.ex;
@@ -1094,13 +1208,13 @@ __device__ __forceinline__ void tile_rows(const LbArgs& A, const BoxDesc& b, con
     unsigned raw[Q][W];
 #pragma unroll
     for (int i = 0; i < Q; i++) {
-      const int so = i * pib + (PRE ? ps : (1 - CZ[i]) * ps);
+      const int so = rslot(i) * pib + (PRE ? ps : (1 - CZ[i]) * ps);
       vload<W>(rsrc, PRE ? voff : vo[1 - CY[i]], so, raw[i]);
     }
     // boundary velocity of the lane's x-face node (first or last lane group of
     // a row; L >= 2, so at most one), written by k_xface for this step and
     // loaded together with the populations
-    const bool xface = act && (c == 0 || c == L - 1);
+    const bool xface = act && (c == 0 || c == cr);
     const int xside = c == 0 ? 0 : 1;
     float xu[3] = {0.0f, 0.0f, 0.0f};
     if (xface) {
@@ -1126,7 +1240,7 @@ __device__ __forceinline__ void tile_rows(const LbArgs& A, const BoxDesc& b, con
 #pragma unroll
         for (int i = 0; i < Q; i++) {
           if (CX[i] != 1) continue;
-          const int so = i * pib + (1 - CZ[i]) * ps - SB;
+          const int so = rslot(i) * pib + (1 - CZ[i]) * ps - SB;
           const int vl = (int)vo[1 - CY[i]];
           if constexpr (SB == 2)
             left[i] = (unsigned)__builtin_amdgcn_raw_buffer_load_b16(rsrc, vl, so, 0) << 16;
@@ -1138,7 +1252,7 @@ __device__ __forceinline__ void tile_rows(const LbArgs& A, const BoxDesc& b, con
 #pragma unroll
         for (int i = 0; i < Q; i++) {
           if (CX[i] != -1) continue;
-          const int so = i * pib + (1 - CZ[i]) * ps + V * SB;
+          const int so = rslot(i) * pib + (1 - CZ[i]) * ps + V * SB;
           const int vr = (int)vo[1 - CY[i]];
           if constexpr (SB == 2)
             right[i] = (unsigned)__builtin_amdgcn_raw_buffer_load_b16(rsrc, vr, so, 0);
@@ -1188,15 +1302,23 @@ __device__ __forceinline__ void tile_rows(const LbArgs& A, const BoxDesc& b, con
         }
       } else {
 #pragma unroll
-        for (int i = 0; i < Q; i++) {
-          const float ke = WCLS[i] == 0 ? ec0 : (WCLS[i] == 1 ? ec1 : ec2);
-          vput_enc<S, W>(out[i], V - 1, eq[i], ke, dither_pop(hx, i));
+        for (int k = 0; k < V; k++) {
+          if (k != kr) continue;  // uniform
+#pragma unroll
+          for (int i = 0; i < Q; i++) {
+            const float ke = WCLS[i] == 0 ? ec0 : (WCLS[i] == 1 ? ec1 : ec2);
+            vput_enc<S, W>(out[i], k, eq[i], ke, dither_pop(hx, i));
+          }
         }
       }
     }
-    if (act) {
+    if constexpr (MODE == ROWS_AA_ODD) {
+      const RowDst<W> to{rdst, vo, pib, ps};
+      push_vectors<S, W>(to, out, act, lane == 0 && c != 0, (lane == 63 || q == q_end - 1) && c != L - 1,
+                         lane_l, lane_r, [](int) { return true; });
+    } else if (act) {
 #pragma unroll
-      for (int i = 0; i < Q; i++) vstore<W>(rdst, voff, i * pib + ps, out[i]);
+      for (int i = 0; i < Q; i++) vstore<W>(rdst, voff, wslot(i) * pib + ps, out[i]);
     }
   }
 }
@@ -1207,8 +1329,10 @@ __device__ __forceinline__ void tile_rows(const LbArgs& A, const BoxDesc& b, con
 // rows y = 0 and y = ny-1.  Every node takes the boundary equilibrium at t_n
 // with the face of lowest index it lies on (-x, +x, -y, +y, -z, +z); a row
 // stores, one W-word vector each, the populations whose target line
-// (y + c_y, z + c_z) is an interior line -- the only ones ever read.
-template <int S, int W, int BS>
+// (y + c_y, z + c_z) is an interior line -- the only ones ever read.  AA: the
+// step in place, which stores population i into the opposite slot (even) or
+// into slot i of node x + c_i (odd).
+template <int S, int W, int BS, bool AA>
 __device__ __forceinline__ void face_rows(const BoxDesc& b, const Item& it,
                                           typename Store<S>::T* dst, long long step,
                                           typename Store<S>::R rho0) {
@@ -1217,17 +1341,23 @@ __device__ __forceinline__ void face_rows(const BoxDesc& b, const Item& it,
   constexpr int V = RowVec<S, W>::V;
   constexpr int SB = (int)sizeof(typename St::T);
   const int nx = b.nx, ny = b.ny, nz = b.nz;
-  const int L = nx / V;
-  const long long nxb = (long long)nx * SB, psb = Q * nxb * ny;
+  const int L = b.px / V;
+  const long long nxb = (long long)b.px * SB;
   const int yl = b.ylog, ym = (1 << b.ylog) - 1;
-  const long long pib = nxb << yl, bkb = Q * pib;
+  const long long pib = nxb << yl, bkb = Q * pib, psb = bkb * b.nyb;
+  const bool odd = AA && (step & 1);
+  const int lane = (int)(threadIdx.x & 63);
   const float ec0 = b.enc[0], ec1 = b.enc[1], ec2 = b.enc[2];
   const int q_end = it.x0 + it.ex;
   const BcTime<R> tm = bc_time<R>(b, step);
 #pragma unroll 1
-  for (int q = it.x0 + (int)threadIdx.x; q < q_end; q += BS) {
-    const int fr = q / L;
-    const int c = q - fr * L;
+  for (int qb = it.x0; qb < q_end; qb += BS) {
+    const int q = qb + (int)threadIdx.x;
+    const bool act = q < q_end;
+    if (!AA && !act) continue;
+    const int qq = act ? q : q_end - 1;  // in place the wavefront shuffles: no lane leaves
+    const int fr = qq / L;
+    const int c = qq - fr * L;
     int y, z;
     if (fr < ny) {
       y = fr;
@@ -1244,7 +1374,7 @@ __device__ __forceinline__ void face_rows(const BoxDesc& b, const Item& it,
     unsigned out[Q][W];
 #pragma unroll
     for (int k = 0; k < V; k++) {
-      const int x = x0 + k;
+      const int x = x0 + k < nx ? x0 + k : nx - 1;  // pad nodes repeat the last
       const int f = x == 0 ? 0 : (x == nx - 1 ? 1 : (y == 0 ? 2 : (y == ny - 1 ? 3 : (z == 0 ? 4 : 5))));
       const int qn[3] = {x, y, z};
       R u[3];
@@ -1259,14 +1389,25 @@ __device__ __forceinline__ void face_rows(const BoxDesc& b, const Item& it,
         vput_enc<S, W>(out[i], k, eq[i], ke, dither_pop(hn, i));
       }
     }
-    char* row = (char*)dst + (long long)z * psb + (long long)(y >> yl) * bkb + (long long)(y & ym) * nxb +
-                (long long)x0 * SB;
+    auto inward = [&](int i) {
+      const int ty = y + CY[i], tz = z + CZ[i];
+      return ty >= 1 && ty <= ny - 2 && tz >= 1 && tz <= nz - 2;
+    };
+    auto ybytes = [&](int yy) { return (long long)(yy >> yl) * bkb + (long long)(yy & ym) * nxb; };
+    char* plane = (char*)dst + (long long)z * psb + (long long)x0 * SB;
+    if (odd) {
+      const PtrDst<W> to{plane, psb, pib, {ybytes(y - 1), ybytes(y), ybytes(y + 1)}};
+      push_vectors<S, W>(to, out, act, lane == 0 && c != 0, (lane == 63 || q == q_end - 1) && c != L - 1,
+                         (unsigned)(lane - 1) & 63u, (unsigned)(lane + 1) & 63u, inward);
+      continue;
+    }
+    if (!act) continue;
+    char* row = plane + ybytes(y);
 #pragma unroll
     for (int i = 0; i < Q; i++) {
       // only populations that stream into an interior line are ever read
-      const int ty = y + CY[i], tz = z + CZ[i];
-      if (ty < 1 || ty > ny - 2 || tz < 1 || tz > nz - 2) continue;
-      char* p = row + i * pib;
+      if (!inward(i)) continue;
+      char* p = row + (AA ? OPP[i] : i) * pib;
       if constexpr (W == 1) *(unsigned*)p = out[i][0];
       else if constexpr (W == 2) *(uint2*)p = make_uint2(out[i][0], out[i][1]);
       else if constexpr (W == 3) *(uint3*)p = make_uint3(out[i][0], out[i][1], out[i][2]);
@@ -1335,6 +1476,75 @@ __device__ __forceinline__ void tile_generic(const LbArgs& A, const BoxDesc& b, 
   }
 }
 
+// The chains of a box (one bit each) whose stencil box meets the rows of an
+// item: a lane per chain, one load for all of them (a loop over 16 chains,
+// each test waiting for its loads: 703 instead of 654 us per step of the
+// 320^3 box).
+__device__ __forceinline__ unsigned long long chains_met(const LbArgs& A, const BoxDesc& b,
+                                                         const Item& it) {
+  const int c = (int)threadIdx.x & 63;
+  bool m = false;
+  if (c < b.chain_count) {
+    const int* bb = A.bbox + 6 * (b.chain_first + c);
+    m = bb[1] < it.y0 + it.ey && bb[4] >= it.y0 && bb[2] < it.z0 + it.ez && bb[5] >= it.z0;
+  }
+  return __ballot(m);
+}
+
+// The nodes of an in-place row item that meets a chain's stencil box, one per
+// thread: the interior ones with the spread force gathered (it is stored by
+// k_chain per node), the x-face ones as boundary nodes.  A few items of a
+// step; the row path would carry the force's registers in all of them.
+template <int S, int COLL, int BS, bool EXT>
+__device__ __forceinline__ void row_nodes_aa(const LbArgs& A, const BoxDesc& b, const Item& it,
+                                             typename Store<S>::T* buf, long long step,
+                                             unsigned long long cmask, typename Store<S>::R rho0,
+                                             typename Store<S>::R omega, typename Store<S>::R omb,
+                                             typename Store<S>::R omg) {
+  using St = Store<S>;
+  using R = typename St::R;
+  const int V = b.vw * 4 / (int)sizeof(typename St::T);
+  const int L = b.px / V, nyi = b.ny - 2;
+  const bool odd = step & 1;
+  const R sc = (R)b.s2;
+  Ext<R> ext{};
+  if constexpr (EXT) ext = make_ext<R>(A, b, step);
+#pragma unroll 1
+  for (int p = threadIdx.x; p < it.ex * V; p += BS) {
+    const int q = it.x0 + p / V, row = q / L;
+    const int x = (q - row * L) * V + p % V;
+    if (x >= b.nx) continue;
+    const int zi = row / nyi, y = 1 + row - zi * nyi, z = 1 + zi;
+    const unsigned node = ((unsigned)z * (unsigned)b.ny + (unsigned)y) * (unsigned)b.nx + (unsigned)x;
+    const unsigned hn = dither_node(node, (unsigned)step);
+    const bool face = x == 0 || x == b.nx - 1;
+    R d[Q];
+    if (face) {
+      const float* xf = A.xface + b.xf_off + 3 * (((x == 0 ? 0 : 1) * (b.nz - 2) + zi) * nyi + (y - 1));
+      eq_dev<R>((R)0, rho0, xf[0], xf[1], xf[2], d);
+    } else {
+      load_pre<S, false>(buf, b, x, y, z, aa_layout(step), d);
+      R gx = 0, gy = 0, gz = 0;
+      gather_force<R, false, 1>(A, b, cmask, x, y, z, gx, gy, gz);
+      if constexpr (EXT) {
+        ext.node = node;
+        collide_ext<R, COLL, comp_weights<S>(), S == 2>(d, gx, gy, gz, rho0, omega, omb, omg, ext, sc);
+      } else {
+        collide_any<R, COLL, comp_weights<S>(), S == 2>(d, gx, gy, gz, rho0, omega, omb, omg, sc);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < Q; i++) {
+      const int tx = x + CX[i], ty = y + CY[i], tz = z + CZ[i];
+      if (face && !is_interior(b, tx, ty, tz)) continue;
+      const typename St::T v = face ? St::enc(d[i], b.enc[WCLS[i]], dither_pop(hn, i))
+                                    : St::keep(d[i], dither_pop(hn, i));
+      if (odd) buf[aidx(b, i, tx, ty, tz)] = v;
+      else buf[aidx(b, OPP[i], x, y, z)] = v;
+    }
+  }
+}
+
 // ----------------------------------------------------------- fused step
 
 // Resident waves per SIMD the step kernel is compiled for: the most that fit
@@ -1355,8 +1565,8 @@ constexpr int lb_min_waves(int S, int COLL) {
 // its instantiations ask for two resident waves per SIMD.
 constexpr int lb_min_waves_ext(int S, int COLL, bool EXT) { return EXT ? 2 : lb_min_waves(S, COLL); }
 
-// AA: the instantiation for in-place streaming (no row items, no stores of the
-// two-buffer step; the chains' force gathered here, whose registers the
+// AA: the instantiation for in-place streaming (no stores of the two-buffer
+// step; the chains' force gathered here, whose registers the
 // two-buffer instantiations do not pay: with both in one periodic kernel a
 // 96^3 FP32 step took 135 us against 107).
 template <int S, int COLL, bool PER, int BS = WG, bool EXT = false, bool AA = false>
@@ -1388,23 +1598,49 @@ __global__ __launch_bounds__(BS, lb_min_waves_ext(S, COLL, EXT)) void k_lb(LbArg
     T* __restrict__ dst = dstA + b.off;
 
     if (it.kind == ITEM_ROWS) {
-      // row boxes are never periodic: their chains couple in k_force
-      if constexpr (S != 0 && !PER && !AA) {
-#define LB_ROWS(PR)                                                                    \
-  do {                                                                                 \
-    if (b.vw == 3)                                                                     \
-      tile_rows<S, 3, COLL, PR, BS, EXT>(A, b, it, src, dst, step, rho0, omega, omb, omg); \
-    else                                                                               \
-      tile_rows<S, 2, COLL, PR, BS, EXT>(A, b, it, src, dst, step, rho0, omega, omb, omg); \
+      // row boxes are never periodic; with two buffers their chains couple in
+      // k_force
+      if constexpr (S != 0 && !PER) {
+#define LB_ROWS(MODE, IT)                                                                \
+  do {                                                                                   \
+    if (b.vw == 3)                                                                       \
+      tile_rows<S, 3, COLL, MODE, BS, EXT>(A, b, IT, src, dst, step, rho0, omega, omb, omg); \
+    else                                                                                 \
+      tile_rows<S, 2, COLL, MODE, BS, EXT>(A, b, IT, src, dst, step, rho0, omega, omb, omg); \
   } while (0)
-        if (pre) LB_ROWS(true);
-        else LB_ROWS(false);
+        if constexpr (AA) {
+          // an item that meets a chain's stencil box goes by single iterations,
+          // and those that meet it node by node
+          const bool meets = chains_met(A, b, it) != 0;
+          const int per = meets ? BS : it.ex;
+          for (int q = it.x0; q < it.x0 + it.ex; q += per) {
+            Item sub = it;
+            sub.x0 = q;
+            sub.ex = it.x0 + it.ex - q < per ? it.x0 + it.ex - q : per;
+            unsigned long long cmask = 0;
+            if (meets) {
+              const int L = b.px / (b.vw * 4 / (int)sizeof(T)), nyi = b.ny - 2;
+              const int r0 = q / L, r1 = (q + sub.ex - 1) / L, z0 = r0 / nyi, z1 = r1 / nyi;
+              sub.z0 = 1 + z0;
+              sub.ez = z1 - z0 + 1;
+              sub.y0 = z0 == z1 ? 1 + r0 - z0 * nyi : 1;
+              sub.ey = z0 == z1 ? r1 - r0 + 1 : nyi;
+              cmask = chains_met(A, b, sub);
+            }
+            if (cmask) row_nodes_aa<S, COLL, BS, EXT>(A, b, sub, dst, step, cmask, rho0, omega, omb, omg);
+            else if (step & 1) LB_ROWS(ROWS_AA_ODD, sub);
+            else LB_ROWS(ROWS_AA_EVEN, sub);
+          }
+        } else {
+          if (pre) LB_ROWS(ROWS_PLACE, it);
+          else LB_ROWS(ROWS_PULL, it);
+        }
 #undef LB_ROWS
       }
     } else if (it.kind == ITEM_FACE_ROWS) {
-      if constexpr (S != 0 && !PER && !AA) {
-        if (b.vw == 3) face_rows<S, 3, BS>(b, it, dst, step, rho0);
-        else face_rows<S, 2, BS>(b, it, dst, step, rho0);
+      if constexpr (S != 0 && !PER) {
+        if (b.vw == 3) face_rows<S, 3, BS, AA>(b, it, dst, step, rho0);
+        else face_rows<S, 2, BS, AA>(b, it, dst, step, rho0);
       }
     } else if (it.kind == ITEM_TILE) {
       // in-place streaming: chains whose stencil box overlaps this tile (with
@@ -1635,16 +1871,22 @@ __global__ __launch_bounds__(WG) void k_check(LbArgs A) {
   const int par = (int)(step & 1);
   const T* __restrict__ arena = (const T*)(par ? A.a0 : A.a1) + b.off;  // written by this step
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  if (!A.aa && !PER && b.nx % 8 == 0) {
+  // where slot i of a node streams to, and along which direction: two buffers
+  // and an in-place even step (slot OPP[i] holds f*_OPP[i], moving along -c_i)
+  // move it on, an in-place odd step left it in place
+  const int mv = A.aa ? ((step & 1) ? 0 : -1) : 1;
+  const int dir = A.aa && !(step & 1) ? -1 : 1;
+  if (!PER && b.px % 8 == 0) {
     // chunks of 8 consecutive nodes of a row, every population read as
     // 16-byte vectors (rows start 16-byte aligned: box offsets are multiples
-    // of 128 elements and 8 nodes span 16 bytes or a multiple of it).  The
+    // of 128 elements and 8 nodes span 16 bytes or a multiple of it; a chunk
+    // may end in pad nodes, whose targets are never interior).  The
     // node's own populations are always inside the box, so all of them are
     // loaded before any is tested (no load waits behind a branch); selects,
     // not products, drop the ones that stream out of the fluid, so that
     // whatever a boundary node holds in them never enters a sum.
     constexpr int NV = 8 * (int)sizeof(T) / 16;
-    const int cpr = b.nx / 8;
+    const int cpr = (b.nx + 7) / 8;
     const int n_chunks = (cw.z - cw.y) * cpr;
     for (int p = tid; p < n_chunks; p += WG) {
       const int r = p / cpr, c = p - r * cpr, row = cw.y + r;
@@ -1659,21 +1901,21 @@ __global__ __launch_bounds__(WG) void k_check(LbArgs A) {
       }
 #pragma unroll
       for (int i = 0; i < Q; i++) {
-        const int ty = y + CY[i], tz = z + CZ[i];
+        const int ty = y + mv * CY[i], tz = z + mv * CZ[i];
         const bool row_in = ty >= 1 && ty <= b.ny - 2 && tz >= 1 && tz <= b.nz - 2;
         const T* v = (const T*)raw[i];
         double sum = 0.0;
 #pragma unroll
         for (int k = 0; k < 8; k++) {
-          const int tx = x0 + k + CX[i];
+          const int tx = x0 + k + mv * CX[i];
           const double d = (double)St::dec(v[k], b.dec[WCLS[i]]);
           sum += (tx >= 1 && tx <= b.nx - 2) ? d : 0.0;
         }
         sum = row_in ? sum : 0.0;
         acc[0] += sum;
-        if (CX[i]) acc[1] += CX[i] * sum;
-        if (CY[i]) acc[2] += CY[i] * sum;
-        if (CZ[i]) acc[3] += CZ[i] * sum;
+        if (CX[i]) acc[1] += dir * CX[i] * sum;
+        if (CY[i]) acc[2] += dir * CY[i] * sum;
+        if (CZ[i]) acc[3] += dir * CZ[i] * sum;
       }
     }
   } else {
@@ -1685,11 +1927,6 @@ __global__ __launch_bounds__(WG) void k_check(LbArgs A) {
       T raw[Q];
 #pragma unroll
       for (int i = 0; i < Q; i++) raw[i] = arena[aidx(b, i, x, y, z)];
-      // where slot i of this node streams to, and along which direction:
-      // two buffers and an in-place even step (slot OPP[i] holds f*_OPP[i],
-      // moving along -c_i) move it on, an in-place odd step left it in place
-      const int mv = A.aa ? ((step & 1) ? 0 : -1) : 1;
-      const int dir = A.aa && !(step & 1) ? -1 : 1;
 #pragma unroll
       for (int i = 0; i < Q; i++) {
         int tx = x + mv * CX[i], ty = y + mv * CY[i], tz = z + mv * CZ[i];

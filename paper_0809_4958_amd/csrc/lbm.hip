@@ -58,6 +58,7 @@ struct BoxHost {
   int ylog = 0;      // log2 of the y lines interleaved per population row
   int xf_off = -1;   // row boxes: first float of the x-face velocities
   int vw = 0;        // row boxes: 32-bit words per lane vector
+  int px = 0, nyb = 0;  // nodes per row and blocks of rows per plane in memory
   // accelerated-frame body force: tracer acceleration samples on the device
   double* d_body = nullptr;
   int body_dt = 1, body_ns = 0;
@@ -125,6 +126,13 @@ size_t store_bytes(int s) { return s == LB_STORE_F64 ? 8 : (s == LB_STORE_F32 ? 
 // nodes per lane of the row items with w 32-bit words per lane
 int row_nodes(int s, int w) { return w * 4 / (int)store_bytes(s); }
 
+// Whether the lane groups of a row of px nodes (w words per lane) end where a
+// wavefront does.
+bool whole_wave_rows(int storage, int px, int w) {
+  const int L = px / row_nodes(storage, w);
+  return 64 % L == 0 || L % 64 == 0;
+}
+
 // Lane-vector width of a row box: prefer 2 words, then 3, among the widths
 // whose lane groups per row divide a wavefront (or fill whole wavefronts) --
 // groups of a row that straddle wavefronts need a halo load per wavefront
@@ -134,11 +142,42 @@ int pick_row_words(int storage, int nx) {
   for (int w : {2, 3}) {
     const int V = row_nodes(storage, w);
     if (nx % V != 0 || nx < 2 * V) continue;
-    const int L = nx / V;
-    if (64 % L == 0 || L % 64 == 0) return w;
+    if (whole_wave_rows(storage, nx, w)) return w;
     if (!fallback) fallback = w;
   }
   return fallback;
+}
+
+// Nodes per row in memory of a row box, 0 where the box runs as tiles (FP64, or
+// so short that x = 0 and x = nx - 1 would share a lane vector).  Rows may be
+// padded: a step costs least per stored node when rows are multiples of 64
+// bytes, a little more when lane groups then straddle wavefronts, and a fifth
+// to two fifths more otherwise, so the pitch with the least nodes times
+// that factor is taken.  Measured ns per interior node (boxes of nx x 96 x 96,
+// pitch in brackets): FP16 nx = 60 0.0228 [60] 0.0174 [64], 100 0.0232 [100]
+// 0.0221 [104] 0.0201 [128], 121 0.0235 [136] 0.0169 [128], 45 0.0208 [48]
+// 0.0233 [64], 150 0.0213 [152] 0.0184 [160]; FP32 50 0.0456 [50] 0.0355
+// [64], 121 0.0410 [124] 0.0289 [128], 130 0.0397 [130] 0.0343 [144] 0.0358 [160].
+int row_pitch(int storage, int nx) {
+  if (storage == LB_STORE_F64 || nx <= row_nodes(storage, 2)) return 0;
+  const int sb = (int)store_bytes(storage), unit = 16 / sb;
+  int best = 0;
+  double least = 0.0;
+  auto consider = [&](int px) {
+    const int w = pick_row_words(storage, px);
+    if (!w) return;
+    const bool whole = whole_wave_rows(storage, px, w);
+    const double cost = px * (px * sb % 64 == 0 ? (whole ? 1.0 : 1.08)
+                              : px % unit == 0  ? (whole ? 1.2 : 1.32)
+                                                : 1.4);
+    if (!best || cost < least) {
+      best = px;
+      least = cost;
+    }
+  };
+  consider(nx);
+  for (int px = (nx + unit - 1) / unit * unit; 2 * px <= 3 * nx + 2 * unit; px += unit) consider(px);
+  return best;
 }
 
 // Staging of the allocation-free site readout (lb_read_sites_noalloc): the
@@ -419,7 +458,7 @@ void load_tune_cache(lb_ctx* ctx) {
     }
     if (b.vec && (v[4] == 2 || v[4] == 3)) {
       const int V = row_nodes(ctx->S, v[4]);
-      if (b.dim.nx % V == 0 && b.dim.nx >= 2 * V) b.vw = v[4];
+      if (b.px % V == 0 && b.dim.nx > V) b.vw = v[4];
     }
   }
 }
@@ -465,7 +504,7 @@ lb_status build_tables(lb_ctx* ctx, int grid_override) {
       // interior rows cut into lane groups of V nodes, numbered row by row
       // (y fastest, then z); an item is b.ez workgroup iterations of WG groups
       const int V = row_nodes(ctx->S, b.vw);
-      const int L = b.dim.nx / V, nyi = b.dim.ny - 2;
+      const int L = b.px / V, nyi = b.dim.ny - 2;
       const int64_t groups = (int64_t)L * nyi * (b.dim.nz - 2);
       const int64_t per = (int64_t)WG * std::max(1, b.ez);
       for (int64_t g0 = 0; g0 < groups; g0 += per) {
@@ -634,6 +673,8 @@ lb_status upload_boxes(lb_ctx* ctx) {
     d.vec = b.vec ? 1 : 0;
     d.ylog = b.ylog;
     d.vw = b.vw;
+    d.px = b.px;
+    d.nyb = b.nyb;
     d.xf_off = b.xf_off;
     d.index = (int)i;
     d.body = b.body_ns > 0 ? b.d_body : nullptr;
@@ -1105,27 +1146,35 @@ lb_status lb_init(const lb_config* cfg, lb_ctx** out) {
     // every box starts on a 128-element boundary (aligned vector access)
     off = (off + 127) / 128 * 128;
     b.off = off;
-    off += nn * Q;
+    b.px = n3[0];
+    b.nyb = n3[1];
     {
-      b.vw = cfg->storage == LB_STORE_F64 ? 0 : pick_row_words(cfg->storage, n3[0]);
+      const int px = row_pitch(cfg->storage, n3[0]);
+      b.vw = px ? pick_row_words(cfg->storage, px) : 0;
       const int V = b.vw ? row_nodes(cfg->storage, b.vw) : 1;
-      const double groups = (double)(n3[0] / V) * (n3[1] - 2) * (n3[2] - 2);
-      // 32-bit buffer offsets: the planes one workgroup iteration touches
-      const double plane = (double)Q * n3[0] * n3[1] * (double)store_bytes(cfg->storage);
-      const double span = (WG / ((double)(n3[0] / V) * (n3[1] - 2)) + 4.0) * plane;
-      b.vec = b.vw != 0 && !ctx->per && !ctx->aa && groups < 2.0e9 && span < 2147483648.0 && !getenv("LBM_NO_VEC");
       // interleave Y = 2^ylog lines per population row so that a row of a
-      // block spans whole 128-byte lines (row boxes only)
-      b.ylog = 0;
+      // block spans whole 128-byte lines; padded rows also pad ny to whole
+      // blocks of up to eight
+      const int rowb = px * (int)store_bytes(cfg->storage);
+      int ylog = 0;
+      for (int yl = 0; yl <= (px > n3[0] ? 3 : 2); yl++)
+        if ((rowb << yl) % 128 == 0 && (px > n3[0] || n3[1] % (1 << yl) == 0)) {
+          ylog = yl;
+          break;
+        }
+      const int nyb = (n3[1] + (1 << ylog) - 1) >> ylog;
+      const double groups = (double)(px / V) * (n3[1] - 2) * (n3[2] - 2);
+      // 32-bit buffer offsets: the planes one workgroup iteration touches
+      const double plane = (double)Q * rowb * (nyb << ylog);
+      const double span = (WG / ((double)(px / V) * (n3[1] - 2)) + 4.0) * plane;
+      b.vec = b.vw != 0 && !ctx->per && groups < 2.0e9 && span < 2147483648.0 && !getenv("LBM_NO_VEC");
       if (b.vec) {
-        const int rowb = n3[0] * (int)store_bytes(cfg->storage);
-        for (int yl = 0; yl <= 2; yl++)
-          if ((rowb << yl) % 128 == 0 && n3[1] % (1 << yl) == 0) {
-            b.ylog = yl;
-            break;
-          }
+        b.px = px;
+        b.ylog = ylog;
+        b.nyb = nyb;
       }
     }
+    off += (int64_t)Q * b.px * ((int64_t)b.nyb << b.ylog) * n3[2];
     face_tables(b);
     default_tile(b);
     ctx->bx.push_back(b);
@@ -2123,10 +2172,10 @@ lb_status lb_autotune(lb_ctx* ctx, int32_t trials) {
     if (ref.vec) {  // row boxes: workgroup iterations per item (ez) and lane-vector width
       for (int w : {2, 3}) {
         const int V = row_nodes(ctx->S, w);
-        if (ref.dim.nx % V != 0 || ref.dim.nx < 2 * V) continue;
+        if (ref.px % V != 0 || ref.dim.nx <= V) continue;
         // the 32-bit offsets of a workgroup iteration's planes (as lb_init checks)
-        const double plane = (double)Q * ref.dim.nx * ref.dim.ny * (double)store_bytes(ctx->S);
-        const double span = (WG / ((double)(ref.dim.nx / V) * (ref.dim.ny - 2)) + 4.0) * plane;
+        const double plane = (double)Q * ref.px * (ref.nyb << ref.ylog) * (double)store_bytes(ctx->S);
+        const double span = (WG / ((double)(ref.px / V) * (ref.dim.ny - 2)) + 4.0) * plane;
         if (span >= 2147483648.0) continue;
         for (int ez : {2, 4, 8, 16, 32, 64}) cands.push_back({ref.ex, ref.ey, ez, w});
       }

@@ -166,3 +166,39 @@ def test_overstretched_bond_latches_at_the_oracles_step(beads):
     assert ctx.read(0, lbm.F_STEP, strict=False)[0] == ob.step_index
     check(compare(ctx, ob, case, "f64", strict=False), "f64", "overstretched")
     ctx.close()
+
+
+@pytest.mark.parametrize("streaming", ["two_buffers", "in_place"])
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("dims", [(3, 3, 3), (4, 5, 3), (5, 4, 6), (7, 9, 5), (8, 6, 7), (13, 12, 11), (33, 10, 6),
+                                  (48, 7, 5), (63, 6, 9), (64, 5, 6), (65, 8, 5), (121, 9, 7), (130, 6, 5),
+                                  (254, 5, 4), (263, 4, 5), (1030, 4, 4)])
+def test_rows_of_any_length(dims, storage, streaming):
+    """Rows that lane vectors divide and rows padded to them, shorter than a
+    wavefront, longer, and cut by its edges at every place; two buffers (read
+    in place, then pulled) and in place (both parities); two boxes, the second
+    with its axes turned, and where one fits a chain next to a wall."""
+    rng = np.random.default_rng(53)
+    cases = []
+    for k, d in enumerate((dims, (dims[1], dims[2], dims[0]))):
+        A = inputs.ou_strain(10, rng, corr_steps=20.0, rms=1e-3 * 8 / max(d))
+        chains = [walk(6, [2.6, 2.4, (d[2] - 1) / 2.0], rng, CHAIN_BOND)] if min(d) >= 5 else []
+        cases.append(Case(d, collision=oracle.MRT, tau=0.8, bc=(oracle.BC_AFFINE, A, 0, 1, 0),
+                          u0=1e-3 * rng.standard_normal(d[::-1] + (3,)), chains=chains, reduce_every=2))
+    say("case rows", dims, storage, streaming)
+    ctx = lbm.Context([c.dims for c in cases], collision=oracle.MRT, tau=0.8, storage=STORE[storage], reduce_every=2,
+                      streaming=lbm.STREAM_AA if streaming == "in_place" else lbm.STREAM_AB)
+    for k, c in enumerate(cases):
+        c.add_to(ctx, k)
+    obs = [c.oracle_box() for c in cases]
+    for n in (1, 1, 3, 4):
+        ctx.step(n)
+        assert ctx.sync_status() == lbm.OK
+        for k, c in enumerate(cases):
+            assert obs[k].step(n) == 0
+            check(compare(ctx, obs[k], c, storage, box=k), storage, f"rows {c.dims} {streaming}")
+            mm_o, mm_g = obs[k].mass_mom(), ctx.read(k, lbm.F_MASS_MOM)
+            if mm_o[0] > 0:
+                assert mm_g[0] == mm_o[0]
+                assert np.abs(mm_g[1:] - mm_o[1:]).max() < {"f32": 1e-6, "f16": 1e-5}[storage] * mm_o[1]
+    ctx.close()
