@@ -172,8 +172,8 @@ int conv_bands(int batch, int per_cu) {
   return bands;
 }
 
-// win.samples != NULL: the window path (inputs gathered by the lift, the
-// face field written by the last layer into u_out; r is not kept)
+// win.samples != NULL: the window path (inputs gathered by the lift; r is not
+// kept).  u_out: the face field, written by the last layer
 // loss.truth != NULL: the training forward, whose last layer also writes dy
 // and the loss partials
 lb_status forward(lbn_ctx* ctx, const float* coarse, const float* theta, int batch,
@@ -190,20 +190,14 @@ lb_status forward(lbn_ctx* ctx, const float* coarse, const float* theta, int bat
   int bands = 1;
   while (bands < IMG / TR && batch * bands < 240) bands *= 2;
   hipLaunchKernelGGL(k_head, dim3(batch * bands), dim3(NBC), 24 * R * R * sizeof(float), st, coarse, theta, win,
-                     R, ctx->w1f, ctx->p + OFF_B1, ctx->a1, u_out ? nullptr : ctx->x0, ctx->base, ctx->scale,
+                     R, ctx->w1f, ctx->p + OFF_B1, ctx->a1, win.samples ? nullptr : ctx->x0, ctx->base, ctx->scale,
                      bands);
   // layers 2 and 3 in one pass; the layer-2 output is stored only outside
   // the window path (the backward pass and lbn_read_buffer read it)
   const int b1 = conv_bands(batch, 1);
-  if (u_out)
-    hipLaunchKernelGGL((k_conv23<3>), dim3(batch * b1), dim3(NBC), 0, st, ctx->a1, ctx->w2f, ctx->p + OFF_B2,
-                       ctx->w3f, ctx->p + OFF_B3, nullptr, (void*)u_out, b1, ctx->base, ctx->scale, loss);
-  else if (loss.truth)
-    hipLaunchKernelGGL((k_conv23<2>), dim3(batch * b1), dim3(NBC), 0, st, ctx->a1, ctx->w2f, ctx->p + OFF_B2,
-                       ctx->w3f, ctx->p + OFF_B3, ctx->a2, (void*)ctx->r, b1, ctx->base, ctx->scale, loss);
-  else
-    hipLaunchKernelGGL((k_conv23<1>), dim3(batch * b1), dim3(NBC), 0, st, ctx->a1, ctx->w2f, ctx->p + OFF_B2,
-                       ctx->w3f, ctx->p + OFF_B3, ctx->a2, (void*)ctx->r, b1, ctx->base, ctx->scale, loss);
+  auto conv23 = win.samples ? k_conv23<3> : (loss.truth ? k_conv23<2> : k_conv23<1>);
+  hipLaunchKernelGGL(conv23, dim3(batch * b1), dim3(NBC), 0, st, ctx->a1, ctx->w2f, ctx->p + OFF_B2, ctx->w3f,
+                     ctx->p + OFF_B3, win.samples ? nullptr : ctx->a2, ctx->r, u_out, b1, ctx->base, ctx->scale, loss);
   HIPCHK(hipGetLastError());
   ctx->last_batch = batch;
   return LB_OK;
@@ -282,7 +276,7 @@ lb_status lbn_init(const lbn_config* cfg, lbn_ctx** out) {
   ctx->dy = dalloc_t<__bf16>(ctx, px * COUT, &ok);
   ctx->dz1 = dalloc_t<__bf16>(ctx, px * CH, &ok);
   ctx->dz2 = dalloc_t<__bf16>(ctx, px * CH, &ok);
-  ctx->r = dalloc_t<float>(ctx, px * COUT, &ok);
+  ctx->r = dalloc_t<float>(ctx, px * RCH, &ok);
   ctx->base = dalloc_t<float>(ctx, px * 3, &ok);
   ctx->scale = dalloc_t<float>(ctx, B, &ok);
   ctx->part = dalloc_t<float>(ctx, (size_t)MAX_PART * NDEV, &ok);
@@ -299,8 +293,10 @@ lb_status lbn_init(const lbn_config* cfg, lbn_ctx** out) {
       lbn_free(ctx);
       return LB_ERR_HIP;
     }
-  // the range sums of the partial reduction: zero where it never writes
+  // the range sums of the partial reduction, and the padded channels of dy:
+  // zero where no kernel writes
   if (hipMemsetAsync(ctx->part_seg, 0, (size_t)RSEG * NDEV * sizeof(float), ctx->stream) != hipSuccess ||
+      hipMemsetAsync(ctx->dy, 0, px * COUT * sizeof(__bf16), ctx->stream) != hipSuccess ||
       hipStreamSynchronize(ctx->stream) != hipSuccess) {
     lbn_free(ctx);
     return LB_ERR_HIP;
@@ -340,13 +336,7 @@ lb_status lbn_forward(lbn_ctx* ctx, const float* coarse_dev, const float* theta_
   lb_status s = check_batch(ctx, batch);
   if (s) return s;
   if (!coarse_dev || !theta_dev || !out_dev) return fail(ctx, LB_ERR_ARG, "null pointer");
-  s = forward(ctx, coarse_dev, theta_dev, batch);
-  if (s) return s;
-  const int n_px = batch * IMG * IMG;
-  hipLaunchKernelGGL(k_combine, dim3((n_px + 255) / 256), dim3(256), 0, ctx->stream, ctx->r, ctx->base,
-                     ctx->scale, n_px, out_dev);
-  HIPCHK(hipGetLastError());
-  return LB_OK;
+  return forward(ctx, coarse_dev, theta_dev, batch, LiftWindow{nullptr, 0, 0, 1}, out_dev);
 }
 
 lb_status lbn_window_forward(lbn_ctx* ctx, const float* samples_dev, int32_t n_samples, int32_t k,
@@ -446,6 +436,11 @@ lb_status lbn_read_buffer(lbn_ctx* ctx, int32_t which, int32_t batch, float* out
       const uint32_t u = (uint32_t)raw[i] << 16;
       std::memcpy(&out[i], &u, 4);
     }
+  } else if (which == 3) {  // kept without the padded channels, which are zero
+    std::vector<float> r(px * RCH);
+    HIPCHK(hipMemcpyAsync(r.data(), src, r.size() * 4, hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHK(hipStreamSynchronize(ctx->stream));
+    for (size_t i = 0; i < count; i++) out[i] = i % COUT < RCH ? r[i / COUT * RCH + i % COUT] : 0.0f;
   } else {
     HIPCHK(hipMemcpyAsync(out, src, count * 4, hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));

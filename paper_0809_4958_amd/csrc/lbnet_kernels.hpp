@@ -48,7 +48,12 @@ constexpr int IMG = 64;     // image edge (face nodes)
 constexpr int CIN = 16;     // lifted input channels (15 used)
 constexpr int CH = 64;      // hidden channels
 constexpr int COUT = 16;    // output channels of the last layer (3 used)
+constexpr int RCH = 4;      // of them kept of the network output r
 constexpr int NTAP = 9;
+#ifndef LBN_KEEP23
+#define LBN_KEEP23 true
+#endif
+constexpr bool KEEP23 = LBN_KEEP23;
 
 __device__ __forceinline__ __bf16 to_bf16(float v) { return (__bf16)v; }  // round to nearest even
 __device__ __forceinline__ float from_bf16(__bf16 v) { return (float)v; }
@@ -309,175 +314,229 @@ __device__ __forceinline__ void store_row(const f32x4 (&acc)[MB][CO / 16], int b
 }
 
 // ---------------------------------------------------------------- layers 2 + 3
-// Layer 2 (64 -> 64, bias, ReLU) and layer 3 (64 -> 16) in one pass, so the
+// Layer 2 (64 -> 64, bias, ReLU) and layer 3 (64 -> 3) in one pass, so the
 // layer-2 activations stay on chip.  Workgroup g takes the 64 / bands output
-// rows [yb, ye) of band g % bands of image g / bands in steps of two rows:
-// step s makes layer-2 rows ya, ya + 1 (ya = yb - 1 + 2 s) from layer-1 rows
-// ya - 1 .. ya + 2 and then layer-3 rows ya - 1, ya (for s >= 1) from layer-2
-// rows ya - 2 .. ya + 1.  Both activations live in LDS rings of four rows
-// (row yy in slot (yy + 4) % 4, 66 pixels with a zero halo); the weights of
-// both layers are staged once (159,744 bytes of LDS in all).  The layer-1
-// rows of the next step travel in registers one step ahead.  Layer-2 rows
-// outside the image are zero (layer 3's padding); the two layer-2 rows past
-// each end of a band are computed by both neighbours.  Each output is the
-// same chain of products (conv_products, chunks in order of increasing K) as
-// a convolution of one layer at a time would compute, so the results do not
-// depend on the band split or the fusion.  a2_out != NULL also stores the band's
-// layer-2 rows (the backward pass reads them).  EPI3: 1 (r), 2 (r and the
-// loss: dy and one partial of sum e^2 per workgroup, see loss_epilogue) or 3 (u).
+// rows [yb, ye) of band g % bands of image g / bands in steps of four rows:
+// step s makes layer-2 rows ya .. ya + 3 (ya = yb - 1 + 4 s), one per wave pair
+// (32 pixels x 64 channels each: 6 LDS fragments for 8 products; 32 x 32 in
+// steps of two rows took one fragment a product), from layer-1 rows ya - 1 ..
+// ya + 4, which live in an LDS ring of six rows (row yy in slot (yy + 6) % 6,
+// 66 pixels with a zero halo); the rows of the next step travel in registers
+// one step ahead.
+// Layer 3 has three output channels, a fifth of a 16-row product block, so it
+// is not convolved: the 27 products of a layer-2 pixel with the weights of
+// every tap and channel, P[tap][co] = sum_ci w3[tap][co][ci] a2[ci], are one
+// 64-deep product straight from the accumulators' bf16 values (two blocks of
+// 16 slots, 8 matrix instructions per wave and step against 36 before, and
+// no LDS copy of the layer-2 rows), and the output is the sum over taps
+// of the P of its nine neighbours, in increasing tap: the first rows of that
+// sum are carried to the next step in registers, so it does not depend on the
+// band split.  Layer-2 rows and pixels outside the image contribute nothing
+// (layer 3's padding); the rows past each end of a band are computed by both
+// neighbours.  a2_out != NULL also stores the band's layer-2 rows (the backward
+// pass reads them).  EPI3: 1 (r and u), 2 (r and the loss: dy and one partial
+// of sum e^2 per workgroup, see loss_epilogue) or 3 (u).
+// The output stage of a step runs in waves 0..3 before their products of the next,
+// beside those of waves 4..7 on the same matrix cores.
+// Bound by the latencies between a step's barriers, which one workgroup per
+// compute unit (the weights fill half its LDS) cannot hide: of a step's 4.5 us
+// 2.2 are products at the matrix cores' rate.  Two workgroups per unit with
+// the weights in registers spilled and were slower (84 us for the window).
+// Measured, before (layer 3 as a convolution, steps of two rows) and now: the
+// window's 120 images (EPI3 3) 61.6 -> 47.1 us; 240 images (EPI3 1) 124.5 -> 104
+// us and the pass that formed u from r gone; 64 in training (EPI3 2) 42.2 -> 37.0.
 struct LossOut {
   const float* truth;  // [B][64][64][3]
   float dy_scale;      // 2 / count
-  __bf16* dy;          // [B][64][64][16]
+  __bf16* dy;          // [B][64][64][16], channels 4..15 zero
   double* part;        // one partial per workgroup
 };
 
 // e = (pred - truth) / s with pred = base + s r (channels 0..2 of the fp32
 // last-layer output r): the error in units of the sample's coarse RMS; the
-// loss is the mean of e^2 and dy = dL/dr = 2 e / count (bf16, channels 3..15
-// zero).  A lane holds channels c3 .. c3 + 3 of pixel p; returns its e^2 sum.
-__device__ __forceinline__ double loss_epilogue(const float (&r)[4], int c3, size_t p, float s,
+// loss is the mean of e^2 and dy = dL/dr = 2 e / count (bf16, the other
+// channels zero).  Returns the e^2 sum of pixel p.
+__device__ __forceinline__ double loss_epilogue(const float (&r)[3], size_t p, float s,
                                                 const float (&bs)[3], const float (&tr)[3],
                                                 const LossOut& L) {
   __bf16 d[4] = {to_bf16(0.0f), to_bf16(0.0f), to_bf16(0.0f), to_bf16(0.0f)};
   double acc = 0.0;
-  if (c3 == 0) {
 #pragma unroll
-    for (int c = 0; c < 3; c++) {
-      const float pred = bs[c] + s * r[c];
-      const float e = (pred - tr[c]) / s;
-      acc += (double)e * (double)e;
-      d[c] = to_bf16(L.dy_scale * e);
-    }
+  for (int c = 0; c < 3; c++) {
+    const float pred = bs[c] + s * r[c];
+    const float e = (pred - tr[c]) / s;
+    acc += (double)e * (double)e;
+    d[c] = to_bf16(L.dy_scale * e);
   }
-  *(uint2*)&L.dy[p * COUT + c3] = *(const uint2*)d;
+  *(uint2*)&L.dy[p * COUT] = *(const uint2*)d;
   return acc;
 }
+
+constexpr int SR4 = 4;            // rows of a step
+constexpr int RING = SR4 + 2;     // rows of an activation ring
+constexpr int NP3 = NTAP * 3;     // layer 3's products of a pixel: tap 3 + co
+constexpr int PW = IMG + 4;       // LDS pitch of a row of them: rows 4 apart 16 banks apart
 
 template <int EPI3>
 __global__ __launch_bounds__(NBC) void k_conv23(const __bf16* __restrict__ a1, const __bf16* __restrict__ w2,
                                                 const float* __restrict__ b2, const __bf16* __restrict__ w3,
                                                 const float* __restrict__ b3, __bf16* __restrict__ a2_out,
-                                                void* __restrict__ out, int bands,
-                                                const float* __restrict__ base,
+                                                float* __restrict__ r_out, float* __restrict__ u_out,
+                                                int bands, const float* __restrict__ base,
                                                 const float* __restrict__ scale, LossOut L) {
   constexpr int C = CH, RW = IMG + 2;          // channels, pixels of a staged row
-  constexpr int RV = RW * (C / 8);             // 16-byte vectors of one staged row
-  constexpr int XS = (2 * RV + NBC - 1) / NBC;
   __shared__ __attribute__((aligned(16))) __bf16 s_w2[NTAP * C * C];
-  __shared__ __attribute__((aligned(16))) __bf16 s_w3[NTAP * COUT * C];
-  __shared__ __attribute__((aligned(16))) __bf16 s_a1[4 * RW * C];
-  __shared__ __attribute__((aligned(16))) __bf16 s_a2[4 * RW * C];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ __attribute__((aligned(16))) __bf16 s_a1[RING * RW * C];
+  __shared__ __attribute__((aligned(16))) float s_p[SR4][NP3][PW];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int b = blockIdx.x / bands, band = blockIdx.x - b * bands;
   const int rows = IMG / bands, yb = band * rows, ye = yb + rows;
   stage_weights<C, C>(w2, s_w2, tid);
-  stage_weights<C, COUT>(w3, s_w3, tid);
-  for (int i = tid; i < 4 * RV; i += NBC) *(uint4*)&s_a2[8 * i] = make_uint4(0u, 0u, 0u, 0u);
-  uint4 xr[XS];
-  auto load_rows = [&](int y) {  // layer-1 rows y, y + 1 into registers
+  // Staging: pixels 0 .. 63 of a row are 512 vectors, one per thread; the zero
+  // halo pixels stay from here on.
+  static_assert(IMG * (C / 8) == NBC, "a thread stages one vector of a row");
+  uint4 xr[SR4];
+  const int sx = tid / (C / 8), sc = tid % (C / 8);  // this thread's pixel and chunk
+  const __bf16* a1t = a1 + ((size_t)b * IMG * IMG + sx) * C + 8 * sc;
+  auto load_rows = [&](int y) {  // layer-1 rows y .. y + 3 into registers
 #pragma unroll
-    for (int j = 0; j < XS; j++) {
-      const int v = tid + j * NBC;
+    for (int j = 0; j < SR4; j++) {
       xr[j] = make_uint4(0u, 0u, 0u, 0u);
-      if (v < 2 * RV) {
-        const int c8 = v % (C / 8), q = v / (C / 8);
-        const int xx = q % RW - 1, yy = y + q / RW;
-        if (yy >= 0 && yy < IMG && xx >= 0 && xx < IMG)
-          xr[j] = *(const uint4*)&a1[(((size_t)b * IMG + yy) * IMG + xx) * C + 8 * c8];
-      }
+      if (y + j >= 0 && y + j < IMG) xr[j] = *(const uint4*)(a1t + (size_t)(y + j) * IMG * C);
     }
   };
-  auto put_rows = [&](int y) {
+  auto put_rows = [&](int y, int j0) {
 #pragma unroll
-    for (int j = 0; j < XS; j++) {
-      const int v = tid + j * NBC;
-      if (v < 2 * RV) {
-        const int c8 = v % (C / 8), q = v / (C / 8);
-        const int yy = y + q / RW;
-        *(uint4*)&s_a1[lds_at<C>(((yy + 4) & 3) * RW + q % RW, c8)] = xr[j];
-      }
-    }
+    for (int j = 0; j < SR4; j++)
+      if (j >= j0) *(uint4*)&s_a1[lds_at<C>(((y + j + RING) % RING) * RW + sx + 1, sc)] = xr[j];
   };
-  // layer-1 rows yb - 2 .. yb + 1 for step 0, rows yb + 2, yb + 3 in flight
-  load_rows(yb - 2);
-  put_rows(yb - 2);
+  for (int i = tid; i < RING * 2 * (C / 8); i += NBC) {
+    const int row = i / (2 * (C / 8)), k = i % (2 * (C / 8));
+    *(uint4*)&s_a1[lds_at<C>(row * RW + (k / (C / 8)) * (RW - 1), k % (C / 8))] = make_uint4(0u, 0u, 0u, 0u);
+  }
+  // layer-1 rows yb - 2 .. yb + 3 for step 0, the next four in flight
+  load_rows(yb - SR4);
+  put_rows(yb - SR4, 2);
   load_rows(yb);
-  put_rows(yb);
-  load_rows(yb + 2);
-  // layer 2: wave = (row r2, pixel half, channel half); layer 3: (row r3, pixel block)
-  const int r2 = wave >> 2, q = wave & 3, px2 = 32 * (q & 1), nb2 = 2 * (q >> 1);
-  const int px3 = 16 * q;
-  const int g = lane >> 4, c2 = 16 * g + 8 * (q >> 1);  // the 8 layer-2 channels a lane holds
-  const int c3 = 4 * g;                                  // the 4 layer-3 channels a lane holds
-  float bb2[8], bb3[4];                                  // their biases, loaded once
+  put_rows(yb, 0);
+  load_rows(yb + SR4);
+  // layer 2: wave = (row, pixel half), all channels; lane: pixel lane % 16 of a
+  // block, the 16 channels from 16 (lane / 16)
+  const int r2 = wave & 3, px2 = 32 * (wave >> 2), g = lane >> 4, c2 = 16 * g;
+  float bb2[16];
 #pragma unroll
-  for (int k = 0; k < 8; k++) bb2[k] = b2[c2 + k];
+  for (int k = 0; k < 16; k++) bb2[k] = b2[c2 + k];
+  // layer 3's weights, one row of 16 slots per lane: slot m = tap 3 + co, the
+  // K values of lane group g and half k the channels 16 g + 8 k ..
+  bf16x8 w3f[2][2];
 #pragma unroll
-  for (int k = 0; k < 4; k++) bb3[k] = b3[c3 + k];
-  __syncthreads();
+  for (int m16 = 0; m16 < 2; m16++) {
+    const int m = 16 * m16 + (lane & 15), tap = m / 3, co = m - 3 * tap;
+#pragma unroll
+    for (int k = 0; k < 2; k++)
+      w3f[m16][k] = m < NP3 ? *(const bf16x8*)&w3[((size_t)tap * COUT + co) * C + c2 + 8 * k] : bf16x8{};
+  }
+  // the output stage: waves 0..3, row ya - 1 + wave, pixel lane
+  float bb3[3], carry[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < 3; k++) bb3[k] = b3[k];
+  // adds row dy = dyi - 1's three taps of slot row rs to t
+  auto add_taps = [&](float (&t)[3], int rs, int dyi) {
+#pragma unroll
+    for (int dxi = 0; dxi < 3; dxi++) {
+      const int x = lane + dxi - 1;
+      const bool in = x >= 0 && x < IMG;
+      const float* p = &s_p[rs][(3 * dyi + dxi) * 3][in ? x : lane];
+#pragma unroll
+      for (int c = 0; c < 3; c++) t[c] += in ? p[c * PW] : 0.0f;
+    }
+  };
   double lsum = 0.0;  // this lane's sum of e^2 (EPI3 2)
-  const int nsteps = rows / 2 + 1;
-  for (int st = 0; st < nsteps; st++) {
-    const int ya = yb - 1 + 2 * st;
+  const int nsteps = (rows + 2 + SR4 - 1) / SR4;
+  auto outputs = [&](int ya) {
+    const int y = ya - 1 + wave;  // output row of this wave: layer-2 rows y - 1 .. y + 1
+    const bool mine = y >= yb && y < ye;
+    const size_t p = ((size_t)b * IMG + y) * IMG + lane;
+    // the epilogue's inputs are loaded before the sums
+    float bs[3] = {0.f, 0.f, 0.f}, tr[3] = {0.f, 0.f, 0.f}, sb = 0.f;
+    if (mine) {
+      sb = scale[b];
+#pragma unroll
+      for (int k = 0; k < 3; k++) {
+        bs[k] = base[p * 3 + k];
+        if (EPI3 == 2) tr[k] = L.truth[p * 3 + k];
+      }
+    }
+    float t[3] = {carry[0], carry[1], carry[2]};
+    if (wave >= 2) add_taps(t, wave - 2, 0);
+    if (wave >= 1) add_taps(t, wave - 1, 1);
+    add_taps(t, wave, 2);
+    // rows ya + 3 and ya + 4, the next step's first two, begin here
+#pragma unroll
+    for (int c = 0; c < 3; c++) carry[c] = 0.0f;
+    if (wave == 0) {
+      add_taps(carry, 2, 0);
+      add_taps(carry, 3, 1);
+    } else if (wave == 1) {
+      add_taps(carry, 3, 0);
+    }
+    if (!mine) return;
+    const float rr[3] = {t[0] + bb3[0], t[1] + bb3[1], t[2] + bb3[2]};
+    if constexpr (EPI3 != 3) *(float4*)&r_out[p * RCH] = make_float4(rr[0], rr[1], rr[2], 0.0f);
+    if constexpr (EPI3 != 2) {
+#pragma unroll
+      for (int k = 0; k < 3; k++) u_out[p * 3 + k] = bs[k] + sb * rr[k];
+    } else {
+      lsum += loss_epilogue(rr, p, sb, bs, tr, L);
+    }
+  };
+  __syncthreads();
+  // The output stage of step st runs in waves 0..3 before their products of step
+  // st + 1, beside those of waves 4..7 on the same matrix cores.
+  for (int st = 0; st <= nsteps; st++) {
+    const int ya = yb - 1 + SR4 * st;
+    if (st >= 1 && wave < SR4) outputs(ya - SR4);
+    if (st == nsteps) break;
     {
       const int y = ya + r2;  // layer-2 row of this wave
-      const int row_at[3] = {((y + 3) & 3) * RW, ((y + 4) & 3) * RW, ((y + 5) & 3) * RW};
-      f32x4 acc[2][2];
-      conv_products<C, C, true, 2, 2>(s_a1, s_w2, row_at, px2, lane, acc, nb2);
+      const int row_at[3] = {((y + RING - 1) % RING) * RW, ((y + RING) % RING) * RW, ((y + RING + 1) % RING) * RW};
+      f32x4 acc[2][4];
+      conv_products<C, C, true, 2, 4, KEEP23>(s_a1, s_w2, row_at, px2, lane, acc, 0);
+      __syncthreads();  // every product of the step and every read of s_p is done
+      if (st + 1 < nsteps) {
+        put_rows(ya + SR4 + 1, 0);  // into the slots of rows ya - 1 .. ya + 2
+        if (st + 2 < nsteps) load_rows(ya + 2 * SR4 + 1);
+      }
       const bool inside = y >= 0 && y < IMG;
 #pragma unroll
       for (int mb = 0; mb < 2; mb++) {
         const int px = px2 + 16 * mb + (lane & 15);
-        __bf16 h[8];
+        bf16x8 h[2];
 #pragma unroll
-        for (int nb = 0; nb < 2; nb++)
+        for (int nb = 0; nb < 4; nb++)
 #pragma unroll
           for (int j = 0; j < 4; j++) {
             const float t = acc[mb][nb][j] + bb2[4 * nb + j];
-            h[4 * nb + j] = to_bf16(inside && t > 0.0f ? t : 0.0f);
+            h[nb >> 1][4 * (nb & 1) + j] = to_bf16(fmaxf(t, 0.0f));
           }
-        const uint4 hv = *(const uint4*)h;
-        *(uint4*)&s_a2[lds_at<C>(((y + 4) & 3) * RW + px + 1, c2 >> 3)] = hv;
-        if (a2_out && y >= yb && y < ye)
-          *(uint4*)&a2_out[(((size_t)b * IMG + y) * IMG + px) * C + c2] = hv;
-      }
-    }
-    __syncthreads();  // layer-2 rows ya, ya + 1 in; layer-1 rows ya - 1, ya free
-    if (st + 1 < nsteps) {
-      put_rows(ya + 3);
-      if (st + 2 < nsteps) load_rows(ya + 5);
-    }
-    if (st >= 1) {
-      const int y = ya - 1 + r2;  // layer-3 row of this wave
-      const int row_at[3] = {((y + 3) & 3) * RW, ((y + 4) & 3) * RW, ((y + 5) & 3) * RW};
-      const size_t p = ((size_t)b * IMG + y) * IMG + px3 + (lane & 15);
-      // the epilogue's inputs are loaded before the products
-      float bs[3] = {0.f, 0.f, 0.f}, tr[3] = {0.f, 0.f, 0.f}, sb = 0.f;
-      if (EPI3 >= 2 && g == 0) {
-        sb = scale[b];
+        if (!inside) h[0] = h[1] = bf16x8{};  // the padding of layer 3 (uniform)
+        if (a2_out && y >= yb && y < ye) {
+          __bf16* o = &a2_out[(((size_t)b * IMG + y) * IMG + px) * C + c2];
+          *(bf16x8*)o = h[0];
+          *(bf16x8*)(o + 8) = h[1];
+        }
 #pragma unroll
-        for (int k = 0; k < 3; k++) bs[k] = base[p * 3 + k];
-        if (EPI3 == 2) {
+        for (int m16 = 0; m16 < 2; m16++) {
+          f32x4 p = {0.f, 0.f, 0.f, 0.f};
+          p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w3f[m16][0], h[0], p, 0, 0, 0);
+          p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w3f[m16][1], h[1], p, 0, 0, 0);
 #pragma unroll
-          for (int k = 0; k < 3; k++) tr[k] = L.truth[p * 3 + k];
+          for (int j = 0; j < 4; j++)
+            if (16 * m16 + 4 * g + j < NP3) s_p[r2][16 * m16 + 4 * g + j][px] = p[j];
         }
       }
-      f32x4 acc[1][1];
-      conv_products<C, COUT, true, 1, 1, true>(s_a2, s_w3, row_at, px3, lane, acc, 0);
-      if constexpr (EPI3 == 3) {
-        if (g == 0) {
-#pragma unroll
-          for (int k = 0; k < 3; k++) ((float*)out)[p * 3 + k] = bs[k] + sb * (acc[0][0][k] + bb3[k]);
-        }
-      } else {
-        const float rr[4] = {acc[0][0][0] + bb3[0], acc[0][0][1] + bb3[1], acc[0][0][2] + bb3[2],
-                             acc[0][0][3] + bb3[3]};
-        *(float4*)&((float*)out)[p * COUT + c3] = make_float4(rr[0], rr[1], rr[2], rr[3]);
-        if constexpr (EPI3 == 2) lsum += loss_epilogue(rr, c3, p, sb, bs, tr, L);
-      }
     }
-    __syncthreads();  // layer-1 rows of the next step in; layer-3 reads of s_a2 done
+    __syncthreads();  // s_p and the next step's layer-1 rows are in
   }
   if constexpr (EPI3 == 2) {
     // the workgroup's partial: lanes, then waves, in a fixed order (the
@@ -485,11 +544,11 @@ __global__ __launch_bounds__(NBC) void k_conv23(const __bf16* __restrict__ a1, c
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) lsum += __shfl_xor(lsum, o);
     double* red = (double*)s_a1;
-    if (lane == 0) red[wave] = lsum;
+    if (lane == 0 && wave < SR4) red[wave] = lsum;
     __syncthreads();
     if (tid == 0) {
       double t = 0.0;
-      for (int w = 0; w < NBC / 64; w++) t += red[w];
+      for (int w = 0; w < SR4; w++) t += red[w];
       L.part[blockIdx.x] = t;
     }
   }
@@ -893,16 +952,6 @@ __global__ void k_reduce_parts(const float* __restrict__ part, int n_parts, int 
 #pragma unroll 8
   for (int g = g0; g < g1; g++) s += part[(size_t)g * n + i];
   out[(size_t)blockIdx.y * n + i] = s;
-}
-
-// u = base + s r for channels 0..2: out [B][64][64][3]
-__global__ void k_combine(const float* __restrict__ r, const float* __restrict__ base,
-                          const float* __restrict__ scale, int n_px, float* __restrict__ out) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n_px) return;
-  const float s = scale[p / (IMG * IMG)];
-#pragma unroll
-  for (int c = 0; c < 3; c++) out[(size_t)p * 3 + c] = base[(size_t)p * 3 + c] + s * r[(size_t)p * COUT + c];
 }
 
 // ---------------------------------------------------------------- parameters
