@@ -273,7 +273,7 @@ lb_status lbn_init(const lbn_config* cfg, lbn_ctx** out) {
   ctx->x0 = dalloc_t<__bf16>(ctx, px * CIN, &ok);
   ctx->a1 = dalloc_t<__bf16>(ctx, px * CH, &ok);
   ctx->a2 = dalloc_t<__bf16>(ctx, px * CH, &ok);
-  ctx->dy = dalloc_t<__bf16>(ctx, px * COUT, &ok);
+  ctx->dy = dalloc_t<__bf16>(ctx, px * RCH, &ok);
   ctx->dz1 = dalloc_t<__bf16>(ctx, px * CH, &ok);
   ctx->dz2 = dalloc_t<__bf16>(ctx, px * CH, &ok);
   ctx->r = dalloc_t<float>(ctx, px * RCH, &ok);
@@ -293,10 +293,8 @@ lb_status lbn_init(const lbn_config* cfg, lbn_ctx** out) {
       lbn_free(ctx);
       return LB_ERR_HIP;
     }
-  // the range sums of the partial reduction, and the padded channels of dy:
-  // zero where no kernel writes
+  // the range sums of the partial reduction: zero where it never writes
   if (hipMemsetAsync(ctx->part_seg, 0, (size_t)RSEG * NDEV * sizeof(float), ctx->stream) != hipSuccess ||
-      hipMemsetAsync(ctx->dy, 0, px * COUT * sizeof(__bf16), ctx->stream) != hipSuccess ||
       hipStreamSynchronize(ctx->stream) != hipSuccess) {
     lbn_free(ctx);
     return LB_ERR_HIP;
