@@ -739,6 +739,9 @@ __device__ __forceinline__ Ext<R> make_ext(const LbArgs& A, const BoxDesc& b, lo
   Ext<R> e;
   body_accel<R>(b, step, e.ax, e.ay, e.az);
   e.mu = (R)(3.0 * A.kT);
+  e.sb = (R)sqrt(A.om_bulk * (2.0 - A.om_bulk));  // 1 - (1 - omega)^2
+  e.ss = (R)sqrt(A.omega * (2.0 - A.omega));
+  e.sg = (R)sqrt(A.om_ghost * (2.0 - A.om_ghost));
   e.k0 = A.key0;
   e.k1 = A.key1;
   e.node = 0u;
@@ -748,22 +751,21 @@ __device__ __forceinline__ Ext<R> make_ext(const LbArgs& A, const BoxDesc& b, lo
 }
 
 // Collision with the extensions: the force density of the chains g plus the
-// body force -rho a (rho the node's pre-collision density), and the
-// fluctuating collision when mu > 0 (MRT only).
-template <typename R, int COLL, bool CW = false, bool WS = false>
+// body force -rho a (rho the node's pre-collision density; the MRT forward
+// transform's first moment), and with EXT 2 the fluctuating collision (MRT only).
+template <typename R, int COLL, int EXT, bool CW = false, bool WS = false>
 __device__ __forceinline__ void collide_ext(R d[Q], R gx, R gy, R gz, R rho0, R omega, R omb,
                                             R omg, const Ext<R>& e, R sc = R(1)) {
-  R drho = 0;
+  if constexpr (COLL != 0) {
+    collide_mrt_pairs<R, COLL == 2, EXT == 2, CW, WS>(d, gx, gy, gz, rho0, omega, omb, omg, &e, sc);
+  } else {
+    static_assert(EXT == 1, "thermal noise acts on the modes of the MRT collision");
+    R drho = 0;
 #pragma unroll
-  for (int i = 0; i < Q; i++) drho += d[i];
-  const R rho = rho0 + drho;
-  gx -= rho * e.ax;
-  gy -= rho * e.ay;
-  gz -= rho * e.az;
-  if (COLL != 0 && e.mu > (R)0)
-    collide_mrt_pairs<R, COLL == 2, true, CW, WS>(d, gx, gy, gz, rho0, omega, omb, omg, &e, sc);
-  else
-    collide_any<R, COLL, CW, WS>(d, gx, gy, gz, rho0, omega, omb, omg, sc);
+    for (int i = 0; i < Q; i++) drho += d[i];
+    const R rho = rho0 + drho;
+    collide_any<R, COLL, CW, WS>(d, gx - rho * e.ax, gy - rho * e.ay, gz - rho * e.az, rho0, omega, omb, omg, sc);
+  }
 }
 
 // Spread force g(x) = - sum_j w_jx dP_j at node (x, y, z): chains whose stencil
@@ -846,7 +848,7 @@ __device__ __forceinline__ void gather_force(const LbArgs& A, const BoxDesc& b,
 // Interior tile of a non-periodic box whose population groups (0..9 and
 // 10..18) each span less than 4 GiB: every load is one 32-bit offset add on
 // a per-thread node offset plus a scalar (uniform) group base.
-template <int S, int COLL, int BS, bool EXT>
+template <int S, int COLL, int BS, int EXT>
 __device__ __forceinline__ void tile_fast(const LbArgs& A, const BoxDesc& b, const Item& it,
                                           const typename Store<S>::T* src,
                                           typename Store<S>::T* dst, bool pre, long long step,
@@ -873,7 +875,7 @@ __device__ __forceinline__ void tile_fast(const LbArgs& A, const BoxDesc& b, con
   const R sc = (R)b.s2;
   const int plane = it.ex * it.ey;
   Ext<R> ext{};
-  if constexpr (EXT) ext = make_ext<R>(A, b, step);
+  if constexpr (EXT != 0) ext = make_ext<R>(A, b, step);
 #pragma unroll 1
   for (int p = threadIdx.x; p < plane; p += BS) {
     const int x = it.x0 + p % it.ex;
@@ -888,9 +890,9 @@ __device__ __forceinline__ void tile_fast(const LbArgs& A, const BoxDesc& b, con
         const float k = WCLS[i] == 0 ? dc0 : (WCLS[i] == 1 ? dc1 : dc2);
         d[i] = St::dec(v, k);
       }
-      if constexpr (EXT) {
+      if constexpr (EXT != 0) {
         ext.node = ((unsigned)z * ny + (unsigned)y) * nx + (unsigned)x;
-        collide_ext<R, COLL, comp_weights<S>(), S == 2>(d, (R)0, (R)0, (R)0, rho0, omega, omb, omg, ext, sc);
+        collide_ext<R, COLL, EXT, comp_weights<S>(), S == 2>(d, (R)0, (R)0, (R)0, rho0, omega, omb, omg, ext, sc);
       } else {
         collide_any<R, COLL, comp_weights<S>(), S == 2>(d, (R)0, (R)0, (R)0, rho0, omega, omb, omg, sc);
       }
@@ -1146,7 +1148,7 @@ struct PtrDst {
   }
 };
 
-template <int S, int W, int COLL, int MODE, int BS, bool EXT>
+template <int S, int W, int COLL, int MODE, int BS, int EXT>
 __device__ __forceinline__ void tile_rows(const LbArgs& A, const BoxDesc& b, const Item& it,
                                           const typename Store<S>::T* src,
                                           typename Store<S>::T* dst, long long step,
@@ -1184,7 +1186,7 @@ __device__ __forceinline__ void tile_rows(const LbArgs& A, const BoxDesc& b, con
   const int ps = (int)psb;
   auto ybytes = [&](int yy) { return (yy >> yl) * bkb + (yy & ym) * nxb; };
   Ext<R> ext{};
-  if constexpr (EXT) ext = make_ext<R>(A, b, step);
+  if constexpr (EXT != 0) ext = make_ext<R>(A, b, step);
 #pragma unroll 1
   for (int qb = it.x0; qb < q_end; qb += BS) {
     const int zf = 1 + (qb / L) / nyi;             // first plane of this iteration
@@ -1272,9 +1274,9 @@ __device__ __forceinline__ void tile_rows(const LbArgs& A, const BoxDesc& b, con
         d[i] = St::dec(velem<S, W>(raw[i], left[i], right[i], e), kd);
       }
       const int x = x0 + k;
-      if constexpr (EXT) {
+      if constexpr (EXT != 0) {
         ext.node = ((unsigned)z * (unsigned)ny + (unsigned)y) * (unsigned)nx + (unsigned)x;
-        collide_ext<R, COLL, comp_weights<S>(), S == 2>(d, (R)0, (R)0, (R)0, rho0, omega, omb, omg, ext, sc);
+        collide_ext<R, COLL, EXT, comp_weights<S>(), S == 2>(d, (R)0, (R)0, (R)0, rho0, omega, omb, omg, ext, sc);
       } else {
         collide_any<R, COLL, comp_weights<S>(), S == 2>(d, (R)0, (R)0, (R)0, rho0, omega, omb, omg, sc);
       }
@@ -1421,7 +1423,7 @@ __device__ __forceinline__ void face_rows(const BoxDesc& b, const Item& it,
 // f*_i into its own slot OPP[i]; an odd step reads those (LAYOUT_SWAP) and
 // writes f*_i into slot i of node x + c_i, where the next even step reads it
 // in place.  Each slot is read and written by one node only.
-template <int S, int COLL, bool PER, int BS, bool EXT>
+template <int S, int COLL, bool PER, int BS, int EXT>
 __device__ __forceinline__ void tile_generic(const LbArgs& A, const BoxDesc& b, const Item& it,
                                              const typename Store<S>::T* src,
                                              typename Store<S>::T* dst, int layout, bool aa,
@@ -1434,7 +1436,7 @@ __device__ __forceinline__ void tile_generic(const LbArgs& A, const BoxDesc& b, 
   const int plane = it.ex * it.ey;
   const R sc = (R)b.s2;
   Ext<R> ext{};
-  if constexpr (EXT) ext = make_ext<R>(A, b, step);
+  if constexpr (EXT != 0) ext = make_ext<R>(A, b, step);
 #pragma unroll 1
   for (int p = threadIdx.x; p < plane; p += BS) {
     const int x = it.x0 + p % it.ex;
@@ -1445,9 +1447,9 @@ __device__ __forceinline__ void tile_generic(const LbArgs& A, const BoxDesc& b, 
       load_pre<S, PER>(src, b, x, y, z, layout, d);
       R gx = 0, gy = 0, gz = 0;
       if (cmask) gather_force<R, PER, 1>(A, b, cmask, x, y, z, gx, gy, gz);
-      if constexpr (EXT) {
+      if constexpr (EXT != 0) {
         ext.node = (unsigned)(((int64_t)z * b.ny + y) * b.nx + x);
-        collide_ext<R, COLL, comp_weights<S>(), S == 2>(d, gx, gy, gz, rho0, omega, omb, omg, ext, sc);
+        collide_ext<R, COLL, EXT, comp_weights<S>(), S == 2>(d, gx, gy, gz, rho0, omega, omb, omg, ext, sc);
       } else {
         collide_any<R, COLL, comp_weights<S>(), S == 2>(d, gx, gy, gz, rho0, omega, omb, omg, sc);
       }
@@ -1495,7 +1497,7 @@ __device__ __forceinline__ unsigned long long chains_met(const LbArgs& A, const 
 // thread: the interior ones with the spread force gathered (it is stored by
 // k_chain per node), the x-face ones as boundary nodes.  A few items of a
 // step; the row path would carry the force's registers in all of them.
-template <int S, int COLL, int BS, bool EXT>
+template <int S, int COLL, int BS, int EXT>
 __device__ __forceinline__ void row_nodes_aa(const LbArgs& A, const BoxDesc& b, const Item& it,
                                              typename Store<S>::T* buf, long long step,
                                              unsigned long long cmask, typename Store<S>::R rho0,
@@ -1508,7 +1510,7 @@ __device__ __forceinline__ void row_nodes_aa(const LbArgs& A, const BoxDesc& b, 
   const bool odd = step & 1;
   const R sc = (R)b.s2;
   Ext<R> ext{};
-  if constexpr (EXT) ext = make_ext<R>(A, b, step);
+  if constexpr (EXT != 0) ext = make_ext<R>(A, b, step);
 #pragma unroll 1
   for (int p = threadIdx.x; p < it.ex * V; p += BS) {
     const int q = it.x0 + p / V, row = q / L;
@@ -1526,9 +1528,9 @@ __device__ __forceinline__ void row_nodes_aa(const LbArgs& A, const BoxDesc& b, 
       load_pre<S, false>(buf, b, x, y, z, aa_layout(step), d);
       R gx = 0, gy = 0, gz = 0;
       gather_force<R, false, 1>(A, b, cmask, x, y, z, gx, gy, gz);
-      if constexpr (EXT) {
+      if constexpr (EXT != 0) {
         ext.node = node;
-        collide_ext<R, COLL, comp_weights<S>(), S == 2>(d, gx, gy, gz, rho0, omega, omb, omg, ext, sc);
+        collide_ext<R, COLL, EXT, comp_weights<S>(), S == 2>(d, gx, gy, gz, rho0, omega, omb, omg, ext, sc);
       } else {
         collide_any<R, COLL, comp_weights<S>(), S == 2>(d, gx, gy, gz, rho0, omega, omb, omg, sc);
       }
@@ -1561,15 +1563,23 @@ constexpr int lb_min_waves(int S, int COLL) {
 #endif
 }
 
-// The extended collision (body force, thermal noise) holds more registers:
-// its instantiations ask for two resident waves per SIMD.
-constexpr int lb_min_waves_ext(int S, int COLL, bool EXT) { return EXT ? 2 : lb_min_waves(S, COLL); }
+// EXT 1 adds the accelerated frame's body force, EXT 2 that and thermal noise.
+// FP16 MRT is bound by its arithmetic and asks for a third wave at the price of
+// a few spilled registers (36-56 bytes per lane): sixteen 96^3 boxes take 271 us
+// a step with a body force and 332 us with noise, at two waves 296 and 354.
+// FP32 takes the same at either (446 and 459 us), FP64 with a body force 1337 us
+// at two waves and 1373 at three.  Noise is a kernel of its own because a branch
+// per node on it in one kernel holds both arms' registers: at three waves
+// 100-980 bytes spilled, up to 1.8 times the time.
+constexpr int lb_min_waves_ext(int S, int COLL, int EXT) {
+  return EXT == 0 ? lb_min_waves(S, COLL) : (S == 2 && COLL != 0 ? 3 : 2);
+}
 
 // AA: the instantiation for in-place streaming (no stores of the two-buffer
 // step; the chains' force gathered here, whose registers the
 // two-buffer instantiations do not pay: with both in one periodic kernel a
 // 96^3 FP32 step took 135 us against 107).
-template <int S, int COLL, bool PER, int BS = WG, bool EXT = false, bool AA = false>
+template <int S, int COLL, bool PER, int BS = WG, int EXT = 0, bool AA = false>
 __global__ __launch_bounds__(BS, lb_min_waves_ext(S, COLL, EXT)) void k_lb(LbArgs A) {
   using St = Store<S>;
   using T = typename St::T;
@@ -1728,7 +1738,7 @@ __global__ __launch_bounds__(BS, lb_min_waves_ext(S, COLL, EXT)) void k_lb(LbArg
 // node and store the same values.  One workgroup per chain.  On steps that
 // have no check pass it also ends the step (step index advance), which then
 // needs no launch of its own.
-template <int S, int COLL, bool PER, bool EXT = false>
+template <int S, int COLL, bool PER, int EXT = 0>
 __global__ __launch_bounds__(WG) void k_force(LbArgs A) {
   using St = Store<S>;
   using T = typename St::T;
@@ -1768,11 +1778,11 @@ __global__ __launch_bounds__(WG) void k_force(LbArgs A) {
       load_pre<S, PER>(src, b, x, y, z, A.pre != 0, d);
       R gx = 0, gy = 0, gz = 0;
       gather_force<R, PER, 4>(A, b, all, x, y, z, gx, gy, gz);
-      if constexpr (EXT) {
+      if constexpr (EXT != 0) {
         // the same body force and noise k_lb gave the node (same counter)
         Ext<R> ext = make_ext<R>(A, b, step);
         ext.node = (unsigned)(((int64_t)z * b.ny + y) * b.nx + x);
-        collide_ext<R, COLL, comp_weights<S>(), S == 2>(d, gx, gy, gz, rho0, omega, omb, omg, ext, sc);
+        collide_ext<R, COLL, EXT, comp_weights<S>(), S == 2>(d, gx, gy, gz, rho0, omega, omb, omg, ext, sc);
       } else {
         collide_any<R, COLL, comp_weights<S>(), S == 2>(d, gx, gy, gz, rho0, omega, omb, omg, sc);
       }

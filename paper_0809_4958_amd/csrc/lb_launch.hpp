@@ -20,14 +20,15 @@ using ChainLaunch = void (*)(int, hipStream_t, const lbdev::BoxDesc*, const lbde
                              float*, unsigned, unsigned);
 
 // fused step launcher: storage S (0 FP64, 1 FP32, 2 FP16 deviations), collision
-// C (0 BGK, 1 MRT, 2 MRT with ghost rate 1), periodic or not; ext: the
-// extended collision (accelerated-frame body force, thermal fluctuations)
+// C (0 BGK, 1 MRT, 2 MRT with ghost rate 1), periodic or not; ext: 0 the
+// plain collision, 1 with the accelerated frame's body force, 2 with that and
+// thermal noise (MRT only)
 template <int S, int C>
-LbLaunch pick_lb(bool periodic, bool ext, bool in_place);
+LbLaunch pick_lb(bool periodic, int ext, bool in_place);
 
 // chain forcing pass after the fused step (grid: one workgroup per chain)
 template <int S, int C>
-LbLaunch pick_force(bool periodic, bool ext);
+LbLaunch pick_force(bool periodic, int ext);
 
 // chain kernel launcher for storage S, for chains of at most 64 beads or of
 // up to 256; the same launch computes the

@@ -13,33 +13,42 @@ namespace lbhost {
 
 using namespace lbdev;
 
-template <int S, int C, bool P, bool E, bool AA>
+template <int S, int C, bool P, int E, bool AA>
 void launch_lb(dim3 g, hipStream_t s, const LbArgs& a) {
   hipLaunchKernelGGL((k_lb<S, C, P, WG, E, AA>), g, dim3(WG), 0, s, a);
 }
 
-template <int S, int C>
-LbLaunch pick_lb(bool periodic, bool ext, bool in_place) {
-  if (periodic && in_place) return ext ? launch_lb<S, C, true, true, true> : launch_lb<S, C, true, false, true>;
-  if (periodic) return ext ? launch_lb<S, C, true, true, false> : launch_lb<S, C, true, false, false>;
-  if (in_place) return ext ? launch_lb<S, C, false, true, true> : launch_lb<S, C, false, false, true>;
-  return ext ? launch_lb<S, C, false, true, false> : launch_lb<S, C, false, false, false>;
+template <int S, int C, int E>
+LbLaunch pick_lb_ext(bool periodic, bool in_place) {
+  if (periodic) return in_place ? launch_lb<S, C, true, E, true> : launch_lb<S, C, true, E, false>;
+  return in_place ? launch_lb<S, C, false, E, true> : launch_lb<S, C, false, E, false>;
 }
 
-template LbLaunch pick_lb<LB_S, LB_C>(bool, bool, bool);
+template <int S, int C>
+LbLaunch pick_lb(bool periodic, int ext, bool in_place) {
+  if constexpr (C != 0) {
+    if (ext == 2) return pick_lb_ext<S, C, 2>(periodic, in_place);
+  }
+  return ext ? pick_lb_ext<S, C, 1>(periodic, in_place) : pick_lb_ext<S, C, 0>(periodic, in_place);
+}
 
-template <int S, int C, bool P, bool E>
+template LbLaunch pick_lb<LB_S, LB_C>(bool, int, bool);
+
+template <int S, int C, bool P, int E>
 void launch_force(dim3 g, hipStream_t s, const LbArgs& a) {
   hipLaunchKernelGGL((k_force<S, C, P, E>), g, dim3(WG), 0, s, a);
 }
 
 template <int S, int C>
-LbLaunch pick_force(bool periodic, bool ext) {
-  if (ext) return periodic ? launch_force<S, C, true, true> : launch_force<S, C, false, true>;
-  return periodic ? launch_force<S, C, true, false> : launch_force<S, C, false, false>;
+LbLaunch pick_force(bool periodic, int ext) {
+  if constexpr (C != 0) {
+    if (ext == 2) return periodic ? launch_force<S, C, true, 2> : launch_force<S, C, false, 2>;
+  }
+  if (ext) return periodic ? launch_force<S, C, true, 1> : launch_force<S, C, false, 1>;
+  return periodic ? launch_force<S, C, true, 0> : launch_force<S, C, false, 0>;
 }
 
-template LbLaunch pick_force<LB_S, LB_C>(bool, bool);
+template LbLaunch pick_force<LB_S, LB_C>(bool, int);
 
 #if LB_C == 0
 template <int S, bool P, int MB, bool TH>

@@ -109,14 +109,14 @@ CheckLaunch pick_check(bool per) {
 
 // coll: 0 BGK, 1 MRT, 2 MRT with ghost relaxation rate 1 (ghost moments not formed)
 template <int S>
-LbLaunch pick_lb(int coll, bool per, bool ext, bool aa) {
+LbLaunch pick_lb(int coll, bool per, int ext, bool aa) {
   if (coll == 0) return lbhost::pick_lb<S, 0>(per, ext, aa);
   if (coll == 1) return lbhost::pick_lb<S, 1>(per, ext, aa);
   return lbhost::pick_lb<S, 2>(per, ext, aa);
 }
 
 template <int S>
-LbLaunch pick_force(int coll, bool per, bool ext) {
+LbLaunch pick_force(int coll, bool per, int ext) {
   if (coll == 0) return lbhost::pick_force<S, 0>(per, ext);
   if (coll == 1) return lbhost::pick_force<S, 1>(per, ext);
   return lbhost::pick_force<S, 2>(per, ext);
@@ -806,11 +806,12 @@ lb_status upload_chains(lb_ctx* ctx) {
   return upload_boxes(ctx);
 }
 
-// Step and force-pass kernels: the extended collision when a box has a body
-// force or the context is thermal, the plain one otherwise.
+// Step and force-pass kernels: with thermal noise (and body force) when the
+// context is thermal, with the body force when a box has one, else plain.
 void select_launchers(lb_ctx* ctx) {
-  bool ext = ctx->kT > 0.0;
-  for (auto& b : ctx->bx) ext = ext || b.body_ns > 0;
+  int ext = ctx->kT > 0.0 ? 2 : 0;
+  for (auto& b : ctx->bx)
+    if (!ext && b.body_ns > 0) ext = 1;
   const int kc = ctx->coll == LB_BGK ? 0 : (ctx->cfg.ghost_rate == 1.0 ? 2 : 1);
   const bool aa = ctx->aa;
   switch (ctx->S) {
