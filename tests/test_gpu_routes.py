@@ -5,8 +5,9 @@ import numpy as np
 import pytest
 
 import oracle
-from lbcase import CHAIN_BOND, Case
+from lbcase import CHAIN_BOND, Case, ks_case
 from paper_0809_4958_amd import inputs
+from test_gpu_extensions import accel_history
 from test_gpu_parity import STORE, check, compare, make_ctx, say
 
 pytestmark = pytest.mark.gpu
@@ -234,4 +235,27 @@ def test_reads_follow_every_step_and_write():
             assert np.array_equal(u_dev.cpu().numpy(), ctx.read(0, lbm.F_U))
             assert np.array_equal(p_dev.cpu().numpy(), ctx.read(0, lbm.F_BEAD_POS, n_beads=5))
         check(compare(ctx, ob, case, "f64"), "f64", f"step {n}")
+    ctx.close()
+
+
+@pytest.mark.parametrize("streaming", ["two_buffers", "in_place"])
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16"])
+@pytest.mark.parametrize("kT,body", [(2e-6, True), (2e-6, False), (0.0, True), (0.0, False)])
+def test_noise_and_body_force_of_a_box_that_was_thermal(kT, body, storage, streaming):
+    """The step kernel follows the last temperature set and the boxes' body
+    force: each of the four combinations, in a context that was made thermal
+    at another temperature first."""
+    steps = 24
+    case = ks_case(21, steps, dt=10, res=9, tau=0.6, n_beads=8, f32_samples=storage != "f64")
+    case.kT, case.seed = kT, 77
+    if body:
+        case.body = accel_history(steps, np.random.default_rng(3))
+    say("case noise", kT, "body", body, storage, streaming)
+    ob = case.oracle_box()
+    assert ob.step(steps) == 0
+    ctx = make_ctx(case, storage, streaming=lbm.STREAM_AA if streaming == "in_place" else lbm.STREAM_AB)
+    ctx.set_thermal(1e-4, 5)
+    ctx.set_thermal(kT, 77)
+    ctx.step(steps)
+    check(compare(ctx, ob, case, storage), storage, f"noise {kT} body {body} {streaming}")
     ctx.close()
