@@ -1549,30 +1549,28 @@ __device__ __forceinline__ void row_nodes_aa(const LbArgs& A, const BoxDesc& b, 
 
 // ----------------------------------------------------------- fused step
 
-// Resident waves per SIMD the step kernel is compiled for: the most that fit
-// without spilling (VGPRs per lane: 512 / waves).  FP64 BGK 2 (197-228 VGPRs),
-// MRT 3 (147-150), MRT with ghost rate 1 4 (124-127); FP32 3-4 (94-122); FP16
-// MRT 3 (101-144), FP16 BGK 2 (127-178).  Left to itself the allocator lands
-// just above a boundary and runs one wave fewer, measured 5-11% slower.
-constexpr int lb_min_waves(int S, int COLL) {
-  return S == 0 ? (COLL == 0 ? 2 : (COLL == 1 ? 3 : 4))
+// Resident waves per SIMD the step kernel is compiled for: FP64 two, FP32 and
+// FP16 three.  us per step of sixteen walled 96^3 boxes with one chain each, at
+// 2 / 3 / 4 waves:
+//             two buffers                        in place
+//          MRT, ghost 1   MRT, 1.4     BGK       MRT, ghost 1    MRT, 1.4     BGK
+//   FP64  1366 1366 1403  1368 1370 1431  1350 1397 1528  1162 1162 1220  1163 1164 1222  1148 1209 1427
+//   FP32   441  441  447   447  447  448   444  443  450   463  463  463   464  464  464   463  462  466
+//   FP16   282  263  380   290  267  375   273  273  512   312  299  333   325  307  388   339  317  562
+// FP64 and FP32 are bound by memory and two waves with their loads in flight
+// are enough; FP16 is bound by its arithmetic and gains from the third, also
+// where that spills: body force (EXT 1) 296 us at two and 271 at three, thermal
+// noise (EXT 2) 354 and 332, at 36-56 bytes per lane.  FP64 with a body force
+// takes 1337 us at two and 1373 at three.
+// Noise is a kernel of its own because a branch per node on it in one kernel
+// holds both arms' registers: at three waves 100-980 bytes spilled, up to 1.8
+// times the time.
+constexpr int lb_min_waves(int S) {
 #ifdef LB_MIN_WAVES
-                : LB_MIN_WAVES;
+  return S == 0 ? 2 : LB_MIN_WAVES;
 #else
-                : (S == 1 ? (COLL == 0 ? 3 : 4) : (COLL == 0 ? 2 : 3));
+  return S == 0 ? 2 : 3;
 #endif
-}
-
-// EXT 1 adds the accelerated frame's body force, EXT 2 that and thermal noise.
-// FP16 MRT is bound by its arithmetic and asks for a third wave at the price of
-// a few spilled registers (36-56 bytes per lane): sixteen 96^3 boxes take 271 us
-// a step with a body force and 332 us with noise, at two waves 296 and 354.
-// FP32 takes the same at either (446 and 459 us), FP64 with a body force 1337 us
-// at two waves and 1373 at three.  Noise is a kernel of its own because a branch
-// per node on it in one kernel holds both arms' registers: at three waves
-// 100-980 bytes spilled, up to 1.8 times the time.
-constexpr int lb_min_waves_ext(int S, int COLL, int EXT) {
-  return EXT == 0 ? lb_min_waves(S, COLL) : (S == 2 && COLL != 0 ? 3 : 2);
 }
 
 // AA: the instantiation for in-place streaming (no stores of the two-buffer
@@ -1580,7 +1578,7 @@ constexpr int lb_min_waves_ext(int S, int COLL, int EXT) {
 // two-buffer instantiations do not pay: with both in one periodic kernel a
 // 96^3 FP32 step took 135 us against 107).
 template <int S, int COLL, bool PER, int BS = WG, int EXT = 0, bool AA = false>
-__global__ __launch_bounds__(BS, lb_min_waves_ext(S, COLL, EXT)) void k_lb(LbArgs A) {
+__global__ __launch_bounds__(BS, lb_min_waves(S)) void k_lb(LbArgs A) {
   using St = Store<S>;
   using T = typename St::T;
   using R = typename St::R;
