@@ -16,7 +16,12 @@ namespace lbdev {
 // One workgroup after the fused step: per-box fixed-order sums of the item
 // partials (on check steps), finiteness check, device step advance.  Runs as
 // its own launch so that the fused kernel needs no device-wide fences.
-__global__ __launch_bounds__(WG) void k_finalize(LbArgs A) {
+// Latency: each box is a chain of loads (offsets, partials), a wavefront sum
+// and a store, about 1.6 us, so check steps launch FIN_CHECK threads and a
+// wavefront takes FIN_BOXES boxes side by side (256 boxes one at a time
+// on four wavefronts: 106 us).
+constexpr int FIN_CHECK = 1024, FIN_BOXES = 4;
+__global__ __launch_bounds__(FIN_CHECK) void k_finalize(LbArgs A) {
   const int tid = threadIdx.x;
   put_stamp(A.stamp_after);
   if (A.st->err_key != ERR_NONE) return;
@@ -26,24 +31,48 @@ __global__ __launch_bounds__(WG) void k_finalize(LbArgs A) {
   if (tid == 0) s_bad = 0x7fffffff;
   __syncthreads();
   if (check) {
-    // a wavefront per box: lane l adds partials l, l + 64, ..., then the lanes
-    for (int bx = tid >> 6; bx < A.n_boxes; bx += WG / 64) {
-      double s[4] = {0.0, 0.0, 0.0, 0.0};
-      for (int q = A.check_off[bx] + (tid & 63); q < A.check_off[bx + 1]; q += 64) {
+    // a box's order: lane l adds partials l, l + 64, ..., then the lanes
+    const int lane = tid & 63;
+    for (int b0 = (tid >> 6) * FIN_BOXES; b0 < A.n_boxes; b0 += (blockDim.x >> 6) * FIN_BOXES) {
+      int off[FIN_BOXES + 1], n = 0;
+      double nodes[FIN_BOXES], s[FIN_BOXES][4];
 #pragma unroll
-        for (int m = 0; m < 4; m++) s[m] += A.partials[4 * q + m];
+      for (int u = 0; u <= FIN_BOXES; u++) off[u] = A.check_off[min(b0 + u, A.n_boxes)];
+#pragma unroll
+      for (int u = 0; u < FIN_BOXES; u++) {
+        n = max(n, off[u + 1] - off[u]);
+        nodes[u] = (double)A.boxes[min(b0 + u, A.n_boxes - 1)].interior;
+#pragma unroll
+        for (int m = 0; m < 4; m++) s[u][m] = 0.0;
+      }
+      for (int q = lane; q < n; q += 64) {
+#pragma unroll
+        for (int u = 0; u < FIN_BOXES; u++) {
+          if (off[u] + q < off[u + 1]) {
+#pragma unroll
+            for (int m = 0; m < 4; m++) s[u][m] += A.partials[4 * (off[u] + q) + m];
+          }
+        }
       }
 #pragma unroll
-      for (int m = 0; m < 4; m++) s[m] = wave_sum(s[m]);
-      if (tid & 63) continue;
-      const double M = A.rho0 * A.boxes[bx].interior + s[0];
-      double* mm = A.mass_mom + 5 * bx;
-      mm[0] = (double)(step + 1);
-      mm[1] = M;
-      mm[2] = s[1];
-      mm[3] = s[2];
-      mm[4] = s[3];
-      if (!(isfinite(M) && isfinite(s[1]) && isfinite(s[2]) && isfinite(s[3]))) atomicMin(&s_bad, bx);
+      for (int u = 0; u < FIN_BOXES; u++) {
+#pragma unroll
+        for (int m = 0; m < 4; m++) s[u][m] = wave_sum(s[u][m]);
+      }
+      if (lane) continue;
+#pragma unroll
+      for (int u = 0; u < FIN_BOXES; u++) {
+        const int bx = b0 + u;
+        if (bx >= A.n_boxes) break;
+        const double M = A.rho0 * nodes[u] + s[u][0];
+        double* mm = A.mass_mom + 5 * bx;
+        mm[0] = (double)(step + 1);
+        mm[1] = M;
+        mm[2] = s[u][1];
+        mm[3] = s[u][2];
+        mm[4] = s[u][3];
+        if (!(isfinite(M) && isfinite(s[u][1]) && isfinite(s[u][2]) && isfinite(s[u][3]))) atomicMin(&s_bad, bx);
+      }
     }
   }
   __syncthreads();

@@ -2,8 +2,8 @@
 //
 // A context owns two structure-of-arrays population arenas (all boxes back to
 // back), the boundary histories, the chain state (double-buffered by step
-// parity) and a work list of items (interior tiles and boundary chunks) for the
-// fused kernel.  Per step it launches k_chain (when chains exist) and k_lb on
+// parity) and a work list of items (interior rows, tiles, boundary chunks) for the
+// fused kernel.  Per step it launches k_chain, k_lb and (with chains) k_force on
 // the context stream; every per-step quantity (time index, buffer parity,
 // check steps) is read on the device from DevState, so a chunk of steps can
 // be captured once into a HIP graph and replayed.
@@ -944,7 +944,7 @@ void enqueue_step(lb_ctx* ctx, hipStream_t s, int pre, const hipEvent_t* ev3,
     ctx->check_fn(ctx->n_check, s, t);
     t.stamp_after = nullptr;
   }
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(WG), 0, s, t);
+  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(ctx->cfg.reduce_every > 0 && chk != 0 ? FIN_CHECK : WG), 0, s, t);
 }
 
 void enqueue_step(lb_ctx* ctx, hipStream_t s, int pre, bool timed, int chk) {
