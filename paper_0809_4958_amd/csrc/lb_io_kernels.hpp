@@ -19,7 +19,7 @@ namespace lbdev {
 // Latency: each box is a chain of loads (offsets, partials), a wavefront sum
 // and a store, about 1.6 us, so check steps launch FIN_CHECK threads and a
 // wavefront takes FIN_BOXES boxes side by side (256 boxes one at a time
-// on four wavefronts: 106 us).
+// on four wavefronts: 106 us, so: 42).
 constexpr int FIN_CHECK = 1024, FIN_BOXES = 4;
 __global__ __launch_bounds__(FIN_CHECK) void k_finalize(LbArgs A) {
   const int tid = threadIdx.x;
