@@ -245,6 +245,7 @@ struct lb_ctx {
   DevState* d_st = nullptr;
   DevState* h_st = nullptr;        // pinned copy, current when st_known: no step since it was read
   bool st_known = false;
+  bool replayable = false;         // the caller has captured steps: its graph replays them unseen
   ChainDesc* d_chains = nullptr;
   void* d_pos = nullptr;
   void* d_vel = nullptr;
@@ -1063,10 +1064,12 @@ lb_status decode_error(lb_ctx* ctx, int key, int64_t step) {
 // lb_write_state change it, so it is fetched once after them, through pinned
 // memory with one wait: a readout of every field of 256 boxes used to wait
 // twice and copy for each (53 us per field and box of the 256-box batch, now 18 us).
+// A context whose steps went into a graph of the caller's fetches it for every
+// call: each replay of that graph steps without a call of the library.
 lb_status sync_state(lb_ctx* ctx, DevState* out) {
   if (!ctx->st_known) {
     HIPCHK(copy_sync(ctx, ctx->h_st, ctx->d_st, sizeof(DevState), hipMemcpyDeviceToHost));
-    ctx->st_known = true;
+    ctx->st_known = !ctx->replayable;
   }
   *out = *ctx->h_st;
   if (out->err_key != ERR_NONE && ctx->latched == LB_OK) decode_error(ctx, out->err_key, out->step);
@@ -1596,6 +1599,10 @@ lb_status lb_step(lb_ctx* ctx, int32_t n_steps) {
   lb_status s = prepare(ctx);
   if (s) return s;
   ctx->st_known = false;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  const bool asked = hipStreamIsCapturing(ctx->stream, &capture) == hipSuccess;
+  if (!asked) (void)hipGetLastError();  // the null stream beside another one's capture: not known
+  if (!asked || capture != hipStreamCaptureStatusNone) ctx->replayable = true;
   int left = n_steps;
   const bool timed = ctx->timing;
   if (timed) {

@@ -259,3 +259,41 @@ def test_noise_and_body_force_of_a_box_that_was_thermal(kT, body, storage, strea
     ctx.step(steps)
     check(compare(ctx, ob, case, storage), storage, f"noise {kT} body {body} {streaming}")
     ctx.close()
+
+
+@pytest.mark.parametrize("streaming", ["two_buffers", "in_place"])
+def test_reads_follow_the_replays_of_a_captured_step(streaming):
+    """A step captured on the context's stream and replayed by the caller: every
+    readout is the state behind the last replay, on the host and on the device."""
+    import ctypes
+
+    import torch
+
+    rng = np.random.default_rng(61)
+    dims = (12, 11, 13)
+    case = Case(dims, collision=oracle.MRT, tau=0.8,
+                bc=(oracle.BC_AFFINE, inputs.ou_strain(20, rng, corr_steps=20.0, rms=1e-3), 0, 1, 0),
+                u0=1e-3 * rng.standard_normal(dims[::-1] + (3,)), chains=[walk(5, [5.4, 5.1, 6.2], rng, CHAIN_BOND)])
+    say("case captured step", streaming)
+    stream = torch.cuda.Stream()
+    ob = case.oracle_box()
+    ctx = make_ctx(case, "f64", stream=stream.cuda_stream,
+                   streaming=lbm.STREAM_AA if streaming == "in_place" else lbm.STREAM_AB)
+    ctx.step(1)
+    assert ob.step(1) == 0 and ctx.read(0, lbm.F_STEP) == 1
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        ctx.step(1)
+    u = torch.zeros(dims[::-1] + (3,), dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    for n in range(2, 8):
+        with torch.cuda.stream(stream):
+            graph.replay()
+        assert ob.step(1) == 0
+        for _ in range(2):
+            assert ctx.read(0, lbm.F_STEP) == n
+            st = lbm.load().lb_read_fields(ctx._h, 0, lbm.F_U, ctypes.c_void_p(u.data_ptr()), u.numel() * 8, 1)
+            assert st == lbm.OK and np.array_equal(u.cpu().numpy(), ctx.read(0, lbm.F_U))
+        assert ctx.sync_status() == lbm.OK
+        check(compare(ctx, ob, case, "f64"), "f64", f"replay {n - 1}")
+    ctx.close()
