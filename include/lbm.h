@@ -118,9 +118,14 @@ typedef struct {
   int32_t streaming;       /* lb_streaming: LB_STREAM_AB (0) or LB_STREAM_AA (1) */
 } lb_config;
 
-/* Creates a context: validates the configuration, allocates two population
- * buffers per box (structure of arrays pop[19][nz][ny][nx]) and initialises
- * every interior node to rest, f = w rho0 (Sec. 2 initial condition with u = 0). */
+/* Creates a context: validates the configuration, allocates the population
+ * buffers of every box (structure of arrays, two buffers, or one with
+ * LB_STREAM_AA) and initialises every interior node to rest, f = w rho0 (Sec. 2
+ * initial condition with u = 0).  Walled FP32 and FP16 boxes may take padded
+ * rows: at most half as many nodes again along x (up to 16 in shorter rows) and
+ * a quarter along y, while that adds less than 1/32 of the device's memory to
+ * the context; where the padded buffers cannot be had, 19 populations per node
+ * and buffer are enough. */
 lb_status lb_init(const lb_config* cfg, lb_ctx** out);
 
 /* Prescribes the initial velocity on all interior sites of a box: f(x, 0) =

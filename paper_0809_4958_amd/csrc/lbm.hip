@@ -230,6 +230,7 @@ struct lb_ctx {
   uint64_t seed = 0;              // their Philox key
   void* arena[2] = {nullptr, nullptr};
   int64_t arena_elems = 0;
+  int64_t xf_floats = 0;           // x-face velocities of the row boxes
   // device tables
   BoxDesc* d_boxes = nullptr;
   Item* d_items = nullptr;
@@ -1036,6 +1037,116 @@ void face_tables(BoxHost& b) {
   }
 }
 
+// What the rows of walled FP32 and FP16 boxes may take in memory.
+enum Rows : int {
+  ROWS_PADDED,  // lane-vector rows, padded where that is the faster pitch
+  ROWS_EXACT,   // lane-vector rows of nx nodes, tile items where no vector divides nx
+  ROWS_LEAST    // the same, and in place tile items alone: no node and no x-face velocity more
+};
+
+// One box in memory: nodes per row, interleaved lines, row or tile items.
+void row_layout(const lb_ctx* ctx, BoxHost& b, Rows rows) {
+  const int nx = b.dim.nx, ny = b.dim.ny, nz = b.dim.nz;
+  b.px = nx;
+  b.nyb = ny;
+  b.ylog = 0;
+  b.xf_off = -1;
+  b.vec = false;
+  const int px = rows == ROWS_PADDED ? row_pitch(ctx->S, nx) : (ctx->S == LB_STORE_F64 ? 0 : nx);
+  b.vw = px ? pick_row_words(ctx->S, px) : 0;
+  const int V = b.vw ? row_nodes(ctx->S, b.vw) : 1;
+  // interleave Y = 2^ylog lines per population row so that a row of a block
+  // spans whole 128-byte lines; padded rows also pad ny to whole blocks of up
+  // to eight, unless that is more than a quarter of it
+  const int rowb = px * (int)store_bytes(ctx->S);
+  int ylog = 0;
+  for (int yl = 0; yl <= (px > nx ? 3 : 2); yl++)
+    if ((rowb << yl) % 128 == 0 && (px > nx || ny % (1 << yl) == 0)) {
+      ylog = yl;
+      break;
+    }
+  int nyb = (ny + (1 << ylog) - 1) >> ylog;
+  if (4 * ((nyb << ylog) - ny) > ny) {
+    ylog = 0;
+    nyb = ny;
+  }
+  const double groups = (double)(px / V) * (ny - 2) * (nz - 2);
+  // 32-bit buffer offsets: the planes one workgroup iteration touches
+  const double plane = (double)Q * rowb * (nyb << ylog);
+  const double span = (WG / ((double)(px / V) * (ny - 2)) + 4.0) * plane;
+  b.vec = b.vw != 0 && !(rows == ROWS_LEAST && ctx->aa) && !ctx->per && groups < 2.0e9 &&
+          span < 2147483648.0 && !getenv("LBM_NO_VEC");
+  if (b.vec) {
+    b.px = px;
+    b.ylog = ylog;
+    b.nyb = nyb;
+  }
+}
+
+// Every box in the arenas, the x-face velocity blocks of the row boxes (2
+// sides x interior y, z x 3 floats), and into `items` (may be NULL) the x-face
+// work list: chunks of at most XF_ITEM nodes of a box, one per wavefront (each
+// lane evaluates XF_NODES nodes with their loads overlapped).  false: the
+// x-face blocks do not fit 32-bit offsets.
+bool lay_out(lb_ctx* ctx, Rows rows, std::vector<int4>* items) {
+  ctx->arena_elems = ctx->xf_floats = 0;
+  if (items) items->clear();
+  for (size_t bi = 0; bi < ctx->bx.size(); bi++) {
+    BoxHost& b = ctx->bx[bi];
+    row_layout(ctx, b, rows);
+    // every box starts on a 128-element boundary (aligned vector access)
+    b.off = (ctx->arena_elems + 127) / 128 * 128;
+    ctx->arena_elems = b.off + (int64_t)Q * b.px * ((int64_t)b.nyb << b.ylog) * b.dim.nz;
+    face_tables(b);
+    default_tile(b);
+    if (!b.vec) continue;
+    const int64_t nodes = 2LL * (b.dim.ny - 2) * (b.dim.nz - 2);
+    if (ctx->xf_floats + 3 * nodes >= (1LL << 31)) return false;
+    b.xf_off = (int)ctx->xf_floats;
+    ctx->xf_floats += 3 * nodes;
+    for (int64_t k = 0; items && k < nodes; k += XF_ITEM)
+      items->push_back(make_int4((int)bi, (int)k, (int)std::min<int64_t>(XF_ITEM, nodes - k), 0));
+  }
+  return true;
+}
+
+// bytes of the layout made last: population arenas and x-face velocities
+int64_t layout_bytes(const lb_ctx* ctx) {
+  return ctx->arena_elems * (int64_t)store_bytes(ctx->S) * (ctx->aa ? 1 : 2) + 4 * ctx->xf_floats;
+}
+
+// The arenas and the x-face velocities, in the fastest layout that memory allows:
+// padding takes up to half as many nodes again in x (rows shorter than 16:
+// up to 16) and a quarter in y, so it is used while what it adds to the context
+// is below 1/32 of the device's memory, and given up where its buffers cannot be
+// had: a context fits wherever its boxes' own nodes do.
+bool allocate_arenas(lb_ctx* ctx, std::vector<int4>& xf_items) {
+  lay_out(ctx, ROWS_LEAST, nullptr);
+  const int64_t least = layout_bytes(ctx);
+  size_t free_bytes = 0, total = 0;
+  for (Rows rows : {ROWS_PADDED, ROWS_EXACT, ROWS_LEAST}) {
+    lay_out(ctx, rows, &xf_items);
+    const int64_t more = layout_bytes(ctx) - least;
+    if (rows != ROWS_LEAST && more > 0) {
+      if (!total && hipMemGetInfo(&free_bytes, &total) != hipSuccess) (void)hipGetLastError();
+      if (32 * more > (int64_t)total) continue;
+    }
+    const size_t bytes = (size_t)ctx->arena_elems * store_bytes(ctx->S);
+    ctx->arena[0] = dalloc(ctx, bytes);
+    // in-place streaming: one buffer serves as both
+    ctx->arena[1] = ctx->aa || !ctx->arena[0] ? ctx->arena[0] : dalloc(ctx, bytes);
+    bool ok = ctx->arena[0] && ctx->arena[1];
+    if (ok && ctx->xf_floats) ctx->d_xface = dalloc_t<float>(ctx, (size_t)ctx->xf_floats, &ok);
+    if (ok) return true;
+    (void)hipGetLastError();  // the failed allocation's
+    if (ctx->arena[1] != ctx->arena[0]) dfree(ctx, ctx->arena[1]);
+    dfree(ctx, ctx->arena[0]);
+    ctx->arena[0] = ctx->arena[1] = nullptr;
+    if (!more) break;  // nothing to save: the next layouts are this one
+  }
+  return false;
+}
+
 lb_status check_box(lb_ctx* ctx, int32_t box) {
   if (!ctx) return LB_ERR_ARG;
   if (box < 0 || box >= (int)ctx->bx.size()) return fail(ctx, LB_ERR_ARG, "box index out of range");
@@ -1131,7 +1242,6 @@ lb_status lb_init(const lb_config* cfg, lb_ctx** out) {
   // context may then be a row box
   for (int i = 0; i < cfg->n_boxes; i++)
     if (cfg->boxes[i].periodic_mask & 7u) ctx->per = true;
-  int64_t off = 0;
   for (int i = 0; i < cfg->n_boxes; i++) {
     BoxHost b;
     b.dim = cfg->boxes[i];
@@ -1160,61 +1270,11 @@ lb_status lb_init(const lb_config* cfg, lb_ctx** out) {
     b.interior = (int64_t)b.ix * b.iy * b.iz;
     b.has_layer = pm != 7u;
     b.nn = nn;
-    // every box starts on a 128-element boundary (aligned vector access)
-    off = (off + 127) / 128 * 128;
-    b.off = off;
-    b.px = n3[0];
-    b.nyb = n3[1];
-    {
-      const int px = row_pitch(cfg->storage, n3[0]);
-      b.vw = px ? pick_row_words(cfg->storage, px) : 0;
-      const int V = b.vw ? row_nodes(cfg->storage, b.vw) : 1;
-      // interleave Y = 2^ylog lines per population row so that a row of a
-      // block spans whole 128-byte lines; padded rows also pad ny to whole
-      // blocks of up to eight
-      const int rowb = px * (int)store_bytes(cfg->storage);
-      int ylog = 0;
-      for (int yl = 0; yl <= (px > n3[0] ? 3 : 2); yl++)
-        if ((rowb << yl) % 128 == 0 && (px > n3[0] || n3[1] % (1 << yl) == 0)) {
-          ylog = yl;
-          break;
-        }
-      const int nyb = (n3[1] + (1 << ylog) - 1) >> ylog;
-      const double groups = (double)(px / V) * (n3[1] - 2) * (n3[2] - 2);
-      // 32-bit buffer offsets: the planes one workgroup iteration touches
-      const double plane = (double)Q * rowb * (nyb << ylog);
-      const double span = (WG / ((double)(px / V) * (n3[1] - 2)) + 4.0) * plane;
-      b.vec = b.vw != 0 && !ctx->per && groups < 2.0e9 && span < 2147483648.0 && !getenv("LBM_NO_VEC");
-      if (b.vec) {
-        b.px = px;
-        b.ylog = ylog;
-        b.nyb = nyb;
-      }
-    }
-    off += (int64_t)Q * b.px * ((int64_t)b.nyb << b.ylog) * n3[2];
-    face_tables(b);
-    default_tile(b);
     ctx->bx.push_back(b);
   }
-  ctx->arena_elems = off;
-  // x-face velocity blocks of the row boxes (2 sides x interior y, z x 3
-  // floats) and the x-face work list: chunks of at most XF_ITEM nodes of a box,
-  // one per wavefront (each lane evaluates XF_NODES nodes with their loads
-  // overlapped)
-  int64_t xf_floats = 0;
-  std::vector<int4> xf_items;
-  for (size_t bi = 0; bi < ctx->bx.size(); bi++) {
-    BoxHost& b = ctx->bx[bi];
-    if (!b.vec) continue;
-    const int64_t nodes = 2LL * (b.dim.ny - 2) * (b.dim.nz - 2);
-    if (xf_floats + 3 * nodes >= (1LL << 31)) {  // 32-bit offsets
-      lb_free(ctx);
-      return LB_ERR_ARG;
-    }
-    b.xf_off = (int)xf_floats;
-    xf_floats += 3 * nodes;
-    for (int64_t k = 0; k < nodes; k += XF_ITEM)
-      xf_items.push_back(make_int4((int)bi, (int)k, (int)std::min<int64_t>(XF_ITEM, nodes - k), 0));
+  if (!lay_out(ctx, ROWS_PADDED, nullptr)) {  // more x-face nodes than 32-bit offsets reach
+    lb_free(ctx);
+    return LB_ERR_ARG;
   }
   // the device this context lives on, and its copy of the static staging
   // array of the allocation-free readout
@@ -1233,16 +1293,14 @@ lb_status lb_init(const lb_config* cfg, lb_ctx** out) {
     lb_free(ctx);
     return LB_ERR_HIP;
   }
-  const size_t sb = store_bytes(ctx->S);
-  ctx->arena[0] = dalloc(ctx, (size_t)off * sb);
-  // in-place streaming: one buffer serves as both
-  ctx->arena[1] = ctx->aa ? ctx->arena[0] : dalloc(ctx, (size_t)off * sb);
-  bool ok = ctx->arena[0] && ctx->arena[1];
+  std::vector<int4> xf_items;
+  bool ok = allocate_arenas(ctx, xf_items);
+  const size_t arena_bytes = (size_t)ctx->arena_elems * store_bytes(ctx->S);
+  const size_t xf_bytes = (size_t)ctx->xf_floats * sizeof(float);
   ctx->d_boxes = dalloc_t<BoxDesc>(ctx, ctx->bx.size(), &ok);
   ctx->d_mass_mom = dalloc_t<double>(ctx, 5 * ctx->bx.size(), &ok);
   ctx->d_st = dalloc_t<DevState>(ctx, 1, &ok);
   if (!xf_items.empty()) {
-    ctx->d_xface = dalloc_t<float>(ctx, (size_t)xf_floats, &ok);
     ctx->d_xf_items = dalloc_t<int4>(ctx, xf_items.size(), &ok);
     ctx->n_xf_items = (int)xf_items.size();
   }
@@ -1251,14 +1309,14 @@ lb_status lb_init(const lb_config* cfg, lb_ctx** out) {
     return LB_ERR_OOM;
   }
   if (!xf_items.empty() &&
-      (dzero(ctx, ctx->d_xface, (size_t)xf_floats * sizeof(float)) != hipSuccess ||
+      (dzero(ctx, ctx->d_xface, xf_bytes) != hipSuccess ||
        h2d(ctx, ctx->d_xf_items, xf_items.data(), xf_items.size() * sizeof(int4)) != hipSuccess)) {
     lb_free(ctx);
     return LB_ERR_HIP;
   }
   // rest state: all deviations zero, in both buffers
-  if (dzero(ctx, ctx->arena[0], (size_t)off * sb) != hipSuccess ||
-      dzero(ctx, ctx->arena[1], (size_t)off * sb) != hipSuccess ||
+  if (dzero(ctx, ctx->arena[0], arena_bytes) != hipSuccess ||
+      dzero(ctx, ctx->arena[1], arena_bytes) != hipSuccess ||
       dzero(ctx, ctx->d_mass_mom, 5 * sizeof(double) * ctx->bx.size()) != hipSuccess) {
     lb_free(ctx);
     return LB_ERR_HIP;

@@ -174,7 +174,10 @@ class Context:
             alloc, delete = torch.cuda.caching_allocator_alloc, torch.cuda.caching_allocator_delete
 
             def _alloc(n, user):
-                return alloc(int(n), dev)
+                try:
+                    return alloc(int(n), dev)
+                except RuntimeError:  # out of memory: the library may go on with less
+                    return None
 
             def _free(ptr, user):
                 try:

@@ -297,3 +297,80 @@ def test_reads_follow_the_replays_of_a_captured_step(streaming):
         assert ctx.sync_status() == lbm.OK
         check(compare(ctx, ob, case, "f64"), "f64", f"replay {n - 1}")
     ctx.close()
+
+
+def arena_bytes(dims, storage):
+    """The populations of one buffer without padding."""
+    return 19 * int(np.prod(dims)) * {"f64": 8, "f32": 4, "f16": 2}[storage]
+
+
+@pytest.fixture
+def torch_allocs(monkeypatch):
+    """Sizes the contexts made with torch_alloc ask for; with `most` set, larger
+    ones are refused as PyTorch refuses what it has no memory for."""
+    import torch
+
+    class Log:
+        def __init__(self):
+            self.sizes, self.most = [], None
+
+    log, give = Log(), torch.cuda.caching_allocator_alloc
+
+    def alloc(n, *a):
+        log.sizes.append(n)
+        if log.most is not None and n > log.most:
+            raise torch.cuda.OutOfMemoryError("refused by the test")
+        return give(n, *a)
+
+    monkeypatch.setattr(torch.cuda, "caching_allocator_alloc", alloc)
+    return log
+
+
+@pytest.mark.parametrize("streaming", ["two_buffers", "in_place"])
+@pytest.mark.parametrize("storage,dims", [("f16", (73, 10, 12)), ("f16", (9, 9, 11)), ("f16", (100, 7, 9)),
+                                          ("f32", (65, 9, 10)), ("f32", (40, 6, 9))])
+def test_context_fits_where_its_own_nodes_do(storage, dims, streaming, torch_allocs):
+    """With memory for the boxes' own nodes alone (no padded row, in place no
+    x-face velocity) a context is made all the same, and steps right."""
+    rng = np.random.default_rng(67)
+    case = Case(dims, collision=oracle.MRT, tau=0.8,
+                bc=(oracle.BC_AFFINE, inputs.ou_strain(8, rng, corr_steps=20.0, rms=1e-3 * 8 / max(dims)), 0, 1, 0),
+                u0=1e-3 * rng.standard_normal(dims[::-1] + (3,)), reduce_every=2,
+                chains=[walk(5, [4.1, 3.6, 4.4], rng, CHAIN_BOND)] if min(dims) > 6 else [])
+    say("case least memory", dims, storage, streaming)
+    torch_allocs.most = arena_bytes(dims, storage)
+    ob = case.oracle_box()
+    ctx = make_ctx(case, storage, torch_alloc=True, streaming=lbm.STREAM_AA if streaming == "in_place" else lbm.STREAM_AB)
+    torch_allocs.most = None  # the readouts below stage FP64 fields
+    for n in (1, 2, 3):
+        ctx.step(n)
+        assert ctx.sync_status() == lbm.OK and ob.step(n) == 0
+        check(compare(ctx, ob, case, storage), storage, f"least memory {dims} {streaming}")
+    ctx.close()
+
+
+@pytest.mark.parametrize("streaming", ["two_buffers", "in_place"])
+@pytest.mark.parametrize("storage,dims", [("f16", (33, 9, 40)), ("f16", (1030, 4, 6)), ("f16", (9, 17, 9)),
+                                          ("f16", (73, 41, 20)), ("f32", (65, 65, 9)), ("f32", (5, 11, 7))])
+def test_padding_stays_within_its_bound(storage, dims, streaming, torch_allocs):
+    """Half as many nodes again in x (short rows: up to 16) and a quarter in y."""
+    nx, ny, nz = dims
+    ctx = lbm.Context([dims], storage=STORE[storage], torch_alloc=True,
+                      streaming=lbm.STREAM_AA if streaming == "in_place" else lbm.STREAM_AB)
+    ctx.close()
+    most = arena_bytes((max(16, 3 * nx // 2 + 8), ny + ny // 4, nz), storage)
+    say("case padding", dims, storage, torch_allocs.sizes[0], "of", most)
+    assert torch_allocs.sizes[0] <= most
+
+
+@pytest.mark.parametrize("streaming,dims", [("two_buffers", (73, 3000, 3000)), ("in_place", (97, 4001, 4001))])
+def test_large_contexts_are_not_padded(streaming, dims, torch_allocs):
+    """Padding that adds more than 1/32 of the device's memory is not asked for
+    (the allocations are recorded and refused)."""
+    torch_allocs.most = 0
+    with pytest.raises(lbm.LBError) as e:
+        lbm.Context([dims], storage=lbm.STORE_F16DEV, torch_alloc=True,
+                    streaming=lbm.STREAM_AA if streaming == "in_place" else lbm.STREAM_AB)
+    assert e.value.status == lbm.ERR_OOM
+    say("case unpadded", dims, max(torch_allocs.sizes))
+    assert max(torch_allocs.sizes) == arena_bytes(dims, "f16")
