@@ -1119,13 +1119,15 @@ int64_t layout_bytes(const lb_ctx* ctx) {
 // padding takes up to half as many nodes again in x (rows shorter than 16:
 // up to 16) and a quarter in y, so it is used while what it adds to the context
 // is below 1/32 of the device's memory, and given up where its buffers cannot be
-// had: a context fits wherever its boxes' own nodes do.
+// had: a context fits wherever its boxes' own nodes do.  A layout whose x-face
+// blocks 32-bit offsets do not reach is passed over too: its boxes padded, or
+// in place, run as tile items.
 bool allocate_arenas(lb_ctx* ctx, std::vector<int4>& xf_items) {
   lay_out(ctx, ROWS_LEAST, nullptr);
   const int64_t least = layout_bytes(ctx);
   size_t free_bytes = 0, total = 0;
   for (Rows rows : {ROWS_PADDED, ROWS_EXACT, ROWS_LEAST}) {
-    lay_out(ctx, rows, &xf_items);
+    if (!lay_out(ctx, rows, &xf_items)) continue;
     const int64_t more = layout_bytes(ctx) - least;
     if (rows != ROWS_LEAST && more > 0) {
       if (!total && hipMemGetInfo(&free_bytes, &total) != hipSuccess) (void)hipGetLastError();
@@ -1272,7 +1274,7 @@ lb_status lb_init(const lb_config* cfg, lb_ctx** out) {
     b.nn = nn;
     ctx->bx.push_back(b);
   }
-  if (!lay_out(ctx, ROWS_PADDED, nullptr)) {  // more x-face nodes than 32-bit offsets reach
+  if (!lay_out(ctx, ROWS_LEAST, nullptr)) {  // more x-face nodes than 32-bit offsets reach
     lb_free(ctx);
     return LB_ERR_ARG;
   }
