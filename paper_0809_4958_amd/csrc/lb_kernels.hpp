@@ -486,7 +486,7 @@ __global__ __launch_bounds__(chain_threads(MB), 4) void k_chain(
   }
   // spread force of the box's nodes, - sum_j w_jx dP_j: 64 nodes at a time,
   // wave w summing its share of the beads, the waves' partials added in order
-  if ((int64_t)len[0] * len[1] * len[2] > GTAB) return;
+  if (!gtab || (int64_t)len[0] * len[1] * len[2] > GTAB) return;
   const int vol = len[0] * len[1] * len[2];
   const int per = (c.nb + NW - 1) / NW;
   const int j0 = wave * per, j1 = j0 + per < c.nb ? j0 + per : c.nb;
@@ -661,7 +661,7 @@ struct LbArgs {
   const void* rec_d;
   const void* rec_dp;
   const int* bbox;
-  const double* gtab;      // [n_chains][GTAB][3] spread force of each chain's stencil box
+  const double* gtab;      // [n_chains][GTAB][3] spread force of each chain's stencil box, or NULL
   DevState* st;
   double* partials;        // [n_check][4] mass/momentum partials of k_check
   const int4* check_items; // k_check workgroups: box, first row, end row (row z ny + y)
@@ -791,7 +791,7 @@ __device__ __forceinline__ void gather_force(const LbArgs& A, const BoxDesc& b,
           in_range<PER>(y, bb[1], bb[4], b.ny, b.pmask & 2)))
       continue;
     const int len0 = bb[3] - bb[0] + 1, len1 = bb[4] - bb[1] + 1, len2 = bb[5] - bb[2] + 1;
-    if ((int64_t)len0 * len1 * len2 <= GTAB) {  // summed by k_chain already
+    if (A.gtab && (int64_t)len0 * len1 * len2 <= GTAB) {  // summed by k_chain already
       int ix = x - bb[0], iy = y - bb[1], iz = z - bb[2];
       if (PER) {
         if (ix < 0) ix += b.nx;

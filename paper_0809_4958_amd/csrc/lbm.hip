@@ -255,7 +255,7 @@ struct lb_ctx {
   void* d_rec_dp = nullptr;
   int* d_bbox = nullptr;
   double* d_bead_out = nullptr;    // [total_beads][3] staging of bead readouts to the host
-  double* d_gtab = nullptr;        // [n_chains][GTAB][3] spread force of the stencil boxes
+  double* d_gtab = nullptr;        // [n_chains][GTAB][3] spread force of the stencil boxes, or none
   int total_beads = 0;
   int n_items = 0, n_entries = 0, grid = 0;
   std::vector<Item> items;
@@ -771,10 +771,16 @@ lb_status upload_chains(lb_ctx* ctx) {
   ctx->d_rec_d = dalloc(ctx, 3 * nbd * rb);
   ctx->d_rec_dp = dalloc(ctx, 3 * nbd * rb);
   ctx->d_bbox = dalloc_t<int>(ctx, 6 * std::max<size_t>(1, cd.size()), &ok);
-  ctx->d_gtab = dalloc_t<double>(ctx, cd.size() * GTAB * 3, &ok);
-  ctx->d_bead_out = dalloc_t<double>(ctx, 3 * nbd, &ok);
   if (!ok || !ctx->d_pos || !ctx->d_vel || !ctx->d_rec_d || !ctx->d_rec_dp)
     return fail(ctx, LB_ERR_OOM, "chain allocation failed");
+  // The force table saves time only: 24 KiB a chain, done without where that is
+  // more than 1/32 of the device's memory (as padded rows are) or cannot be had.
+  // The force is then gathered bead by bead.
+  const size_t gtab_bytes = cd.size() * GTAB * 3 * sizeof(double);
+  size_t free_bytes = 0, total = 0;
+  if (hipMemGetInfo(&free_bytes, &total) == hipSuccess && gtab_bytes <= total / 32)
+    ctx->d_gtab = (double*)dalloc(ctx, gtab_bytes);
+  (void)hipGetLastError();
   if (!cd.empty())
     HIPCHK(h2d(ctx, ctx->d_chains, cd.data(), cd.size() * sizeof(ChainDesc)));
   const int par = (int)(ctx->host_step & 1);
@@ -1810,8 +1816,12 @@ lb_status lb_read_fields(lb_ctx* ctx, int32_t box, lb_field field, void* dst, si
       HIPCHK(hipStreamSynchronize(ctx->stream));
       return ctx->latched;
     }
-    double* out = dst_on_device ? (double*)dst : ctx->d_bead_out;
     const size_t nbd = std::max(1, ctx->total_beads);
+    if (!dst_on_device && !ctx->d_bead_out) {  // kept for the next readout
+      ctx->d_bead_out = (double*)dalloc(ctx, 3 * nbd * sizeof(double));
+      if (!ctx->d_bead_out) return fail(ctx, LB_ERR_OOM, "readout allocation failed");
+    }
+    double* out = dst_on_device ? (double*)dst : ctx->d_bead_out;
     const bool is_pos = field != LB_F_BEAD_VEL;
     const void* src = (char*)(is_pos ? ctx->d_pos : ctx->d_vel) + (size_t)par * 3 * nbd * sizeof(double);
     hipLaunchKernelGGL(k_read_beads<double>, dim3(1), dim3(WG), 0, ctx->stream, ctx->d_chains, c0, c1,

@@ -374,3 +374,26 @@ def test_large_contexts_are_not_padded(streaming, dims, torch_allocs):
     assert e.value.status == lbm.ERR_OOM
     say("case unpadded", dims, max(torch_allocs.sizes))
     assert max(torch_allocs.sizes) == arena_bytes(dims, "f16")
+
+
+@pytest.mark.parametrize("streaming", ["two_buffers", "in_place"])
+@pytest.mark.parametrize("storage,pmask", [("f64", 0), ("f16", 0), ("f32", 7)])
+def test_chains_step_without_a_force_table(storage, pmask, streaming, torch_allocs):
+    """The chains' force table (24 KiB each) is an allocation that can be done
+    without: the force is gathered from the beads, k_chain writes no table."""
+    rng = np.random.default_rng(71)
+    dims, steps = (16, 15, 17), 6
+    bc = None if pmask else (oracle.BC_AFFINE, inputs.ou_strain(steps + 1, rng, corr_steps=20.0, rms=1e-3), 0, 1, 0)
+    case = Case(dims, collision=oracle.MRT, tau=0.8, periodic_mask=pmask, bc=bc,
+                u0=1e-3 * rng.standard_normal(dims[::-1] + (3,)),
+                chains=[walk(b, [7.4, 7.1, 8.2], rng, CHAIN_BOND) for b in (5, 9, 70)])
+    say("case no force table", storage, pmask, streaming)
+    ob = case.oracle_box()
+    assert ob.step(steps) == 0
+    ctx = make_ctx(case, storage, torch_alloc=True, streaming=lbm.STREAM_AA if streaming == "in_place" else lbm.STREAM_AB)
+    torch_allocs.most = 3 * 24576 - 1
+    ctx.step(steps)
+    assert ctx.sync_status() == lbm.OK and max(torch_allocs.sizes[-12:]) >= 3 * 24576
+    torch_allocs.most = None
+    check(compare(ctx, ob, case, storage), storage, f"no force table {streaming}")
+    ctx.close()
