@@ -140,6 +140,28 @@ def _p(a: np.ndarray):
     return a.ctypes.data_as(ct.c_void_p)
 
 
+def torch_allocator():
+    """The (dev_alloc, dev_free) hooks that take device memory from PyTorch's
+    caching allocator on the current device.  No exception may leave them: ctypes
+    drops it, and the library would get whatever the last call returned."""
+    import torch
+    dev = torch.cuda.current_device()
+    alloc, delete = torch.cuda.caching_allocator_alloc, torch.cuda.caching_allocator_delete
+
+    def _alloc(n, user):
+        try:
+            return alloc(int(n), dev)
+        except Exception:  # out of memory
+            return None
+
+    def _free(ptr, user):
+        try:
+            delete(ptr)
+        except Exception:  # interpreter shutdown: the process frees everything
+            pass
+    return ALLOC_FN(_alloc), FREE_FN(_free)
+
+
 class Context:
     """One library context (one or many boxes advanced together)."""
 
@@ -168,23 +190,7 @@ class Context:
             self._tc = tune_cache.encode()
             cfg.tune_cache = self._tc
         if torch_alloc:
-            import torch
-            dev = torch.cuda.current_device()
-
-            alloc, delete = torch.cuda.caching_allocator_alloc, torch.cuda.caching_allocator_delete
-
-            def _alloc(n, user):
-                try:
-                    return alloc(int(n), dev)
-                except RuntimeError:  # out of memory: the library may go on with less
-                    return None
-
-            def _free(ptr, user):
-                try:
-                    delete(ptr)
-                except Exception:  # interpreter shutdown: the process frees everything
-                    pass
-            self._cb = (ALLOC_FN(_alloc), FREE_FN(_free))
+            self._cb = torch_allocator()
             cfg.dev_alloc, cfg.dev_free = self._cb
         h = ct.c_void_p()
         st = self._lib.lb_init(ct.byref(cfg), ct.byref(h))

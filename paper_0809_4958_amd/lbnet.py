@@ -83,20 +83,7 @@ class Upsampler:
         cfg.max_batch = self.max_batch
         cfg.stream = stream
         if torch_alloc:
-            import torch
-            dev = torch.cuda.current_device()
-
-            alloc, delete = torch.cuda.caching_allocator_alloc, torch.cuda.caching_allocator_delete
-
-            def _alloc(n, user):
-                return alloc(int(n), dev)
-
-            def _free(ptr, user):
-                try:
-                    delete(ptr)
-                except Exception:  # interpreter shutdown: the process frees everything
-                    pass
-            self._cb = (lbm.ALLOC_FN(_alloc), lbm.FREE_FN(_free))
+            self._cb = lbm.torch_allocator()
             cfg.dev_alloc, cfg.dev_free = self._cb
         h = ct.c_void_p()
         st = self._lib.lbn_init(ct.byref(cfg), ct.byref(h))

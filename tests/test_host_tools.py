@@ -127,3 +127,33 @@ def test_long_run_sites_and_subset():
         f = full[b["index"]]
         assert f["n"] == b["n"] and np.array_equal(f["faces"], b["faces"])
         assert np.array_equal(f["u0"], b["u0"]) and np.array_equal(f["pos"], b["pos"])
+
+
+@pytest.mark.parametrize("binding", ["lbm", "lbnet"])
+def test_pytorch_out_of_memory_reaches_the_library_as_null(binding, monkeypatch):
+    """An allocation that PyTorch refuses is NULL in C, not the pointer that the
+    hook returned before it."""
+    torch = pytest.importorskip("torch")
+    from paper_0809_4958_amd import lbm, lbnet
+
+    def alloc(n, dev):
+        if n > 1000:
+            raise torch.cuda.OutOfMemoryError("no memory")
+        return 0x7F0000001000
+
+    got = []
+
+    class Library:
+        @staticmethod
+        def init(cfg, h):
+            got.extend(cfg._obj.dev_alloc(n, None) for n in (8, 4096, 16, 1 << 30))
+            return lbm.ERR_OOM
+
+    Library.lb_init = Library.lbn_init = Library.init
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "caching_allocator_alloc", alloc)
+    monkeypatch.setattr(lbm, "load", lambda *a: Library)
+    monkeypatch.setattr(lbnet, "_lib", lambda: Library)
+    with pytest.raises(lbm.LBError):
+        lbm.Context([(8, 8, 8)], torch_alloc=True) if binding == "lbm" else lbnet.Upsampler(stream=0)
+    assert got == [0x7F0000001000, None, 0x7F0000001000, None]
