@@ -254,7 +254,7 @@ struct lb_ctx {
   void* d_rec_d = nullptr;
   void* d_rec_dp = nullptr;
   int* d_bbox = nullptr;
-  double* d_bead_out = nullptr;    // [total_beads][3] staging of bead readouts to the host
+  double* d_bead_out = nullptr;    // [total_beads][3] staging of bead readouts, once one needs it
   double* d_gtab = nullptr;        // [n_chains][GTAB][3] spread force of the stencil boxes, or none
   int total_beads = 0;
   int n_items = 0, n_entries = 0, grid = 0;
@@ -1195,6 +1195,16 @@ lb_status sync_state(lb_ctx* ctx, DevState* out) {
   return LB_OK;
 }
 
+// Whether p is memory of the context's device, which its kernels can write.
+bool own_memory(const lb_ctx* ctx, const void* p) {
+  hipPointerAttribute_t a{};
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();  // not known to the runtime
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && a.device == ctx->dev;
+}
+
 lb_status vorticity_run(lb_ctx* ctx, int32_t box, int32_t n_vol, const int32_t* vol,
                         double* mean_host, double* field_dev);
 
@@ -1817,17 +1827,20 @@ lb_status lb_read_fields(lb_ctx* ctx, int32_t box, lb_field field, void* dst, si
       return ctx->latched;
     }
     const size_t nbd = std::max(1, ctx->total_beads);
-    if (!dst_on_device && !ctx->d_bead_out) {  // kept for the next readout
+    // straight into this device's memory; anything else that a copy reaches
+    // (another device's, a host buffer) through a staging buffer that is kept
+    const bool direct = dst_on_device && own_memory(ctx, dst);
+    if (!direct && !ctx->d_bead_out) {
       ctx->d_bead_out = (double*)dalloc(ctx, 3 * nbd * sizeof(double));
       if (!ctx->d_bead_out) return fail(ctx, LB_ERR_OOM, "readout allocation failed");
     }
-    double* out = dst_on_device ? (double*)dst : ctx->d_bead_out;
+    double* out = direct ? (double*)dst : ctx->d_bead_out;
     const bool is_pos = field != LB_F_BEAD_VEL;
     const void* src = (char*)(is_pos ? ctx->d_pos : ctx->d_vel) + (size_t)par * 3 * nbd * sizeof(double);
     hipLaunchKernelGGL(k_read_beads<double>, dim3(1), dim3(WG), 0, ctx->stream, ctx->d_chains, c0, c1,
                        (const double*)src, out, field == LB_F_BEAD_POS ? 1 : 0);
     HIPCHK(hipGetLastError());
-    if (dst_on_device)
+    if (direct)
       HIPCHK(hipStreamSynchronize(ctx->stream));
     else
       HIPCHK(copy_sync(ctx, dst, out, (size_t)nb * 3 * sizeof(double), kind));

@@ -397,3 +397,28 @@ def test_chains_step_without_a_force_table(storage, pmask, streaming, torch_allo
     torch_allocs.most = None
     check(compare(ctx, ob, case, storage), storage, f"no force table {streaming}")
     ctx.close()
+
+
+@pytest.mark.parametrize("target", ["device", "device, odd address", "pinned host"])
+def test_bead_readouts_reach_every_target_a_copy_does(target):
+    """Bead readouts into memory given as the device's: this device's (written by
+    the kernel) and the rest (staged and copied; another device's is one of them)."""
+    import ctypes
+
+    import torch
+
+    rng = np.random.default_rng(73)
+    case = Case((12, 12, 12), bc=(oracle.BC_AFFINE, inputs.ou_strain(4, rng, corr_steps=20.0, rms=1e-3), 0, 1, 0),
+                chains=[walk(7, [5.4, 5.1, 6.2], rng, CHAIN_BOND)])
+    say("case bead target", target)
+    ctx = make_ctx(case, "f64")
+    ctx.step(2)
+    n = 7 * 3 * 8
+    buf = torch.zeros(n + 8, dtype=torch.uint8, device="cuda" if "device" in target else "cpu",
+                      pin_memory=target.startswith("pinned"))
+    off = 1 if "odd" in target else 0
+    for field in (lbm.F_BEAD_POS, lbm.F_BEAD_VEL, lbm.F_BEAD_REL):
+        st = lbm.load().lb_read_fields(ctx._h, 0, field, ctypes.c_void_p(buf.data_ptr() + off), n, 1)
+        assert st == lbm.OK, ctx.last_error()
+        assert buf[off:off + n].cpu().numpy().tobytes() == ctx.read(0, field, n_beads=7).tobytes()
+    ctx.close()
