@@ -560,8 +560,11 @@ static_assert(pair_backward_matches_basis(), "pair-form back transform != basis"
 // NOISE: the fluctuating collision (Duenweg, Schiller and Ladd): every relaxed
 // mode k >= 4 gains sqrt(mu rho b_k (1 - gamma_k^2)) r_k, which keeps its
 // fluctuations at the equilibrium variance mu rho b_k (mu = 3 kT); the ghosts
-// are then formed whatever GZ says.
-template <typename R, bool GZ, bool NOISE = false, bool CW = false, bool WS = false>
+// are then formed whatever GZ says.  BODY: with the accelerated frame's force.
+// It is a template argument because the plain collision must not see it: a
+// test of ext that the compiler folds away still reordered the products it fuses,
+// by an ulp at 15 % of the nodes of an FP32 step.
+template <typename R, bool GZ, bool NOISE = false, bool CW = false, bool WS = false, bool BODY = false>
 __device__ __forceinline__ void collide_mrt_pairs(R d[Q], R gx, R gy, R gz, R rho0, R omega,
                                                   R om_bulk, R om_ghost,
                                                   const Ext<R>* ext = nullptr, R sc = R(1)) {
@@ -569,7 +572,7 @@ __device__ __forceinline__ void collide_mrt_pairs(R d[Q], R gx, R gy, R gz, R rh
   mrt_forward<R>(d, m);
   const R drho = m[0];
   const R rho = rho0 + drho;
-  if (ext) {  // the accelerated frame's force density -rho a
+  if constexpr (BODY) {  // the accelerated frame's force density -rho a
     gx -= rho * ext->ax;
     gy -= rho * ext->ay;
     gz -= rho * ext->az;

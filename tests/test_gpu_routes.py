@@ -1,6 +1,8 @@
 """Routes of the step kernels at the sizes where they can go wrong, each against
 the FP64 oracle within the bounds of test_gpu_parity: stencil boxes that wrap
 around periodic axes."""
+import hashlib
+
 import numpy as np
 import pytest
 
@@ -422,3 +424,37 @@ def test_bead_readouts_reach_every_target_a_copy_does(target):
         assert st == lbm.OK, ctx.last_error()
         assert buf[off:off + n].cpu().numpy().tobytes() == ctx.read(0, field, n_beads=7).tobytes()
     ctx.close()
+
+
+# First 16 hex digits of the SHA-256 of the populations behind each step.
+PLAIN_STEP_BITS = {
+    ("f32", "mrt"): ["dac02b90f3528f46", "d41e2e064b3108dd", "f476958486f8cfe0"],
+    ("f32", "bgk"): ["2e0bc38bb79ead1d", "eb74b4b2e3d732a8", "e5c62ad05582ef26"],
+    ("f16", "mrt"): ["47a80750daeb32e6", "20d5697b8ee77a54", "164d81fa9889261f"],
+    ("f16", "bgk"): ["53fd99d6c4679fd6", "2c6ad08155da820c", "6c54f521cb7cbe9e"],
+}
+
+
+def plain_step_bits(storage, collision):
+    rng = np.random.default_rng(79)
+    dims = (40, 36, 44)
+    case = Case(dims, collision=collision, tau=0.6,
+                bc=(oracle.BC_AFFINE, inputs.ou_strain(8, rng, corr_steps=20.0, rms=1e-4), 0, 1, 0),
+                u0=1e-3 * rng.standard_normal(dims[::-1] + (3,)))
+    ctx = make_ctx(case, storage)
+    bits = []
+    for _ in range(3):
+        ctx.step(1)
+        bits.append(hashlib.sha256(np.ascontiguousarray(ctx.read(0, lbm.F_POP_DEV)).tobytes()).hexdigest()[:16])
+    ctx.close()
+    return bits
+
+
+@pytest.mark.parametrize("storage,collision", [("f32", "mrt"), ("f16", "mrt"), ("f32", "bgk"), ("f16", "bgk")])
+def test_plain_step_rounds_as_before(storage, collision):
+    """The plain step's rounding is part of its results: FP16 storage turns a last
+    bit into another half-precision value now and then, and a long run into
+    another, equally accurate one.  A change to the extended collisions (body
+    force, noise) leaves it alone."""
+    say("case plain step bits", storage, collision)
+    assert plain_step_bits(storage, {"mrt": oracle.MRT, "bgk": oracle.BGK}[collision]) == PLAIN_STEP_BITS[storage, collision]
