@@ -343,6 +343,16 @@ hipError_t dzero(lb_ctx* ctx, void* dst, size_t bytes) {
   return hipMemsetAsync(dst, 0, bytes, ctx->stream);
 }
 
+// Whether memory that only saves time may take so much: 1/32 of the device's.
+// (1 GiB is below that on the smallest partition of an MI355X, 36 GB, and is not
+// worth asking for.)
+bool spare(int64_t bytes) {
+  size_t free_bytes = 0, total = 0;
+  if (bytes <= (int64_t)1 << 30) return true;
+  if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) (void)hipGetLastError();
+  return bytes <= (int64_t)(total / 32);
+}
+
 template <typename X>
 X* dalloc_t(lb_ctx* ctx, size_t n, bool* ok) {
   X* p = (X*)dalloc(ctx, n * sizeof(X));
@@ -777,10 +787,8 @@ lb_status upload_chains(lb_ctx* ctx) {
   // more than 1/32 of the device's memory (as padded rows are) or cannot be had.
   // The force is then gathered bead by bead.
   const size_t gtab_bytes = cd.size() * GTAB * 3 * sizeof(double);
-  size_t free_bytes = 0, total = 0;
-  if (hipMemGetInfo(&free_bytes, &total) == hipSuccess && gtab_bytes <= total / 32)
-    ctx->d_gtab = (double*)dalloc(ctx, gtab_bytes);
-  (void)hipGetLastError();
+  if (spare((int64_t)gtab_bytes)) ctx->d_gtab = (double*)dalloc(ctx, gtab_bytes);
+  if (!ctx->d_gtab) (void)hipGetLastError();
   if (!cd.empty())
     HIPCHK(h2d(ctx, ctx->d_chains, cd.data(), cd.size() * sizeof(ChainDesc)));
   const int par = (int)(ctx->host_step & 1);
@@ -1131,14 +1139,10 @@ int64_t layout_bytes(const lb_ctx* ctx) {
 bool allocate_arenas(lb_ctx* ctx, std::vector<int4>& xf_items) {
   lay_out(ctx, ROWS_LEAST, nullptr);
   const int64_t least = layout_bytes(ctx);
-  size_t free_bytes = 0, total = 0;
   for (Rows rows : {ROWS_PADDED, ROWS_EXACT, ROWS_LEAST}) {
     if (!lay_out(ctx, rows, &xf_items)) continue;
     const int64_t more = layout_bytes(ctx) - least;
-    if (rows != ROWS_LEAST && more > 0) {
-      if (!total && hipMemGetInfo(&free_bytes, &total) != hipSuccess) (void)hipGetLastError();
-      if (32 * more > (int64_t)total) continue;
-    }
+    if (!spare(more)) continue;
     const size_t bytes = (size_t)ctx->arena_elems * store_bytes(ctx->S);
     ctx->arena[0] = dalloc(ctx, bytes);
     // in-place streaming: one buffer serves as both
