@@ -33,6 +33,9 @@ using namespace lbdev;
 namespace {
 
 constexpr int BND_CHUNK = 256;
+// k_force workgroups of a periodic context with fewer chains: one per compute unit
+constexpr int FORCE_GRID = 256;
+static_assert(FORCE_GRID < MAX_FORCE_PARTS, "parts of a chain in k_force");
 
 struct BoxHost {
   lb_box dim;
@@ -892,6 +895,8 @@ LbArgs make_args(lb_ctx* ctx, int pre, int advance, int reduce_every) {
   a.kT = ctx->kT;
   a.key0 = (unsigned)(ctx->seed & 0xffffffffu);
   a.key1 = (unsigned)(ctx->seed >> 32);
+  // periodic boxes: a stretched chain's stencil box can be the whole box
+  a.force_parts = ctx->per ? std::max(1, FORCE_GRID / std::max(1, (int)ctx->ch.size())) : 1;
   return a;
 }
 
@@ -952,7 +957,7 @@ void enqueue_step(lb_ctx* ctx, hipStream_t s, int pre, const hipEvent_t* ev3,
   if (chains && !ctx->aa) {  // spread force of the chains
     LbArgs f = t;
     f.advance = force_ends ? 1 : 0;
-    ctx->force_fn(dim3((unsigned)ctx->ch.size()), s, f);
+    ctx->force_fn(dim3((unsigned)ctx->ch.size() * f.force_parts), s, f);
     t.stamp_after = nullptr;
   }
   if (force_ends) return;

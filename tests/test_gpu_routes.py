@@ -458,3 +458,39 @@ def test_plain_step_rounds_as_before(storage, collision):
     force, noise) leaves it alone."""
     say("case plain step bits", storage, collision)
     assert plain_step_bits(storage, {"mrt": oracle.MRT, "bgk": oracle.BGK}[collision]) == PLAIN_STEP_BITS[storage, collision]
+
+
+@pytest.mark.parametrize("storage", ["f64", "f16"])
+@pytest.mark.parametrize("nch,pmask,dims", [(1, 7, (20, 18, 22)), (3, 7, (17, 19, 21)), (2, 5, (26, 13, 24)),
+                                            (40, 7, (16, 15, 17))])
+def test_chains_stretched_over_a_periodic_box(nch, pmask, dims, storage):
+    """Stencil boxes of thousands of nodes, shared by several workgroups of the
+    force pass: beads on a line along the periodic axes, beside compact chains that
+    need one; steps with and without a check pass, graph replays."""
+    rng = np.random.default_rng(83)
+    steps = 11
+    bc = None if pmask == 7 else (oracle.BC_AFFINE, inputs.ou_strain(steps + 1, rng, corr_steps=20.0, rms=1e-4),
+                                  0, 1, 0)
+    chains = []
+    for k in range(nch):
+        # a line over the periodic axes, or a compact walk somewhere in the box
+        line, free = k % 8 == 0, [pmask >> a & 1 for a in range(3)]
+        mid = np.array([rng.uniform(0, n) if f and k else (n - 1) / 2.0 for n, f in zip(dims, free)])
+        beads = 40 if line else 6
+        if line:
+            span = np.array([n - 1.5 if f else 2.0 for n, f in zip(dims, free)])
+            pos = ((np.arange(beads)[:, None] + 0.5) / beads - 0.5) * span + mid
+        else:
+            pos = walk(beads, mid, rng, CHAIN_BOND)["pos"]
+        chains.append(dict(pos=pos, vel=np.zeros((beads, 3)), fene_k=1e-4, anchor=list(mid)))
+    case = Case(dims, collision=oracle.MRT, tau=0.8, periodic_mask=pmask, bc=bc,
+                u0=1e-3 * rng.standard_normal(dims[::-1] + (3,)), chains=chains, reduce_every=4)
+    say("case stretched", nch, pmask, dims, storage)
+    ob = NearestImage(case)
+    ctx = make_ctx(case, storage, graph_steps=4)
+    for n in (1, 2, 8):
+        ctx.step(n)
+        assert ob.step(n) == 0 and ctx.sync_status() == lbm.OK
+        assert ctx.read(0, lbm.F_STEP) == ob.step_index
+    check(compare(ctx, ob, case, storage), storage, f"stretched {nch} {dims}")
+    ctx.close()
