@@ -399,6 +399,15 @@ void default_tile(BoxHost& b) {
   b.ez = b.vec ? 4 : std::min(b.iz, 16);
 }
 
+// An item shape; the face rows of a row box, a small share of its work, follow
+// its row items up to the default.
+void set_shape(BoxHost& b, int ex, int ey, int ez) {
+  b.ex = ex;
+  b.ey = ey;
+  b.ez = ez;
+  b.fez = std::min(4, ez);
+}
+
 // Small contexts: the default items above leave most of the chip idle (a 32^3
 // FP64 box was 4 tiles and 12 boundary chunks for 256 CUs), so items shrink
 // until the context has about SPLIT_ITEMS of them, down to one position per
@@ -415,8 +424,7 @@ void split_small(lb_ctx* ctx) {
   for (auto& b : ctx->bx) {
     if (b.vec) {
       const int64_t iter = (int64_t)WG * row_nodes(ctx->S, b.vw);
-      b.ez = (int)std::max<int64_t>(1, std::min<int64_t>(b.ez, per / iter));
-      b.fez = b.ez;
+      set_shape(b, b.ex, b.ey, (int)std::max<int64_t>(1, std::min<int64_t>(b.ez, per / iter)));
     } else {
       while (b.ez > 1 && 2 * (int64_t)b.ex * b.ey * b.ez > 3 * per) b.ez = (b.ez + 1) / 2;
       if (2 * (int64_t)b.ex * b.ey > 3 * per) b.ey = std::max(1, std::min(b.ey, WG / b.ex));
@@ -469,11 +477,8 @@ void load_tune_cache(lb_ctx* ctx) {
     if (it == entries.end()) continue;
     const auto& v = it->second;
     if (v[0] >= 1 && v[1] >= 1 && v[2] >= 1 && v[0] <= b.ix && v[1] <= b.iy && v[2] <= b.iz &&
-        v[0] * v[1] <= WG * MAX_SLOTS) {
-      b.ex = v[0];
-      b.ey = v[1];
-      b.ez = v[2];
-    }
+        v[0] * v[1] <= WG * MAX_SLOTS)
+      set_shape(b, v[0], v[1], v[2]);
     if (b.vec && (v[4] == 2 || v[4] == 3)) {
       const int V = row_nodes(ctx->S, v[4]);
       if (b.px % V == 0 && b.dim.nx > V) b.vw = v[4];
@@ -2263,9 +2268,7 @@ lb_status lb_autotune(lb_ctx* ctx, int32_t trials) {
     bool vw_changed = false;
     for (int i : members) {
       BoxHost& b = ctx->bx[i];
-      b.ex = c[0];
-      b.ey = c[1];
-      b.ez = c[2];
+      set_shape(b, c[0], c[1], c[2]);
       if (b.vec && b.vw != c[3]) {
         b.vw = c[3];
         vw_changed = true;
@@ -2294,6 +2297,11 @@ lb_status lb_autotune(lb_ctx* ctx, int32_t trials) {
     BoxHost& ref = ctx->bx[kv.second[0]];
     std::vector<Cand> cands;
     std::vector<int> exs;
+    // the shape in place first: of equally fast ones it stays
+    auto add = [&](const Cand& c) {
+      if (std::find(cands.begin(), cands.end(), c) == cands.end()) cands.push_back(c);
+    };
+    add({ref.ex, ref.ey, ref.ez, ref.vw});
     if (ref.vec) {  // row boxes: workgroup iterations per item (ez) and lane-vector width
       for (int w : {2, 3}) {
         const int V = row_nodes(ctx->S, w);
@@ -2302,7 +2310,7 @@ lb_status lb_autotune(lb_ctx* ctx, int32_t trials) {
         const double plane = (double)Q * ref.px * (ref.nyb << ref.ylog) * (double)store_bytes(ctx->S);
         const double span = (WG / ((double)(ref.px / V) * (ref.dim.ny - 2)) + 4.0) * plane;
         if (span >= 2147483648.0) continue;
-        for (int ez : {2, 4, 8, 16, 32, 64}) cands.push_back({ref.ex, ref.ey, ez, w});
+        for (int ez : {1, 2, 4, 8, 16, 32, 64}) add({ref.ex, ref.ey, ez, w});
       }
     } else {
       for (int ex : {ref.ix, 32, 64, 128, 256})
@@ -2315,10 +2323,9 @@ lb_status lb_autotune(lb_ctx* ctx, int32_t trials) {
         if (ex * ey > WG * MAX_SLOTS) continue;
         for (int ez : {1, 2, 4, 8, 16}) {
           if (ez > ref.iz) continue;
-          cands.push_back({ex, ey, ez, ref.vw});
+          add({ex, ey, ez, ref.vw});
         }
       }
-    if (cands.empty()) continue;
     std::vector<double> ms(cands.size());
     for (size_t k = 0; k < cands.size(); k++) {
       s = apply(kv.second, cands[k]);

@@ -494,3 +494,26 @@ def test_chains_stretched_over_a_periodic_box(nch, pmask, dims, storage):
         assert ctx.read(0, lbm.F_STEP) == ob.step_index
     check(compare(ctx, ob, case, storage), storage, f"stretched {nch} {dims}")
     ctx.close()
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+def test_autotuning_keeps_the_shape_that_fills_the_chip(storage, tmp_path):
+    """A 32^3 box starts with items of one workgroup iteration; two are 40 % slower
+    (8 and 11 us), so tuning keeps what it began with, and so does the cache."""
+    cache = str(tmp_path / "tune.jsonl")
+
+    def make():
+        ctx = lbm.Context([(32, 32, 32)], collision=oracle.MRT, tau=0.6, storage=STORE[storage], tune_cache=cache)
+        ctx.set_boundary(0, lbm.BC_AFFINE, np.zeros((2, 9)), t0=0, dt=1000)
+        ctx.step(1)
+        ctx.sync()
+        return ctx, ctx.describe()
+
+    ctx, start = make()
+    ctx.autotune(7)
+    say("case autotune", storage, start, "->", ctx.describe())
+    assert "->30x17x1" in start and ctx.describe() == start
+    ctx.close()
+    ctx, again = make()
+    assert again == start
+    ctx.close()
