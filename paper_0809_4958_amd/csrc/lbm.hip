@@ -476,6 +476,9 @@ void load_tune_cache(lb_ctx* ctx) {
     auto it = entries.find(box_key(ctx, b));
     if (it == entries.end()) continue;
     const auto& v = it->second;
+    // a padded row box ran as tile items once: a shape saved without a vector
+    // width is one of tiles, whose planes are not iterations of row items
+    if (b.vec && b.px != b.dim.nx && v[4] < 2) continue;
     if (v[0] >= 1 && v[1] >= 1 && v[2] >= 1 && v[0] <= b.ix && v[1] <= b.iy && v[2] <= b.iz &&
         v[0] * v[1] <= WG * MAX_SLOTS)
       set_shape(b, v[0], v[1], v[2]);

@@ -517,3 +517,30 @@ def test_autotuning_keeps_the_shape_that_fills_the_chip(storage, tmp_path):
     ctx, again = make()
     assert again == start
     ctx.close()
+
+
+def tune_line(storage, dims, shape, periodic=0, vw=None):
+    """A line of an autotuner cache: the item shape of an MRT box."""
+    import json
+
+    d = dict(key=f"S{STORE[storage]}C1_{dims[0]}x{dims[1]}x{dims[2]}p{periodic}", ex=shape[0], ey=shape[1], ez=shape[2])
+    return json.dumps(d if vw is None else dict(d, vw=vw)) + "\n"
+
+
+@pytest.mark.parametrize("vw,taken", [(0, False), (None, False), (2, True)])
+def test_tile_shapes_of_older_caches_are_not_row_shapes(vw, taken, tmp_path):
+    """An autotuner cache from when a 121-node row ran as tiles: its 16 planes per
+    item do not become 16 iterations of a row item."""
+    cache, dims = tmp_path / "tune.jsonl", (121, 24, 25)
+
+    def shape(path):
+        ctx = lbm.Context([dims], collision=oracle.MRT, tau=0.6, storage=lbm.STORE_F32, tune_cache=path)
+        ctx.set_boundary(0, lbm.BC_AFFINE, np.zeros((2, 9)), t0=0, dt=1000)
+        ctx.step(1)
+        d = ctx.describe().split("->")[-1]
+        ctx.close()
+        return d
+
+    cache.write_text(tune_line("f32", dims, (64, 4, 16), vw=vw))
+    say("case old cache", vw, shape(None), shape(str(cache)))
+    assert (shape(str(cache)) == "64x4x16") if taken else (shape(str(cache)) == shape(None))
