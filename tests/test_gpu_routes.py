@@ -544,3 +544,94 @@ def test_tile_shapes_of_older_caches_are_not_row_shapes(vw, taken, tmp_path):
     cache.write_text(tune_line("f32", dims, (64, 4, 16), vw=vw))
     say("case old cache", vw, shape(None), shape(str(cache)))
     assert (shape(str(cache)) == "64x4x16") if taken else (shape(str(cache)) == shape(None))
+
+
+SHAPES = [  # dims, periodic axes, items of one iteration each, items of several
+    ("tiles", (34, 30, 25), 0, (16, 8, 1), (32, 20, 7)),
+    ("tiles", (23, 37, 18), 0, (21, 1, 1), (21, 35, 16)),
+    ("tiles", (48, 20, 19), 7, (16, 4, 1), (48, 20, 6)),
+    ("tiles", (19, 33, 14), 5, (19, 1, 1), (19, 31, 14)),
+    ("rows", (150, 21, 22), 0, (64, 8, 1), (64, 8, 2)),
+    ("rows", (150, 21, 22), 0, (64, 8, 1), (64, 8, 4)),
+    ("rows", (95, 25, 23), 0, (93, 5, 1), (93, 5, 3)),
+    ("rows", (61, 40, 24), 0, (59, 8, 1), (59, 8, 3)),
+    ("rows", (64, 33, 20), 0, (62, 8, 1), (62, 8, 4)),
+]
+
+
+@pytest.mark.parametrize("streaming", ["two_buffers", "in_place"])
+@pytest.mark.parametrize("kind,dims,pmask,small,large", SHAPES)
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16"])
+def test_item_shape_does_not_change_a_bit(kind, dims, pmask, small, large, storage, streaming, tmp_path, monkeypatch):
+    """Items of several planes, positions per thread or workgroup iterations (the
+    shapes of large contexts, fixed here through the autotuner cache) give the
+    bits of items that take one pass through every loop, as the small boxes of the
+    parity tests do; a chain meets some of the iterations of an item."""
+    if storage == "f64" and kind == "rows":
+        pytest.skip("FP64 boxes run as tiles")
+    if kind == "tiles":
+        monkeypatch.setenv("LBM_NO_VEC", "1")
+    rng = np.random.default_rng(89)
+    bc = None if pmask == 7 else (oracle.BC_AFFINE, inputs.ou_strain(8, rng, corr_steps=20.0, rms=1e-3 * 8 / max(dims)),
+                                  0, 1, 0)
+    case = Case(dims, collision=oracle.MRT, tau=0.8, periodic_mask=pmask, bc=bc,
+                u0=1e-3 * rng.standard_normal(dims[::-1] + (3,)), reduce_every=3,
+                chains=[walk(9, [(n - 1) / 2.0 for n in dims], rng, CHAIN_BOND),
+                        walk(5, [4.3, 5.1, 3.7], rng, CHAIN_BOND)])
+    mode = lbm.STREAM_AA if streaming == "in_place" else lbm.STREAM_AB
+    say("case item shapes", kind, dims, pmask, small, large, storage, streaming)
+    ctxs = []
+    for k, shape in enumerate((small, large)):
+        cache = tmp_path / f"tune{k}.jsonl"
+        cache.write_text(tune_line(storage, dims, shape, periodic=pmask, vw=2 if kind == "rows" else 0))
+        ctxs.append(make_ctx(case, storage, streaming=mode, tune_cache=str(cache)))
+    for n in (1, 4, 1):
+        out = []
+        for ctx, shape in zip(ctxs, (small, large)):
+            ctx.step(n)
+            assert ctx.sync_status() == lbm.OK
+            assert ctx.describe().endswith("->%dx%dx%d" % shape)
+            out.append([ctx.read(0, lbm.F_POP_DEV), ctx.read(0, lbm.F_BEAD_POS, n_beads=14),
+                        ctx.read(0, lbm.F_MASS_MOM)])
+        assert all(np.array_equal(a, b) for a, b in zip(*out))
+    for ctx in ctxs:
+        ctx.close()
+
+
+@pytest.mark.parametrize("streaming", ["two_buffers", "in_place"])
+@pytest.mark.parametrize("storage,dims", [("f16", (41, 6, 7)), ("f16", (47, 9, 5)), ("f16", (73, 5, 9)), ("f16", (95, 7, 5)),
+                                          ("f16", (161, 4, 5)), ("f16", (191, 5, 4)), ("f32", (37, 6, 7)),
+                                          ("f32", (47, 5, 9)), ("f32", (81, 9, 5)), ("f32", (95, 5, 6)),
+                                          ("f32", (177, 4, 5)), ("f32", (191, 5, 4))])
+def test_padded_rows_of_three_word_vectors(dims, storage, streaming):
+    """Row lengths padded to whole vectors of three words, the last node in each
+    place of its vector."""
+    test_rows_of_any_length(dims, storage, streaming)
+
+
+@pytest.mark.parametrize("items", ["tiles", "rows"])
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+def test_in_place_equals_two_buffers(storage, items, monkeypatch):
+    """In-place tile and row items against the two-buffer tiles: FP16 bit for bit,
+    FP32 to the 8 units in the last place of test_gpu_aa."""
+    cases = [ks_case(n, 40, dt=20, res=9, n_beads=6, config_idx=2, box_idx=i) for i, n in enumerate([20, 27])]
+    say("case in place", items, "vs two-buffer tiles", storage)
+    ctxs = []
+    for mode, tiles in ((lbm.STREAM_AA, items == "tiles"), (lbm.STREAM_AB, True)):
+        monkeypatch.setenv("LBM_NO_VEC", "1") if tiles else monkeypatch.delenv("LBM_NO_VEC", raising=False)
+        ctx = lbm.Context([c.dims for c in cases], collision=cases[0].collision, tau=cases[0].tau,
+                          storage=STORE[storage], streaming=mode)
+        for k, c in enumerate(cases):
+            c.add_to(ctx, k)
+        ctxs.append(ctx)
+    for n in (13, 14):  # odd, then even step counts
+        for ctx in ctxs:
+            ctx.step(n)
+        for k in range(len(cases)):
+            pa, pb = (c.read(k, lbm.F_POP_DEV) for c in ctxs)
+            if storage == "f16":
+                assert np.array_equal(pa, pb), (n, k)
+            else:
+                assert np.abs(pa - pb).max() <= 8 * np.spacing(np.float32(np.abs(pb).max())), (n, k)
+    for ctx in ctxs:
+        ctx.close()
