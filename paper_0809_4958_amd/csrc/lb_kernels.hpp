@@ -682,7 +682,6 @@ struct LbArgs {
   double kT;               // thermal fluctuations (fluctuating MRT) when > 0
   unsigned key0, key1;     // Philox key of the context's random numbers
   int aa;                  // in-place streaming on one buffer (a0 == a1)
-  int force_parts;         // k_force workgroups per chain, below MAX_FORCE_PARTS
 };
 
 // Collision dispatcher: 0 BGK, 1 MRT, 2 MRT with ghost rate 1.  CW: the
@@ -1735,25 +1734,23 @@ __global__ __launch_bounds__(BS, lb_min_waves(S)) void k_lb(LbArgs A) {
 // chains took 1461 us, 1414 us of it k_lb; with this pass 98 us, k_lb 48 us
 // and the pass 10 us.)
 // Where the stencil boxes of two chains overlap, both workgroups compute the
-// node and store the same values.  One workgroup per chain, in periodic contexts
-// A.force_parts: part k of chain c is workgroup k n_chains + c and takes every
-// force_parts-th 256 nodes from node 256 k on; parts that a stencil box has no
-// nodes for leave at once.  They are enough to fill the chip, because a chain's
-// stencil box can be its whole box: a step with 256 beads on the diagonal of a
-// 96^3 FP32 box took 138 ms on one workgroup, 0.67 ms so, four chains of 128 there
-// 280 and 4.5 ms (gathered in k_lb 2.7 and 5.3 ms).  On steps that have no check
-// pass the last workgroup also ends the step (step index advance), which then
-// needs no launch of its own.
+// node and store the same values.  One workgroup per chain; in periodic contexts
+// gridDim.y of them, each taking every gridDim.y-th 256 nodes of the stencil box,
+// and those that it has no nodes for leave at once.  They are enough to fill the
+// chip, because a chain's stencil box can be its whole box: a step with 256 beads
+// on the diagonal of a 96^3 FP32 box took 138 ms on one workgroup, 0.67 ms so, four
+// chains of 128 there 280 and 4.5 ms (gathered in k_lb 2.7 and 5.3 ms).  Walled
+// boxes keep one: their stencil boxes end at the walls that bound the flow, and
+// the parts cost a 25 us step of a 32^3 box 0.3 us (a 64^3 FP32 box spanned by 128
+// beads takes 15.0 ms a step, and 0.11 with parts).  On steps that have no check pass
+// the last workgroup also ends the step (step index advance), which then needs
+// no launch of its own.
 template <int S, int COLL, bool PER, int EXT = 0>
 __global__ __launch_bounds__(WG) void k_force(LbArgs A) {
   using St = Store<S>;
   using T = typename St::T;
   using R = typename St::R;
-  // a constant where there is one part: the division and the tests on the way to
-  // the first load took 0.6 us of a 25 us step of a 32^3 box
-  const int parts = PER ? A.force_parts : 1;
-  const int n_chains = PER ? (int)gridDim.x / parts : (int)gridDim.x;
-  const int part = PER ? (int)blockIdx.x / n_chains : 0, gc = (int)blockIdx.x - part * n_chains;
+  const int gc = blockIdx.x, part = PER ? blockIdx.y : 0, parts = PER ? gridDim.y : 1;
   // inputs read before the timestamp store (see k_check)
   const bool latched =
       __hip_atomic_load(&A.st->err_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != ERR_NONE;
@@ -1763,7 +1760,7 @@ __global__ __launch_bounds__(WG) void k_force(LbArgs A) {
   int bb[6];
 #pragma unroll
   for (int a = 0; a < 6; a++) bb[a] = A.bbox[6 * gc + a];
-  put_stamp(A.stamp_after);
+  if (part == 0) put_stamp(A.stamp_after);
   if (latched) return;  // uniform: set before this launch or not at all
   const int lx = bb[3] - bb[0] + 1, ly = bb[4] - bb[1] + 1, lz = bb[5] - bb[2] + 1;
   const int n = (lx > 0 && ly > 0 && lz > 0) ? lx * ly * lz : 0;
@@ -1777,7 +1774,7 @@ __global__ __launch_bounds__(WG) void k_force(LbArgs A) {
     const unsigned long long all =
         b.chain_count >= MAX_BOX_CHAINS ? ~0ull : (1ull << b.chain_count) - 1ull;
 #pragma unroll 1
-    for (int64_t q = part * WG + (int)threadIdx.x; q < n; q += parts * WG) {
+    for (unsigned q = part * WG + threadIdx.x; q < (unsigned)n; q += parts * WG) {
       const int p = (int)q;
       int x = bb[0] + p % lx, y = bb[1] + (p / lx) % ly, z = bb[2] + p / (lx * ly);
       if (PER) {  // a stencil box may wrap on periodic axes
@@ -1817,7 +1814,7 @@ __global__ __launch_bounds__(WG) void k_force(LbArgs A) {
       const int chain = parts > 1 ? MAX_FORCE_PARTS : 1;
       const int others = min(parts - 1, (max(n, 1) - 1) / WG);
       const int mine = part > 0 ? 1 : chain - others;
-      if (atomicAdd(&A.st->tickets, mine) + mine == chain * n_chains) {
+      if (atomicAdd(&A.st->tickets, mine) + mine == chain * (int)gridDim.x) {
         atomicExch(&A.st->tickets, 0);
         A.st->step = step + 1;
       }

@@ -34,7 +34,7 @@ namespace {
 
 constexpr int BND_CHUNK = 256;
 // k_force workgroups of a periodic context with fewer chains: one per compute unit
-constexpr int FORCE_GRID = 256;
+constexpr unsigned FORCE_GRID = 256;
 static_assert(FORCE_GRID < MAX_FORCE_PARTS, "parts of a chain in k_force");
 
 struct BoxHost {
@@ -903,8 +903,6 @@ LbArgs make_args(lb_ctx* ctx, int pre, int advance, int reduce_every) {
   a.kT = ctx->kT;
   a.key0 = (unsigned)(ctx->seed & 0xffffffffu);
   a.key1 = (unsigned)(ctx->seed >> 32);
-  // periodic boxes: a stretched chain's stencil box can be the whole box
-  a.force_parts = ctx->per ? std::max(1, FORCE_GRID / std::max(1, (int)ctx->ch.size())) : 1;
   return a;
 }
 
@@ -965,7 +963,8 @@ void enqueue_step(lb_ctx* ctx, hipStream_t s, int pre, const hipEvent_t* ev3,
   if (chains && !ctx->aa) {  // spread force of the chains
     LbArgs f = t;
     f.advance = force_ends ? 1 : 0;
-    ctx->force_fn(dim3((unsigned)ctx->ch.size() * f.force_parts), s, f);
+    const unsigned n = (unsigned)ctx->ch.size();
+    ctx->force_fn(dim3(n, ctx->per ? std::max(1u, FORCE_GRID / n) : 1u), s, f);
     t.stamp_after = nullptr;
   }
   if (force_ends) return;
