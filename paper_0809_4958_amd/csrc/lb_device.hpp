@@ -650,9 +650,10 @@ __device__ __forceinline__ void collide_mrt_pairs(R d[Q], R gx, R gy, R gz, R rh
 // 19 population rows of a block of Y consecutive y lines are adjacent, and
 // each population's Y rows are contiguous, so that a population row of a
 // block spans whole 128-byte lines when nx is short (Y = 1 gives
-// pop[z][y][i][x]).  Row boxes whose nx no lane vector divides pad their rows
-// to px nodes and ny to whole blocks; pad nodes belong to no one: the step
-// computes on them, and nothing reads them into a node of the box.  The
+// pop[z][y][i][x]).  Row boxes may pad their rows to px nodes, where that pitch is
+// the faster one, and then ny to whole blocks (Y up to 8); pad nodes belong to
+// no one: the step computes on them, and nothing reads them into a node of the
+// box.  The
 // populations a node pulls lie in at most nine
 // neighbouring lines (y - c_y, z - c_z).
 __host__ __device__ __forceinline__ int64_t aidx(const BoxDesc& b, int i, int x, int y, int z) {

@@ -19,7 +19,8 @@ namespace lbdev {
 // Latency: each box is a chain of loads (offsets, partials), a wavefront sum
 // and a store, about 1.6 us, so check steps launch FIN_CHECK threads and a
 // wavefront takes FIN_BOXES boxes side by side (256 boxes one at a time
-// on four wavefronts: 106 us, so: 42).
+// on four wavefronts: 106 us, so: 42; with the few partials of whole-plane check
+// slabs it was 10, and k_check 611 instead of 580, so a check step takes as long).
 constexpr int FIN_CHECK = 1024, FIN_BOXES = 4;
 __global__ __launch_bounds__(FIN_CHECK) void k_finalize(LbArgs A) {
   const int tid = threadIdx.x;

@@ -10,10 +10,12 @@
 //             pull streaming, collide and store (in-place streaming also
 //             gathers the spread force of the chains); boundary items store
 //             the boundary equilibrium populations that point into the interior.
-//   k_force   after k_lb with two buffers, one workgroup per chain: the
-//             nodes of the chain's stencil box collide again with the spread
-//             force gathered from the records (fixed bead order, no atomics);
-//             on steps without a check pass its last workgroup ends the step.
+//   k_force   after k_lb with two buffers, one workgroup per chain (several in
+//             periodic contexts): the nodes of the chain's stencil box collide
+//             again with the spread force that k_chain left in its table, or,
+//             for a stencil box larger than that, gathered from the records
+//             (fixed bead order, no atomics); on steps without a check pass its
+//             last workgroup ends the step.
 //   k_check   on check steps: FP64 partial sums of the interior's mass and
 //             momentum at t_{n+1} from the arena k_lb wrote; k_finalize
 //             (lb_io_kernels.hpp) adds them per box.
@@ -141,7 +143,9 @@ constexpr int GTAB = 1024;
 // second substep on (thermal noise has no such form and is summed).
 // Measured per launch, 128^3 FP32 with 64 beads 25.4 -> 13.8 us, 32^3 FP64 with
 // 16 beads 21.4 -> 11.0 us, 384^3 FP16 with 16 chains of 256 beads 46 -> 36 us;
-// k_force in the same boxes 13.3 -> 4.9, 6.7 -> 4.4 and 53 -> 8.5 us.  256
+// k_force in the same boxes 13.3 -> 4.9, 6.7 -> 4.4 and 53 -> 8.5 us.  In the
+// batch of 256 FP16 boxes, where the x-face work beside the chains decides, this
+// launch went from 26.0 to 28.3 us and k_force from 14.7 to 9.7.  256
 // threads instead of 512 take 18.0 us on the 128^3 box (two rounds of
 // interpolation), 512 instead of 1024 with 256 beads 38-41 us.
 // Workgroups n_chains and up compute the x-face boundary velocities of the
@@ -910,10 +914,10 @@ __device__ __forceinline__ void tile_fast(const LbArgs& A, const BoxDesc& b, con
 // Row items: each lane owns V consecutive nodes of one x-row, held as W 32-bit
 // words (V = 2W FP16 or W FP32 values), and moves every population with one
 // aligned W-word load and one W-word store.  The interior rows (y, z) of a box
-// (1 <= y <= ny-2, 1 <= z <= nz-2), each cut into L = nx / V lane groups, are
-// numbered consecutively, and a workgroup walks BS consecutive groups per
-// iteration, so rows may straddle wavefronts and every lane is busy for any
-// nx divisible by V.  The pull's +-1 shift in x is an element selection
+// (1 <= y <= ny-2, 1 <= z <= nz-2), each cut into L = px / V lane groups (px the
+// nodes a row takes in memory), are numbered consecutively, and a workgroup
+// walks BS consecutive groups per iteration, so rows may straddle wavefronts and
+// every lane has a group.  The pull's +-1 shift in x is an element selection
 // inside the lane's vector plus one element of the neighbouring group: a lane
 // shuffle inside the wavefront, or a direct load for the first and last lane
 // of a wavefront.  The groups holding x = 0 or x = nx-1 store the boundary
@@ -1041,18 +1045,6 @@ __device__ __forceinline__ void vput_keep(unsigned (&w)[W], int e, typename Stor
     Store<2>::keep_into(w[e >> 1], (e & 1) != 0, x, r, true);
   } else {
     w[e] = __builtin_bit_cast(unsigned, Store<S>::keep(x, r));
-  }
-}
-
-template <int S, int W>
-__device__ __forceinline__ void vput(unsigned (&w)[W], int e, typename Store<S>::T val) {
-  using T = typename Store<S>::T;
-  if constexpr (sizeof(T) == 2) {
-    const unsigned h = (unsigned)__builtin_bit_cast(unsigned short, val);
-    unsigned& word = w[e >> 1];
-    word = (e & 1) ? ((word & 0xffffu) | (h << 16)) : ((word & 0xffff0000u) | h);
-  } else {
-    w[e] = __builtin_bit_cast(unsigned, val);
   }
 }
 
@@ -1238,7 +1230,7 @@ __device__ __forceinline__ void tile_rows(const LbArgs& A, const BoxDesc& b, con
     if (!PRE) {
       // first / last lane of the wavefront: the neighbour group sits in
       // another wavefront; load its element directly (in bounds: c > 0 means
-      // x0 - 1 >= 0, c < L - 1 means x0 + V <= nx - 1)
+      // x0 - 1 >= 0, c < L - 1 means x0 + V <= px - 1)
       if (lane == 0 && c != 0) {
 #pragma unroll
         for (int i = 0; i < Q; i++) {
@@ -1285,7 +1277,6 @@ __device__ __forceinline__ void tile_rows(const LbArgs& A, const BoxDesc& b, con
           dither_node(((unsigned)z * (unsigned)ny + (unsigned)y) * (unsigned)nx + (unsigned)x, (unsigned)step);
 #pragma unroll
       for (int i = 0; i < Q; i++) {
-        const float ke = WCLS[i] == 0 ? ec0 : (WCLS[i] == 1 ? ec1 : ec2);
         vput_keep<S, W>(out[i], k, d[i], dither_pop(hn, i));
       }
     }
@@ -1563,6 +1554,12 @@ __device__ __forceinline__ void row_nodes_aa(const LbArgs& A, const BoxDesc& b, 
 // where that spills: body force (EXT 1) 296 us at two and 271 at three, thermal
 // noise (EXT 2) 354 and 332, at 36-56 bytes per lane.  FP64 with a body force
 // takes 1337 us at two and 1373 at three.
+// Periodic boxes follow the same line; eight of 96^3, us per step at 2 / 3 / 4:
+//             two buffers                     in place
+//          MRT, ghost 1  MRT, 1.4     BGK     MRT, ghost 1  MRT, 1.4     BGK
+//   FP64   434 433 433   429 429 437  424 442 791   455 454 455  448 448 468  443 468 674
+//   FP32   220 220 220   220 220 220  220 220 220   229 229 229  231 231 231  233 233 232
+//   FP16   161 161 162   164 164 163  189 189 172   137 138 137  145 145 145  161 161 158
 // Noise is a kernel of its own because a branch per node on it in one kernel
 // holds both arms' registers: at three waves 100-980 bytes spilled, up to 1.8
 // times the time.
@@ -1715,12 +1712,6 @@ __global__ __launch_bounds__(BS, lb_min_waves(S)) void k_lb(LbArgs A) {
   }
 }
 
-// ----------------------------------------------------------- x-face velocities
-// Before the fused step: the boundary velocity u_b(y, t_n) of every x-face node
-// of the interior rows of the row boxes (faces -x and +x, interior y and z), so
-// that the row lanes that own those nodes read three floats instead of
-// evaluating the boundary source with dependent loads.  Node k of a box:
-// k = side (ny-2)(nz-2) + (z-1)(ny-2) + (y-1), velocity at xface[xf_off + 3k].
 // ------------------------------------------------------------ chain forcing
 // With two buffers the chains couple to the fluid in a pass of their own,
 // right after the fused step: the interior nodes of each chain's stencil box
@@ -1765,41 +1756,39 @@ __global__ __launch_bounds__(WG) void k_force(LbArgs A) {
   const int lx = bb[3] - bb[0] + 1, ly = bb[4] - bb[1] + 1, lz = bb[5] - bb[2] + 1;
   const int n = (lx > 0 && ly > 0 && lz > 0) ? lx * ly * lz : 0;
   if (part > 0 && part * WG >= n) return;  // takes no ticket
-  {
-    const int par = (int)(step & 1);
-    const T* __restrict__ src = (const T*)(par ? A.a1 : A.a0) + b.off;
-    T* __restrict__ dst = (T*)(par ? A.a0 : A.a1) + b.off;
-    const R rho0 = (R)A.rho0, omega = (R)A.omega, omb = (R)A.om_bulk, omg = (R)A.om_ghost;
-    const R sc = (R)b.s2;
-    const unsigned long long all =
-        b.chain_count >= MAX_BOX_CHAINS ? ~0ull : (1ull << b.chain_count) - 1ull;
+  const int par = (int)(step & 1);
+  const T* __restrict__ src = (const T*)(par ? A.a1 : A.a0) + b.off;
+  T* __restrict__ dst = (T*)(par ? A.a0 : A.a1) + b.off;
+  const R rho0 = (R)A.rho0, omega = (R)A.omega, omb = (R)A.om_bulk, omg = (R)A.om_ghost;
+  const R sc = (R)b.s2;
+  const unsigned long long all =
+      b.chain_count >= MAX_BOX_CHAINS ? ~0ull : (1ull << b.chain_count) - 1ull;
 #pragma unroll 1
-    for (unsigned q = part * WG + threadIdx.x; q < (unsigned)n; q += parts * WG) {
-      const int p = (int)q;
-      int x = bb[0] + p % lx, y = bb[1] + (p / lx) % ly, z = bb[2] + p / (lx * ly);
-      if (PER) {  // a stencil box may wrap on periodic axes
-        if ((b.pmask & 1) && x >= b.nx) x -= b.nx;
-        if ((b.pmask & 2) && y >= b.ny) y -= b.ny;
-        if ((b.pmask & 4) && z >= b.nz) z -= b.nz;
-      }
-      if (!is_interior(b, x, y, z)) continue;
-      R d[Q];
-      load_pre<S, PER>(src, b, x, y, z, A.pre != 0, d);
-      R gx = 0, gy = 0, gz = 0;
-      gather_force<R, PER, 4>(A, b, all, x, y, z, gx, gy, gz);
-      if constexpr (EXT != 0) {
-        // the same body force and noise k_lb gave the node (same counter)
-        Ext<R> ext = make_ext<R>(A, b, step);
-        ext.node = (unsigned)(((int64_t)z * b.ny + y) * b.nx + x);
-        collide_ext<R, COLL, EXT, comp_weights<S>(), S == 2>(d, gx, gy, gz, rho0, omega, omb, omg, ext, sc);
-      } else {
-        collide_any<R, COLL, comp_weights<S>(), S == 2>(d, gx, gy, gz, rho0, omega, omb, omg, sc);
-      }
-      const unsigned hn = dither_node((unsigned)(((int64_t)z * b.ny + y) * b.nx + x), (unsigned)step);
-#pragma unroll
-      for (int i = 0; i < Q; i++)
-        dst[aidx(b, i, x, y, z)] = St::keep(d[i], dither_pop(hn, i));
+  for (unsigned q = part * WG + threadIdx.x; q < (unsigned)n; q += parts * WG) {
+    const int p = (int)q;
+    int x = bb[0] + p % lx, y = bb[1] + (p / lx) % ly, z = bb[2] + p / (lx * ly);
+    if (PER) {  // a stencil box may wrap on periodic axes
+      if ((b.pmask & 1) && x >= b.nx) x -= b.nx;
+      if ((b.pmask & 2) && y >= b.ny) y -= b.ny;
+      if ((b.pmask & 4) && z >= b.nz) z -= b.nz;
     }
+    if (!is_interior(b, x, y, z)) continue;
+    R d[Q];
+    load_pre<S, PER>(src, b, x, y, z, A.pre != 0, d);
+    R gx = 0, gy = 0, gz = 0;
+    gather_force<R, PER, 4>(A, b, all, x, y, z, gx, gy, gz);
+    if constexpr (EXT != 0) {
+      // the same body force and noise k_lb gave the node (same counter)
+      Ext<R> ext = make_ext<R>(A, b, step);
+      ext.node = (unsigned)(((int64_t)z * b.ny + y) * b.nx + x);
+      collide_ext<R, COLL, EXT, comp_weights<S>(), S == 2>(d, gx, gy, gz, rho0, omega, omb, omg, ext, sc);
+    } else {
+      collide_any<R, COLL, comp_weights<S>(), S == 2>(d, gx, gy, gz, rho0, omega, omb, omg, sc);
+    }
+    const unsigned hn = dither_node((unsigned)(((int64_t)z * b.ny + y) * b.nx + x), (unsigned)step);
+#pragma unroll
+    for (int i = 0; i < Q; i++)
+      dst[aidx(b, i, x, y, z)] = St::keep(d[i], dither_pop(hn, i));
   }
   // On steps without a check pass (advance set) the last workgroup to take a
   // ticket ends the step instead of a separate launch: every workgroup has
@@ -1822,6 +1811,12 @@ __global__ __launch_bounds__(WG) void k_force(LbArgs A) {
   }
 }
 
+// ----------------------------------------------------------- x-face velocities
+// Before the fused step: the boundary velocity u_b(y, t_n) of every x-face node
+// of the interior rows of the row boxes (faces -x and +x, interior y and z), so
+// that the row lanes that own those nodes read three floats instead of
+// evaluating the boundary source with dependent loads.  Node k of a box:
+// k = side (ny-2)(nz-2) + (z-1)(ny-2) + (y-1), velocity at xface[xf_off + 3k].
 constexpr int XF_NODES = 4;  // x-face nodes per lane
 constexpr int XF_ITEM = XF_NODES * 64;  // nodes per x-face work item (one wavefront)
 

@@ -819,7 +819,8 @@ lb_status upload_chains(lb_ctx* ctx) {
   HIPCHK(dzero(ctx, ctx->d_rec_base, nbd * sizeof(int4)));
   HIPCHK(dzero(ctx, ctx->d_rec_d, 3 * nbd * rb));
   HIPCHK(dzero(ctx, ctx->d_rec_dp, 3 * nbd * rb));
-  // chain kernel: one wavefront per chain when every chain fits in one
+  // chain kernel: 512 threads a chain where no chain has more than 64 beads (the
+  // substeps in one wavefront), else 1,024
   int max_nb = 0;
   for (auto& c : ctx->ch) max_nb = std::max(max_nb, c.p.n_beads);
   const bool th = ctx->kT > 0.0;

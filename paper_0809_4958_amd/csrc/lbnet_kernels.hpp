@@ -50,10 +50,6 @@ constexpr int CH = 64;      // hidden channels
 constexpr int COUT = 16;    // output channels of the last layer (3 used)
 constexpr int RCH = 4;      // of them kept of the network output r and its gradient dy
 constexpr int NTAP = 9;
-#ifndef LBN_KEEP23
-#define LBN_KEEP23 true
-#endif
-constexpr bool KEEP23 = LBN_KEEP23;
 
 __device__ __forceinline__ __bf16 to_bf16(float v) { return (__bf16)v; }  // round to nearest even
 __device__ __forceinline__ float from_bf16(__bf16 v) { return (float)v; }
@@ -226,15 +222,13 @@ __device__ __forceinline__ void store_pixel(const float (&v)[NC], size_t p, int 
 
 // The products of one tile row for a wave: 32 pixels (px0 ..) of output row
 // y against all CO output slots of the staged weights, K = 9 CI in chunks of
-// 32 (with PF, the fragments of the next two chunks load while a chunk
-// multiplies; with KEEP_ORDER, the compiler may not move those loads down to
-// their use, which it otherwise does: measured faster in the backward pass
-// and the forward's last layer, not in its 64 -> 64 layer).  The input
-// row y + dy starts at LDS pixel row_at[dy + 1] (rows of IMG + 2 pixels, zero
+// 32 (with PF, in the 64 -> 64 layer and its backward pass, the fragments of the
+// next two chunks load while a chunk multiplies, and the compiler may not move
+// those loads down to their use, which it otherwise does).  The input row y + dy starts at LDS pixel row_at[dy + 1] (rows of IMG + 2 pixels, zero
 // halo).
-template <int CI, int CO, bool PF = true, int MB = 2, int NBK = CO / 16, bool KEEP_ORDER = false>
+template <int CI, int CO, bool PF, int MB = 2, int NBK = CO / 16>
 __device__ __forceinline__ void conv_products(const __bf16* sx, const __bf16* sw, const int (&row_at)[3], int px0,
-                                              int lane, f32x4 (&acc)[MB][NBK], int nb0 = 0) {
+                                              int lane, f32x4 (&acc)[MB][NBK]) {
   constexpr int KCH = (NTAP * CI + 31) / 32;
 #pragma unroll
   for (int mb = 0; mb < MB; mb++)
@@ -253,7 +247,7 @@ __device__ __forceinline__ void conv_products(const __bf16* sx, const __bf16* sw
     }
 #pragma unroll
     for (int nb = 0; nb < NBK; nb++) {
-      const int slot = 16 * (nb0 + nb) + (lane & 15);
+      const int slot = 16 * nb + (lane & 15);
       bb[nb] = kv ? *(const bf16x8*)&sw[lds_at<CI>(tap * CO + slot, ci >> 3)] : bf16x8{};
     }
   };
@@ -272,7 +266,7 @@ __device__ __forceinline__ void conv_products(const __bf16* sx, const __bf16* sw
 #pragma unroll
     for (int kc = 0; kc < KCH; kc++) {
       if (kc + 2 < KCH) frag(kc + 2, fa[(kc + 2) % 3], fb[(kc + 2) % 3]);
-      if constexpr (KEEP_ORDER) __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_sched_barrier(0);
       mult(fa[kc % 3], fb[kc % 3]);
     }
   } else {
@@ -501,7 +495,7 @@ __global__ __launch_bounds__(NBC) void k_conv23(const __bf16* __restrict__ a1, c
       const int y = ya + r2;  // layer-2 row of this wave
       const int row_at[3] = {((y + RING - 1) % RING) * RW, ((y + RING) % RING) * RW, ((y + RING + 1) % RING) * RW};
       f32x4 acc[2][4];
-      conv_products<C, C, true, 2, 4, KEEP23>(s_a1, s_w2, row_at, px2, lane, acc, 0);
+      conv_products<C, C, true>(s_a1, s_w2, row_at, px2, lane, acc);
       __syncthreads();  // every product of the step and every read of s_p is done
       if (st + 1 < nsteps) {
         put_rows(ya + SR4 + 1, 0);  // into the slots of rows ya - 1 .. ya + 2
@@ -664,7 +658,7 @@ __global__ __launch_bounds__(NBC) void k_back32(const __bf16* __restrict__ dy, c
       bf16x8 mv[2][2];
       mask_load(mv, a1, y);
       f32x4 acc[2][4];
-      conv_products<C, C, true, 2, 4, true>(s_dz, s_wb, row_at, px0, lane, acc, 0);
+      conv_products<C, C, true>(s_dz, s_wb, row_at, px0, lane, acc);
 #pragma unroll
       for (int mb = 0; mb < 2; mb++)
 #pragma unroll
