@@ -84,9 +84,11 @@ typedef enum { LB_STORE_F64 = 0, LB_STORE_F32 = 1, LB_STORE_F16DEV = 2 } lb_stor
  * an odd step reads those from the neighbours and writes f*_i into slot i of
  * node x + c_i, where the next even step finds the next pre-collision state
  * in place.  Every slot is read and written by one node only, so no step needs
- * a second buffer.  The same arithmetic as LB_STREAM_AB, bit for bit on tile
- * boxes; in-place contexts gather the chains' spread force inside the fused
- * step, and have no autotuner. */
+ * a second buffer.  The same arithmetic as LB_STREAM_AB, on tile and row items
+ * alike; the kernels are compiled apart, and a fused multiply-add may round
+ * another way in FP32 and FP64 (half-precision stores hardly ever show it).
+ * In-place contexts gather the chains' spread force inside the fused step, and
+ * have no autotuner. */
 typedef enum { LB_STREAM_AB = 0, LB_STREAM_AA = 1 } lb_streaming;
 
 typedef struct {
