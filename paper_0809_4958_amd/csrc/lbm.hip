@@ -416,6 +416,12 @@ void set_shape(BoxHost& b, int ex, int ey, int ez) {
 // 13.1 / 13.1 / 13.1, 96^3 periodic FP32 48 / 24.6 / 24.0 / 24.0, 128^3 FP32
 // 69.7 / 70.2 / 66.9 / 66.8, four 121^3 FP32 380 / 380 / 346 / 323; contexts
 // of 35 million nodes and more keep the default items.
+// FP16 row items carry more arithmetic per iteration and lose by being cut from
+// 4 million nodes on, so theirs are half as large again, to the nearest whole
+// iteration: 64^3 boxes with 1, 2, 3 and 4 iterations, us, 16 boxes 83 / 80 / 80 /
+// 86, 32 boxes 156 / 141 / 137 / 142 (in place 185 / 166 / 159 / 162), 64 boxes
+// 304 / 263 / 256 / 257; eight 96^3 boxes 133 / 121 / 127 / 128.  FP32 of the same
+// sizes 122 / 118 / 120 / 123, 239 / 227 / 231 / 234, 461 / 439 / 445 / 454.
 constexpr int SPLIT_ITEMS = 4096;
 void split_small(lb_ctx* ctx) {
   int64_t work = 0;
@@ -424,7 +430,8 @@ void split_small(lb_ctx* ctx) {
   for (auto& b : ctx->bx) {
     if (b.vec) {
       const int64_t iter = (int64_t)WG * row_nodes(ctx->S, b.vw);
-      set_shape(b, b.ex, b.ey, (int)std::max<int64_t>(1, std::min<int64_t>(b.ez, per / iter)));
+      const int64_t n = ctx->S == LB_STORE_F16DEV ? (3 * per + iter) / (2 * iter) : per / iter;
+      set_shape(b, b.ex, b.ey, (int)std::max<int64_t>(1, std::min<int64_t>(b.ez, n)));
     } else {
       while (b.ez > 1 && 2 * (int64_t)b.ex * b.ey * b.ez > 3 * per) b.ez = (b.ez + 1) / 2;
       if (2 * (int64_t)b.ex * b.ey > 3 * per) b.ey = std::max(1, std::min(b.ey, WG / b.ex));
