@@ -155,12 +155,15 @@ int pick_row_words(int storage, int nx) {
 // so short that x = 0 and x = nx - 1 would share a lane vector).  Rows may be
 // padded: a step costs least per stored node when rows are multiples of 64
 // bytes, a little more when lane groups then straddle wavefronts, and a fifth
-// to two fifths more otherwise, so the pitch with the least nodes times
+// to a third more otherwise, so the pitch with the least nodes times
 // that factor is taken.  Measured ns per interior node (boxes of nx x 96 x 96,
 // pitch in brackets): FP16 nx = 60 0.0228 [60] 0.0174 [64], 100 0.0232 [100]
 // 0.0221 [104] 0.0201 [128], 121 0.0235 [136] 0.0169 [128], 45 0.0208 [48]
 // 0.0233 [64], 150 0.0213 [152] 0.0184 [160]; FP32 50 0.0456 [50] 0.0355
 // [64], 121 0.0410 [124] 0.0289 [128], 130 0.0397 [130] 0.0343 [144] 0.0358 [160].
+// The last factor is the ratio at the rows nearest to even: FP16 42 nodes in
+// their own pitch or in 48 598 and 648 us (78 boxes), FP32 21 in 21 or 24 1129 and
+// 1218 us (155 boxes).
 int row_pitch(int storage, int nx) {
   if (storage == LB_STORE_F64 || nx <= row_nodes(storage, 2)) return 0;
   const int sb = (int)store_bytes(storage), unit = 16 / sb;
@@ -172,7 +175,7 @@ int row_pitch(int storage, int nx) {
     const bool whole = whole_wave_rows(storage, px, w);
     const double cost = px * (px * sb % 64 == 0 ? (whole ? 1.0 : 1.08)
                               : px % unit == 0  ? (whole ? 1.2 : 1.32)
-                                                : 1.4);
+                                                : 1.36);
     if (!best || cost < least) {
       best = px;
       least = cost;
