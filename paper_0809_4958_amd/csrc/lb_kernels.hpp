@@ -1898,22 +1898,26 @@ __global__ __launch_bounds__(WG) void k_check(LbArgs A) {
   // move it on, an in-place odd step left it in place
   const int mv = A.aa ? ((step & 1) ? 0 : -1) : 1;
   const int dir = A.aa && !(step & 1) ? -1 : 1;
-  if (!PER && b.px % 8 == 0) {
-    // chunks of 8 consecutive nodes of a row, every population read as
+  // chunks of CN nodes of a row: in FP64 four, because eight hold 336 registers,
+  // one wave per SIMD, also in the node-by-node walk below (what a check adds to
+  // a step of a 206^3 box 491 us, with four 344)
+  constexpr int CN = S == 0 ? 4 : 8;
+  if (!PER && b.px % CN == 0) {
+    // CN consecutive nodes of a row, every population read as
     // 16-byte vectors (rows start 16-byte aligned: box offsets are multiples
-    // of 128 elements and 8 nodes span 16 bytes or a multiple of it; a chunk
+    // of 128 elements and CN nodes span 16 bytes or a multiple of it; a chunk
     // may end in pad nodes, whose targets are never interior).  The
     // node's own populations are always inside the box, so all of them are
     // loaded before any is tested (no load waits behind a branch); selects,
     // not products, drop the ones that stream out of the fluid, so that
     // whatever a boundary node holds in them never enters a sum.
-    constexpr int NV = 8 * (int)sizeof(T) / 16;
-    const int cpr = (b.nx + 7) / 8;
+    constexpr int NV = CN * (int)sizeof(T) / 16;
+    const int cpr = (b.nx + CN - 1) / CN;
     const int n_chunks = (cw.z - cw.y) * cpr;
     for (int p = tid; p < n_chunks; p += WG) {
       const int r = p / cpr, c = p - r * cpr, row = cw.y + r;
       const int z = row / b.ny, y = row - z * b.ny;
-      const int x0 = 8 * c;
+      const int x0 = CN * c;
       uint4 raw[Q][NV];
 #pragma unroll
       for (int i = 0; i < Q; i++) {
@@ -1928,7 +1932,7 @@ __global__ __launch_bounds__(WG) void k_check(LbArgs A) {
         const T* v = (const T*)raw[i];
         double sum = 0.0;
 #pragma unroll
-        for (int k = 0; k < 8; k++) {
+        for (int k = 0; k < CN; k++) {
           const int tx = x0 + k + mv * CX[i];
           const double d = (double)St::dec(v[k], b.dec[WCLS[i]]);
           sum += (tx >= 1 && tx <= b.nx - 2) ? d : 0.0;

@@ -625,14 +625,18 @@ lb_status build_tables(lb_ctx* ctx, int grid_override) {
   ctx->d_items = dalloc_t<Item>(ctx, items.size(), &ok);
   ctx->d_order = dalloc_t<int>(ctx, order.size(), &ok);
   // mass/momentum check work list: ranges of rows, about 1/128 of a box each
-  // within 4k..64k nodes (of the box alone, so that its record does not depend
-  // on its batch).  Slabs of 64k nodes were 14 workgroups on a 96^3 box: 674 us.
+  // within 4k..8k nodes, 1/2048 of larger boxes up to 64k (of the box alone, so
+  // that its record does not depend on its batch).  Slabs of 64k nodes were 14
+  // workgroups on a 96^3 box: 674 us.  Ranges of up to 64k nodes were 133 on a
+  // 206^3 box, fewer than its planes: a check step of it cost 130 us in FP16 and
+  // 660 in FP32 with periodic axes, so 83 and 201 (whole planes 527 and 438).
   std::vector<int4> check;
   std::vector<int> check_off(ctx->bx.size() + 1, 0);
   for (size_t bi = 0; bi < ctx->bx.size(); bi++) {
     const BoxHost& b = ctx->bx[bi];
     check_off[bi] = (int)check.size();
-    const int64_t nodes = std::max<int64_t>(4096, std::min<int64_t>(65536, b.nn / 128));
+    const int64_t most = std::max<int64_t>(8192, std::min<int64_t>(65536, b.nn / 2048));
+    const int64_t nodes = std::max<int64_t>(4096, std::min(most, b.nn / 128));
     const int rows = b.dim.ny * b.dim.nz, rc = (int)std::max<int64_t>(1, nodes / b.dim.nx);
     for (int r = 0; r < rows; r += rc) check.push_back(make_int4((int)bi, r, std::min(rows, r + rc), 0));
   }
