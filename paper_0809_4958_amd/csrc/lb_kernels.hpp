@@ -20,6 +20,8 @@
 //             momentum at t_{n+1} from the arena k_lb wrote; k_finalize
 //             (lb_io_kernels.hpp) adds them per box.
 #pragma once
+#include <type_traits>
+
 #include "lb_device.hpp"
 
 namespace lbdev {
@@ -1898,30 +1900,28 @@ __global__ __launch_bounds__(WG) void k_check(LbArgs A) {
   // move it on, an in-place odd step left it in place
   const int mv = A.aa ? ((step & 1) ? 0 : -1) : 1;
   const int dir = A.aa && !(step & 1) ? -1 : 1;
-  // chunks of CN nodes of a row: in FP64 four, because eight hold 336 registers,
-  // one wave per SIMD, also in the node-by-node walk below (what a check adds to
-  // a step of a 206^3 box 491 us, with four 344)
-  constexpr int CN = S == 0 ? 4 : 8;
-  if (!PER && b.px % CN == 0) {
-    // CN consecutive nodes of a row, every population read as
-    // 16-byte vectors (rows start 16-byte aligned: box offsets are multiples
-    // of 128 elements and CN nodes span 16 bytes or a multiple of it; a chunk
-    // may end in pad nodes, whose targets are never interior).  The
-    // node's own populations are always inside the box, so all of them are
-    // loaded before any is tested (no load waits behind a branch); selects,
-    // not products, drop the ones that stream out of the fluid, so that
-    // whatever a boundary node holds in them never enters a sum.
-    constexpr int NV = CN * (int)sizeof(T) / 16;
+  // Chunks of CN consecutive nodes of a row, every population read as vectors of
+  // up to 16 bytes (CN divides the pitch and box offsets are multiples of 128
+  // elements, so they are aligned; a chunk may end in pad nodes, whose targets are
+  // never interior).  The node's own populations are always inside the box, so
+  // all of them are loaded before any is tested (no load waits behind a branch);
+  // selects, not products, drop the ones that stream out of the fluid, so that
+  // whatever a boundary node holds in them never enters a sum.
+  auto chunks = [&](auto width) {
+    constexpr int CN = decltype(width)::value;
+    constexpr int LB = CN * (int)sizeof(T) < 16 ? CN * (int)sizeof(T) : 16;  // bytes of a load
+    constexpr int NV = CN * (int)sizeof(T) / LB;
+    typedef unsigned Vec __attribute__((ext_vector_type(LB / 4)));
     const int cpr = (b.nx + CN - 1) / CN;
     const int n_chunks = (cw.z - cw.y) * cpr;
     for (int p = tid; p < n_chunks; p += WG) {
       const int r = p / cpr, c = p - r * cpr, row = cw.y + r;
       const int z = row / b.ny, y = row - z * b.ny;
       const int x0 = CN * c;
-      uint4 raw[Q][NV];
+      Vec raw[Q][NV];
 #pragma unroll
       for (int i = 0; i < Q; i++) {
-        const uint4* src = (const uint4*)(arena + aidx(b, i, x0, y, z));
+        const Vec* src = (const Vec*)(arena + aidx(b, i, x0, y, z));
 #pragma unroll
         for (int q = 0; q < NV; q++) raw[i][q] = src[q];
       }
@@ -1944,6 +1944,18 @@ __global__ __launch_bounds__(WG) void k_check(LbArgs A) {
         if (CZ[i]) acc[3] += dir * CZ[i] * sum;
       }
     }
+  };
+  // The widest chunk that divides the pitch.  In FP64 four nodes at most, because
+  // eight hold 336 registers, one wave per SIMD, also in the node-by-node walk
+  // below (what a check adds to a step of a 206^3 box 491 us, with four 344).
+  // Pairs and fours serve rows kept at their own length (FP16, a 68 x 62 x 7 box and
+  // a smaller one: 7 us by fours, 21 node by node).
+  if (!PER && S != 0 && b.px % 8 == 0) {
+    chunks(std::integral_constant<int, S != 0 ? 8 : 4>{});
+  } else if (!PER && b.px % 4 == 0) {
+    chunks(std::integral_constant<int, 4>{});
+  } else if (!PER && b.px % 2 == 0) {
+    chunks(std::integral_constant<int, 2>{});
   } else {
     // node by node (32-bit indices); loads first and selects after, as above
     const int n_slab = (cw.z - cw.y) * b.nx;

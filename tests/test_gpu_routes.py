@@ -661,10 +661,11 @@ def test_rows_are_padded_where_that_is_faster(storage, nx, padded, torch_allocs)
 
 
 @pytest.mark.parametrize("storage,tol", [("f64", 1e-13), ("f32", 1e-6), ("f16", 1e-5)])
-@pytest.mark.parametrize("dims", [(12, 31, 40), (44, 30, 26), (206, 70, 130)])
+@pytest.mark.parametrize("dims", [(12, 31, 40), (44, 30, 26), (206, 70, 130), (42, 11, 13), (66, 9, 8), (68, 7, 9),
+                                  (34, 8, 11), (21, 12, 10)])
 def test_check_record_of_short_chunks_and_capped_ranges(dims, storage, tol):
-    """FP64 rows of whole four-node chunks but not eight, and a box whose row
-    ranges are capped, against the sums of the oracle's populations in extended
+    """Rows of whole four- and two-node chunks but not eight, single nodes, and a
+    box whose row ranges are capped, against the sums of the oracle's populations in extended
     precision (its own running sum of 34 million terms is 1.2e-13 off them)."""
     rng = np.random.default_rng(37)
     case = Case(dims, collision=oracle.MRT, tau=0.7,
