@@ -764,7 +764,7 @@ template <typename R, int COLL, int EXT, bool CW = false, bool WS = false>
 __device__ __forceinline__ void collide_ext(R d[Q], R gx, R gy, R gz, R rho0, R omega, R omb,
                                             R omg, const Ext<R>& e, R sc = R(1)) {
   if constexpr (COLL != 0) {
-    collide_mrt_pairs<R, COLL == 2, EXT == 2, CW, WS, true>(d, gx, gy, gz, rho0, omega, omb, omg, &e, sc);
+    collide_mrt_pairs<R, COLL == 2, EXT == 2, CW, WS, sizeof(R) == 4>(d, gx, gy, gz, rho0, omega, omb, omg, &e, sc);
   } else {
     static_assert(EXT == 1, "thermal noise acts on the modes of the MRT collision");
     R drho = 0;
