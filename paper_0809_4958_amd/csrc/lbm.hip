@@ -161,12 +161,15 @@ int pick_row_words(int storage, int nx) {
 // 0.0221 [104] 0.0201 [128], 121 0.0235 [136] 0.0169 [128], 45 0.0208 [48]
 // 0.0233 [64], 150 0.0213 [152] 0.0184 [160]; FP32 50 0.0456 [50] 0.0355
 // [64], 121 0.0410 [124] 0.0289 [128], 130 0.0397 [130] 0.0343 [144] 0.0358 [160].
-// The last factor is the ratio at the rows nearest to even: FP16 42 nodes in
-// their own pitch or in 48 598 and 648 us (78 boxes), FP32 21 in 21 or 24 1129 and
-// 1218 us (155 boxes).
-int row_pitch(int storage, int nx) {
+// The last factor decides for 42 FP16 and 21 FP32 nodes, in 42 or 48 and in 21 or
+// 24 (us a step, boxes of nx x 96 x 96): 78 FP16 boxes on two buffers 609 and 653, in
+// place 792 and 638, one of 42 x 46 x 73 17.6 and 17.4; 155 FP32 boxes 1148 and
+// 1236, in place 1539 and 1229, 16 of 21 x 45 x 79 51.7 and 51.8, 4 of them 21.6 and
+// 20.0.  It asks for nothing but the box, so that its sums do not depend on its batch.
+int row_pitch(int storage, int nx, bool in_place) {
   if (storage == LB_STORE_F64 || nx <= row_nodes(storage, 2)) return 0;
   const int sb = (int)store_bytes(storage), unit = 16 / sb;
+  const double unaligned = storage == LB_STORE_F16DEV && !in_place ? 1.36 : 1.4;
   int best = 0;
   double least = 0.0;
   auto consider = [&](int px) {
@@ -175,7 +178,7 @@ int row_pitch(int storage, int nx) {
     const bool whole = whole_wave_rows(storage, px, w);
     const double cost = px * (px * sb % 64 == 0 ? (whole ? 1.0 : 1.08)
                               : px % unit == 0  ? (whole ? 1.2 : 1.32)
-                                                : 1.36);
+                                                : unaligned);
     if (!best || cost < least) {
       best = px;
       least = cost;
@@ -1093,7 +1096,7 @@ void row_layout(const lb_ctx* ctx, BoxHost& b, Rows rows) {
   b.ylog = 0;
   b.xf_off = -1;
   b.vec = false;
-  const int px = rows == ROWS_PADDED ? row_pitch(ctx->S, nx) : (ctx->S == LB_STORE_F64 ? 0 : nx);
+  const int px = rows == ROWS_PADDED ? row_pitch(ctx->S, nx, ctx->aa) : (ctx->S == LB_STORE_F64 ? 0 : nx);
   b.vw = px ? pick_row_words(ctx->S, px) : 0;
   const int V = b.vw ? row_nodes(ctx->S, b.vw) : 1;
   // interleave Y = 2^ylog lines per population row so that a row of a block
